@@ -646,7 +646,7 @@ gdn_status gdn_nearest(gdn_ctx* ctx, const float* a, int64_t na, const float* b,
     if (workspace_bytes < gdn::nearest_workspace_bytes((uint32_t)na))
         return fail(ctx, GDN_ENOMEM, "workspace too small");
     DeviceGuard guard(ctx->device);
-    gdn::launch_nearest(a, (uint32_t)na, b, (uint32_t)nb, workspace, idx, d2, (hipStream_t)stream);
+    gdn::launch_nearest(a, (uint32_t)na, b, (uint32_t)nb, workspace, workspace_bytes, idx, d2, (hipStream_t)stream);
     hipError_t he = hipGetLastError();
     if (he != hipSuccess) return fail(ctx, GDN_EHIP, hipGetErrorString(he));
     ctx->err.clear();
@@ -670,10 +670,10 @@ gdn_status gdn_eval_metrics(gdn_ctx* ctx, const float* clean, int64_t nc, const 
     if (e != GDN_OK) return e;
     if (!clean || !den || !workspace || !out) return fail(ctx, GDN_EINVAL, "NULL argument");
     if (((uintptr_t)workspace & 255u) != 0) return fail(ctx, GDN_EINVAL, "workspace must be 256-byte aligned");
-    if (workspace_bytes < gdn::eval_workspace_bytes((uint32_t)nc, (uint32_t)nd))
+    if (workspace_bytes < gdn::eval_min_workspace_bytes((uint32_t)nc, (uint32_t)nd))
         return fail(ctx, GDN_ENOMEM, "workspace too small");
     DeviceGuard guard(ctx->device);
-    gdn::launch_eval(clean, (uint32_t)nc, den, (uint32_t)nd, workspace, out, (hipStream_t)stream);
+    gdn::launch_eval(clean, (uint32_t)nc, den, (uint32_t)nd, workspace, workspace_bytes, out, (hipStream_t)stream);
     hipError_t he = hipGetLastError();
     if (he != hipSuccess) return fail(ctx, GDN_EHIP, hipGetErrorString(he));
     ctx->err.clear();

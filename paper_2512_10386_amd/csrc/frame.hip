@@ -3,6 +3,7 @@
 // the stable LSD radix sort of (key, original index) on the digits the octree
 // needs, and the whole-key re-sort of deep level-10 cells.
 #include "kernels.hpp"
+#include "radix.hpp"
 
 namespace gdn {
 
@@ -449,13 +450,26 @@ void launch_morton(const Plan& P, const Params& prm, const float* xyz, hipStream
 
 // ---------------------------------------------------------------- radix sort
 
-// One stable LSD pass over digit `pass` (8 bits) in the onesweep style: local
-// ranks by wave-level digit matching, digit offsets of earlier tiles by
-// decoupled look-back (bounded waits), global digit bases from the histogram.
-// Passes past the key's 8 take the digit from the frame of the payload (the
-// original index, found in the frame offsets), so a batch ends sorted by
-// (frame, key bits 32..62, index); only passes from SORT_SHORT_FIRST on are
-// launched.
+// Digit `pass` of the frame sort. Passes past the key's 8 take the digit from
+// the frame of the payload (the original index, found in the frame offsets),
+// so a batch ends sorted by (frame, key bits 32..62, index); only passes from
+// SORT_SHORT_FIRST on are launched.
+struct FrameDigit {
+    int pass;
+    const uint32_t* foff;    // frame offsets in memory
+    const uint32_t* s_foff;  // the same staged in LDS, if `lds`
+    bool lds;
+    uint32_t nf;
+    __device__ bool of_key() const { return pass < SORT_PASSES; }
+    __device__ uint32_t key_digit(uint64_t k) const { return (uint32_t)((k >> (8 * pass)) & 255u); }
+    __device__ uint32_t operator()(uint64_t k, uint32_t v, bool ok) const {
+        if (of_key()) return key_digit(k);
+        v = ok ? v : 0u;
+        const uint32_t f = lds ? frame_of(s_foff, nf, v) : frame_of(foff, nf, v);
+        return (f >> (8 * (pass - SORT_PASSES))) & 255u;
+    }
+};
+
 template <int ITEMS>
 __global__ __launch_bounds__(SORT_BLOCK) void radix_pass_kernel(const uint64_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
@@ -465,181 +479,13 @@ __global__ __launch_bounds__(SORT_BLOCK) void radix_pass_kernel(const uint64_t* 
                                                                 uint32_t* status, uint32_t* dev_status,
                                                                 const uint32_t* __restrict__ foff,
                                                                 uint32_t nf) {
-    __shared__ uint32_t s_w[SORT_BLOCK / 64][256];
-    __shared__ uint32_t s_base[256];
-    __shared__ uint32_t s_scan[SORT_BLOCK / 64 + 1];
     __shared__ uint32_t s_foff[SORT_FOFF_LDS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int shift = 8 * pass;
-    // this digit's total over the pass, needed only after the ranking: read first
-    const uint32_t hv = hist[tid];
     // frame passes of batches with few frames search the offsets in LDS
     const bool foff_lds = pass >= SORT_PASSES && nf < SORT_FOFF_LDS;
     if (foff_lds)
-        for (uint32_t i = tid; i <= nf; i += SORT_BLOCK) s_foff[i] = foff[i];
-    for (int i = tid; i < (SORT_BLOCK / 64) * 256; i += SORT_BLOCK) (&s_w[0][0])[i] = 0u;
-
-    uint64_t key[ITEMS];
-    uint32_t val[ITEMS], dig[ITEMS], rank[ITEMS];
-    auto load_tile = [&](uint32_t tl) {
-        const uint32_t tb = tl * (SORT_BLOCK * ITEMS) + wave * (64 * ITEMS);
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const uint32_t pos = tb + i * 64 + lane;
-            const bool ok = pos < n;
-            key[i] = ok ? kin[pos] : 0ull;
-            val[i] = ok ? vin[pos] : 0u;
-        }
-    };
-    // Tile = workgroup index. Each XCD starts its workgroups in index order,
-    // so every tile a look-back waits on has been started and only waits on
-    // lower tiles in turn; the waits are bounded anyway (SPIN_LIMIT, then a
-    // status bit). A tile counter taken with an atomic cost a round trip
-    // before the loads, and on large inputs, where the workgroups that start
-    // together race for it, a second load of the tile.
-    load_tile(blockIdx.x);
-    __syncthreads();
-    const uint32_t tile = blockIdx.x;
-    const uint32_t tbase = tile * (SORT_BLOCK * ITEMS) + wave * (64 * ITEMS);
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        uint32_t pos = tbase + i * 64 + lane;
-        bool ok = pos < n;
-        uint32_t d;
-        if (pass < SORT_PASSES) {
-            d = (uint32_t)((key[i] >> shift) & 255u);
-        } else {
-            const uint32_t v = ok ? val[i] : 0u;
-            const uint32_t f = foff_lds ? frame_of(s_foff, nf, v) : frame_of(foff, nf, v);
-            d = (f >> (8 * (pass - SORT_PASSES))) & 255u;
-        }
-        dig[i] = ok ? d : 256u;
-    }
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const uint32_t d = dig[i];
-        const bool ok = d < 256u;
-        uint64_t m = __ballot(ok);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            bool bit = (d >> b) & 1u;
-            uint64_t bb = __ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
-        uint32_t before = __popcll(m & lt_mask);
-        uint32_t cnt = __popcll(m);
-        uint32_t wb = ok ? s_w[wave][d & 255u] : 0u;
-        rank[i] = wb + before;
-        bool leader = ok && ((m >> lane) == 1ull);
-        if (leader) s_w[wave][d] = wb + cnt;
-    }
-    __syncthreads();
-
-    // per digit: offsets of the waves of this tile, tile total
-    uint32_t tcnt = 0;
-    {
-        const int d = tid;
-        uint32_t run = 0;
-#pragma unroll
-        for (int w = 0; w < SORT_BLOCK / 64; ++w) {
-            uint32_t c = s_w[w][d];
-            s_w[w][d] = run;
-            run += c;
-        }
-        tcnt = run;
-    }
-    // look-back over earlier tiles, digit by digit
-    uint32_t* st = status + (size_t)tile * 256 + tid;
-    uint32_t excl = 0;
-    st_relaxed_agent(st, (tile == 0 ? LB_FLAG_PRE : LB_FLAG_AGG) | tcnt);
-    // global base of each digit (while the earlier tiles publish theirs)
-    uint32_t total;
-    const uint32_t gex = block_excl_scan(hv, s_scan, &total);
-    if (tile != 0) {
-        // LB_WINDOW predecessors per round trip; consume ready words nearest
-        // first until an inclusive prefix, stop at the first one not ready
-        int j = (int)tile - 1;
-        uint32_t spins = 0;
-        while (j >= 0) {
-            uint32_t w[LB_WINDOW];
-#pragma unroll
-            for (int b = 0; b < LB_WINDOW; ++b)
-                w[b] = j - b >= 0 ? ld_relaxed_agent(status + (size_t)(j - b) * 256 + tid) : 0u;
-            int used = 0;
-            bool stop = false, pre = false;
-#pragma unroll
-            for (int b = 0; b < LB_WINDOW; ++b) {
-                if (!stop) {
-                    if (j - b < 0 || (w[b] & ~LB_VALUE) == 0u) {
-                        stop = true;
-                    } else {
-                        excl += w[b] & LB_VALUE;
-                        ++used;
-                        if (w[b] & LB_FLAG_PRE) pre = stop = true;
-                    }
-                }
-            }
-            if (pre) break;
-            j -= used;
-            if (used == 0) {
-                if (++spins > SPIN_LIMIT) {
-                    atomicOr(dev_status, DEV_WAIT_LIMIT);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-        }
-        st_relaxed_agent(st, LB_FLAG_PRE | ((excl + tcnt) & LB_VALUE));
-    }
-    s_base[tid] = gex + excl;
-    if constexpr (ITEMS >= 16) {
-        // Large tiles: stage the tile in LDS in digit order, then write each
-        // digit's run with consecutive threads (coalesced) instead of
-        // scattering from registers.
-        __shared__ uint64_t s_k[SORT_BLOCK * ITEMS];
-        __shared__ uint32_t s_v[SORT_BLOCK * ITEMS];
-        __shared__ uint8_t s_dg[SORT_BLOCK * ITEMS];  // frame digits, found once per element
-        __shared__ uint32_t s_toff[256];
-        uint32_t ttot;
-        const uint32_t tex = block_excl_scan(tcnt, s_scan, &ttot);
-        s_toff[tid] = tex;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const uint32_t d = dig[i];
-            if (d < 256u) {
-                const uint32_t lp = s_toff[d] + s_w[wave][d] + rank[i];
-                s_k[lp] = key[i];
-                s_v[lp] = val[i];
-                if (pass >= SORT_PASSES) s_dg[lp] = (uint8_t)d;
-            }
-        }
-        __syncthreads();
-        for (uint32_t p = tid; p < ttot; p += SORT_BLOCK) {
-            const uint64_t kk = s_k[p];
-            const uint32_t vv = s_v[p];
-            const uint32_t d = pass < SORT_PASSES ? (uint32_t)((kk >> shift) & 255u) : (uint32_t)s_dg[p];
-            const uint32_t o = s_base[d] + (p - s_toff[d]);
-            if (o < n) {  // always true unless a look-back wait expired
-                kout[o] = kk;
-                vout[o] = vv;
-            }
-        }
-    } else {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const uint32_t d = dig[i];
-            if (d < 256u) {
-                const uint32_t o = s_base[d] + s_w[wave][d] + rank[i];
-                if (o < n) {  // always true unless a look-back wait expired
-                    kout[o] = key[i];
-                    vout[o] = val[i];
-                }
-            }
-        }
-    }
+        for (uint32_t i = threadIdx.x; i <= nf; i += SORT_BLOCK) s_foff[i] = foff[i];
+    radix_tile<ITEMS, false>(kin, vin, kout, vout, n, blockIdx.x, hist, status, dev_status, DEV_WAIT_LIMIT,
+                             FrameDigit{pass, foff, s_foff, foff_lds, nf});
 }
 
 // ---------------------------------------------------------------- deep cells

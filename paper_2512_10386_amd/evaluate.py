@@ -53,6 +53,8 @@ class Evaluator:
         t = self.torch
         na, nb = a.shape[0], b.shape[0]
         need = B.gdn_nearest_workspace_size(self.ctx, na)
+        if nb > 0:  # room for the sorted search
+            need = max(need, B.gdn_eval_workspace_size(self.ctx, na, nb))
         ws = t.empty(need, dtype=t.uint8, device=self.device)
         idx = t.empty(na, dtype=t.int32, device=self.device)
         d2 = t.empty(na, dtype=t.float32, device=self.device)
