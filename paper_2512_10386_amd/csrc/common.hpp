@@ -39,7 +39,7 @@ constexpr uint32_t KNN_TQ_SMALL_MAX_N = 1u << 20;
 constexpr int KNN_CC0 = 32768;                // default initial candidate chunk
 constexpr int KNN_NCH_MAX = 32;               // max candidate chunks per leaf
 constexpr int KNN_GRP = 64;                   // P1 positions per culling group of the kNN (one per lane)
-constexpr uint32_t KNN_STREAMS = 8;           // kNN work-queue streams (cursors)
+constexpr uint32_t KNN_STREAMS = 64;          // kNN work-queue streams (cursors)
 constexpr int HALO = 27;
 constexpr int VOX_BLOCK = 256;
 constexpr int VOX_LDS_SLOTS = 4096;           // LDS hash slots (leaves <= 2048 pts)
