@@ -73,7 +73,8 @@ struct Counters {
     unsigned long long pairs;
     uint32_t n_chunked_items; // kNN items of chunked leaves (they come first)
     uint32_t plan_cc;         // chosen kNN chunk length (parallel plan)
-    uint32_t pad[2];
+    uint32_t knn_tq;          // queries per kNN work item (a power of two)
+    uint32_t pad;
     unsigned long long plan_acc[PLAN_LEVELS][3];  // per candidate chunk length: lists, items, chunked items
     unsigned long long plan_pairs;
     // kNN work queue: item i belongs to stream i % KNN_STREAMS; one cursor
@@ -99,6 +100,17 @@ struct GroupBox {
 struct KnnItem {
     uint32_t leaf, q0, q1, chunk, grp, pad;
 };
+
+// Queries per kNN work item of inputs with n1 P1 points. A wave takes an
+// item's queries in turn, so few points make short items to fill the chip's
+// 4096 waves, and many points long ones, which share the walk over the leaf's
+// groups. Whole calls with 8 / 4 / 2 / 1 queries: 914 points 131 / 120 / 115 /
+// 112 us; 12.2k 180 / 161 / 157 / 164; 35.6k 309 / 272 / 264 / 291; 52k 248 /
+// 245 / 258 / 297; 96k 307 / 313 / 353 / 442.
+__host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1, uint32_t most) {
+    if (most > (uint32_t)KNN_TQ_SMALL) return most;  // large inputs
+    return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 40960u ? 4u : most;
+}
 
 // Method parameters as the kernels use them.
 struct Params {
@@ -143,7 +155,7 @@ struct Plan {
     uint32_t* scan_status;    // [SCAN_SLOTS][scan_tiles]
     uint32_t sort_tiles, scan_tiles;
     uint32_t sort_items;      // keys per thread of the radix passes (4 or 16)
-    uint32_t tq;              // queries per kNN work item (KNN_TQ_SMALL or KNN_TQ)
+    uint32_t tq_max;          // queries per kNN work item, at most (KNN_TQ_SMALL or KNN_TQ)
     uint8_t* deepf;           // [n] 1 at sorted positions inside deep level-10 cells; between the two
                               // deep-cell kernels, 2 marks the start of a cell to re-sort (zeroed block)
     // frames

@@ -1,8 +1,8 @@
 // Leaf-local brute-force kNN with halo candidates (Sec. 3: N_K(i), d_ij and
 // r_K,i on the voxel-filtered set P1).
 //
-// Work item = (leaf, a tile of 8 queries (16 above 2^20 points), candidate
-// chunk), one wave each. The candidates are the P1 positions of the leaf's
+// Work item = (leaf, a tile of 1 to 8 queries by the number of P1 points (16
+// above 2^20 input points), candidate chunk), one wave each. The candidates are the P1 positions of the leaf's
 // merged halo ranges; they are visited in aligned groups of 64 positions (one
 // per lane), whose bounding boxes the bound kernel writes. Up to 64 groups at
 // a time are box-tested against every query of the tile (a query mask per
@@ -186,7 +186,7 @@ struct StagedPts {
 __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P, const float4* __restrict__ cand4,
                                                                          int k) {
     __shared__ float4 s_pts[BOUND_Q + 2 * BOUND_MARGIN + 1];
-    const uint32_t np1 = P.ctr->n_p1;
+    const uint32_t np1 = P.ctr->n_p1, tq = P.ctr->knn_tq;
     const uint32_t sub = threadIdx.x % BOUND_SPLIT, ql = threadIdx.x / BOUND_SPLIT;
     for (uint32_t q_first = blockIdx.x * BOUND_Q; q_first < np1; q_first += gridDim.x * BOUND_Q) {
         const uint32_t lo = q_first > (uint32_t)BOUND_MARGIN ? q_first - (uint32_t)BOUND_MARGIN : 0u;
@@ -226,10 +226,10 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
         const float b = query_bound(StagedPts{s_pts, lo}, rb, re, qi, k, sub, live);
         if (live && sub == 0u) {
             P.tau_c[qi] = b;
-            if ((qi - qb) % P.tq == 0u) {
+            if ((qi - qb) % tq == 0u) {
                 const uint32_t nch = P.leaf_nch[t];
-                const uint32_t grp = P.leaf_item[t] + ((qi - qb) / P.tq) * nch;
-                const uint32_t q1 = min(qe, qi + P.tq);
+                const uint32_t grp = P.leaf_item[t] + ((qi - qb) / tq) * nch;
+                const uint32_t q1 = min(qe, qi + tq);
                 for (uint32_t c = 0; c < nch; ++c) P.items[grp + c] = KnnItem{t, qi, q1, c, grp, 0u};
             }
         }
@@ -808,15 +808,16 @@ __global__ __launch_bounds__(64) void knn_merge_kernel(Plan P, int kk) {
     __shared__ unsigned long long s_lst[QPW * 64];
     const uint32_t lane = threadIdx.x;
     const uint32_t k = (uint32_t)kk;
-    const uint32_t nci = P.ctr->n_chunked_items;
+    const uint32_t nci = P.ctr->n_chunked_items, tq = P.ctr->knn_tq;
     for (uint32_t u = blockIdx.x; u < nci * MERGE_SPLIT; u += gridDim.x) {
         const uint32_t it = u / MERGE_SPLIT, part = u % MERGE_SPLIT;
         const KnnItem w = P.items[it];
         if (w.chunk != 0u) continue;
         // this wave's share of the tile's queries
-        const uint32_t q0 = w.q0 + part * (P.tq / (uint32_t)MERGE_SPLIT);
+        const uint32_t share = (tq + (uint32_t)MERGE_SPLIT - 1u) / (uint32_t)MERGE_SPLIT;
+        const uint32_t q0 = w.q0 + part * share;
         if (q0 >= w.q1) continue;
-        const uint32_t q1 = min(w.q1, q0 + P.tq / (uint32_t)MERGE_SPLIT);
+        const uint32_t q1 = min(w.q1, q0 + share);
         const uint32_t t = w.leaf;
         const uint32_t nch = P.leaf_nch[t];
         const uint32_t qb = P.p1pos[P.leaf_begin[t]];

@@ -418,16 +418,17 @@ struct P1Emit {
 struct P1Fin {
     Counters* c;
     uint32_t* p1pos;
-    uint32_t n;
+    uint32_t n, tq_max;
     __device__ void operator()(uint32_t total) const {
         c->n_p1 = total;
+        c->knn_tq = knn_tile_queries(total, tq_max);
         p1pos[n] = total;
     }
 };
 
 void launch_p1_compact(const Plan& P, hipStream_t st) {
     launch_scan(P1Get{P.p1}, P1Emit{P.p1pos, P.pos4, P.leaf_of, P.cand4, P.cand_leaf, P.inv_p1},
-                P1Fin{P.ctr, P.p1pos, P.n}, nullptr, P.n, P.scan_status + P.scan_tiles,
+                P1Fin{P.ctr, P.p1pos, P.n, P.tq_max}, nullptr, P.n, P.scan_status + P.scan_tiles,
                 &P.ctr->status, st);
 }
 
@@ -628,7 +629,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
     __shared__ uint32_t s_scan[NS * (PLAN_BLOCK / 64 + 1)];
     __shared__ uint32_t s_cc, s_done, s_carry[NS], s_base[NS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t nl = P.ctr->n_leaves;
+    const uint32_t nl = P.ctr->n_leaves, tq = P.ctr->knn_tq;
     // this thread's leaves t = tid + r * PLAN_BLOCK: P1 points and candidates
     uint32_t c_n1[PLAN_R], c_nc[PLAN_R];
 #pragma unroll
@@ -666,7 +667,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
             if (n1 == 0) return;
             const uint32_t nch = nch_of(n1, nc, cc);
             if (nch > 1) lists += (unsigned long long)n1 * nch;
-            items += (unsigned long long)((n1 + P.tq - 1) / P.tq) * nch;
+            items += (unsigned long long)((n1 + tq - 1) / tq) * nch;
             pairs += (unsigned long long)n1 * (nc - 1);
         });
         for (int o = 32; o > 0; o >>= 1) {
@@ -695,7 +696,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
         nch = nch_of(n1, nc, cc);
 #pragma unroll
         for (int i = 0; i < NS; ++i) v[i] = 0;
-        const uint32_t ni = n1 ? ((n1 + P.tq - 1) / P.tq) * nch : 0u;
+        const uint32_t ni = n1 ? ((n1 + tq - 1) / tq) * nch : 0u;
         if (nch > 1) {
             v[0] = n1 * nch;
             v[1] = ni;
@@ -812,14 +813,14 @@ __global__ __launch_bounds__(256) void plan_count_kernel(Plan P, uint32_t chunk0
     __shared__ unsigned long long s_acc[PLAN_LEVELS * 3 + 1];
     for (int i = threadIdx.x; i < PLAN_LEVELS * 3 + 1; i += blockDim.x) s_acc[i] = 0ull;
     __syncthreads();
-    const uint32_t nl = P.ctr->n_leaves;
+    const uint32_t nl = P.ctr->n_leaves, tq = P.ctr->knn_tq;
     unsigned long long acc[PLAN_LEVELS * 3 + 1];
 #pragma unroll
     for (int i = 0; i < PLAN_LEVELS * 3 + 1; ++i) acc[i] = 0ull;
     for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nl; t += gridDim.x * blockDim.x) {
         const uint32_t n1 = P.p1pos[P.leaf_begin[t + 1]] - P.p1pos[P.leaf_begin[t]], nc = P.leaf_ncand[t];
         if (n1 == 0) continue;
-        const unsigned long long tiles = (n1 + P.tq - 1) / P.tq;
+        const unsigned long long tiles = (n1 + tq - 1) / tq;
 #pragma unroll
         for (int l = 0; l < PLAN_LEVELS; ++l) {
             const uint32_t cc = chunk0 << l;
@@ -899,7 +900,8 @@ struct ItemsGet {
     __device__ uint32_t operator()(uint32_t t) const {
         uint32_t n1, nc, nch;
         PlanLeaf{&P}.get(t, &n1, &nc, &nch);
-        return ((nch > 1) == CHUNKED && n1) ? ((n1 + P.tq - 1) / P.tq) * nch : 0u;
+        const uint32_t tq = P.ctr->knn_tq;
+        return ((nch > 1) == CHUNKED && n1) ? ((n1 + tq - 1) / tq) * nch : 0u;
     }
 };
 template <bool CHUNKED>

@@ -1,0 +1,28 @@
+"""kNN work items of 1, 2, 4 and 8 queries (chosen by the number of P1 points)
+against the oracle by the usual parity bar: bit-exact neighbour sets and
+distances, scores to 1e-5. With the voxel filter off every point is in P1, so
+the sizes sit exactly on the rule's edges."""
+import pytest
+
+from paper_2512_10386_amd import synth
+from tests.parity import compare, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,k,cap,chunk", [
+    (4096, 12, 256, 0), (4097, 12, 256, 0), (20_480, 16, 512, 0), (20_481, 16, 512, 0), (40_960, 32, 256, 0),
+    (40_961, 32, 256, 0),
+    # chunked leaves: partial lists of one- and two-query tiles, merged
+    (4096, 33, 4096, 1024), (5000, 64, 5000, 700), (13, 12, 4, 3)])
+def test_tile_sizes(oracle, n, k, cap, chunk):
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz, _ = synth.uniform_cube(n, n)
+    prm = dict(k=k, leaf_cap=cap, stages=6)
+    ref = oracle.denoise(xyz, **prm)
+    assert int(ref["p1"].sum()) == n
+    den = Denoiser(0, knn_chunk=chunk, **prm)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
