@@ -34,8 +34,8 @@ constexpr uint32_t SCAN_SMALL_N = 1u << 20;   // scans up to this size: 4 items 
 constexpr int SCAN_SLOTS = 6;                 // scans per call: leaves, P1, keep, 3 kNN plan scans
 constexpr int PLAN_LEVELS = 8;                // candidate chunk lengths chunk0 << 0..7 (parallel plan)
 constexpr int KNN_TQ = 16;                    // queries per kNN work item (one wave), at most
-constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^20 points (shorter items, shorter tail)
-constexpr uint32_t KNN_TQ_SMALL_MAX_N = 1u << 20;
+constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^19 points (shorter items, shorter tail)
+constexpr uint32_t KNN_TQ_SMALL_MAX_N = 1u << 19;
 constexpr int KNN_CC0 = 32768;                // default initial candidate chunk
 constexpr int KNN_NCH_MAX = 32;               // max candidate chunks per leaf
 constexpr int KNN_GRP = 64;                   // P1 positions per culling group of the kNN (one per lane)
@@ -74,7 +74,7 @@ struct Counters {
     uint32_t n_chunked_items; // kNN items of chunked leaves (they come first)
     uint32_t plan_cc;         // chosen kNN chunk length (parallel plan)
     uint32_t knn_tq;          // queries per kNN work item (a power of two)
-    uint32_t pad;
+    uint32_t n_big;           // 1: some leaf has more than SMALL_LEAF P1 points
     unsigned long long plan_acc[PLAN_LEVELS][3];  // per candidate chunk length: lists, items, chunked items
     unsigned long long plan_pairs;
     // kNN work queue: item i belongs to stream i % KNN_STREAMS; one cursor
@@ -100,6 +100,19 @@ struct GroupBox {
 struct KnnItem {
     uint32_t leaf, q0, q1, chunk, grp, pad;
 };
+
+// Leaves of at most SMALL_LEAF P1 points take one wave in the density and
+// top-lambda selects (four values per lane, no block barriers) where the input
+// has so many of them that a workgroup per leaf runs in many rounds: above
+// 2^20 points, above 2^19 with a leaf cap of at most 512, or above 3 * 2^16
+// with one of at most 256. Whole calls, workgroups against waves: 120k points
+// at cap 256 249 and 252 us, 250k 368 and 347, 500k 608 and 547, 900k in nine
+// frames 1014 and 886; at cap 512 250k 355 and 367, 900k 1175 and 1117; 500k
+// at cap 1024 703 and 718.
+constexpr uint32_t SMALL_LEAF = 256;
+inline bool small_leaf_path(uint32_t n, int32_t leaf_cap) {
+    return n > (1u << 20) || (n > (1u << 19) && leaf_cap <= 512) || (n > (3u << 16) && leaf_cap <= 256);
+}
 
 // Queries per kNN work item of inputs with n1 P1 points. A wave takes an
 // item's queries in turn, so few points make short items to fill the chip's

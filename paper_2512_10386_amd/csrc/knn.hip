@@ -2,7 +2,7 @@
 // r_K,i on the voxel-filtered set P1).
 //
 // Work item = (leaf, a tile of 1 to 8 queries by the number of P1 points (16
-// above 2^20 input points), candidate chunk), one wave each. The candidates are the P1 positions of the leaf's
+// above 2^19 input points), candidate chunk), one wave each. The candidates are the P1 positions of the leaf's
 // merged halo ranges; they are visited in aligned groups of 64 positions (one
 // per lane), whose bounding boxes the bound kernel writes. Up to 64 groups at
 // a time are box-tested against every query of the tile (a query mask per
@@ -15,7 +15,7 @@
 //
 // Each query keeps, in LDS, its k best (d2, original index) keys (d2 bits <<
 // 32 | index), sorted, and a pending buffer of up to 64 candidates (the keys,
-// or their P1 positions above 1M points, which halves the LDS a wave needs; a
+// or their P1 positions above 2^19 points, which halves the LDS a wave needs; a
 // key is then rebuilt from the position with the same fp32 expression). A
 // candidate passes with one compare against the query's bound; the passing
 // ones are appended (ballot + lane rank). A full buffer, and the buffer at
@@ -50,7 +50,7 @@ constexpr unsigned long long KEY_EMPTY = (unsigned long long)LLONG_MAX;
 constexpr int QPW = KNN_TQ;  // queries per wave item
 constexpr int PEND = 64;     // pending keys per query
 constexpr int PEND_HALF = 32;  // pending keys a half-wave merge takes (k <= 32)
-constexpr uint32_t KNN_POS_MIN_N = 1u << 20;  // above: pending buffers of positions
+constexpr uint32_t KNN_POS_MIN_N = 1u << 19;  // above: pending buffers of positions
 constexpr int KNN_NB = 4;      // needed groups held in registers at a time
 
 __device__ __forceinline__ float dist2(const float4 q, const float4 c) {
@@ -920,9 +920,11 @@ size_t knn_lds_bytes(uint32_t q, int k, bool pos) {
 
 void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st) {
     const unsigned blocks = (unsigned)(num_cus > 0 ? num_cus : 256) * (P.n > KNN_POS_MIN_N ? 20u : 16u);
-    // Large batches run long enough for occupancy to pay (positions); a single
-    // frame's run is set by its longest items, where a gather per merge costs
-    // more (keys).
+    // Large inputs run long enough for occupancy to pay (positions); a smaller
+    // input's run is set by its longest items, where a gather per merge costs
+    // more (keys). Whole calls, keys against positions: 250k points 368 and
+    // 390 us, 500k 608 and 616, 1M 1193 and 1131, 900k in nine frames 1013 and
+    // 992.
     // The plan's tile size goes with the pending-buffer kind: tiles of
     // KNN_TQ_SMALL queries exactly for the inputs that keep keys.
     static_assert(KNN_TQ_SMALL_MAX_N == KNN_POS_MIN_N, "tile size and buffer kind switch together");

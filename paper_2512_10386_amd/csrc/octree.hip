@@ -180,7 +180,7 @@ __device__ __forceinline__ float leaf_voxel_size(const float* lo, const float* h
 // expressions and hash as voxel_kernel, so the counts are identical.
 constexpr uint32_t VOX_WAVE_MAX = 256;
 constexpr uint32_t VOX_WAVE_SLOTS = 2 * VOX_WAVE_MAX;
-constexpr uint32_t VOX_WAVE_MIN_N = 1u << 20;
+constexpr uint32_t VOX_WAVE_MIN_N = 1u << 19;
 
 __global__ __launch_bounds__(256) void voxel_wave_kernel(Plan P, double beta, uint32_t nv) {
     __shared__ unsigned long long s_key[4][VOX_WAVE_SLOTS];
@@ -665,6 +665,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
         unsigned long long lists = 0, items = 0, pairs = 0;
         for_leaves([&](uint32_t, uint32_t n1, uint32_t nc) {
             if (n1 == 0) return;
+            if (n1 > SMALL_LEAF) P.ctr->n_big = 1u;  // (any thread's store of the same value)
             const uint32_t nch = nch_of(n1, nc, cc);
             if (nch > 1) lists += (unsigned long long)n1 * nch;
             items += (unsigned long long)((n1 + tq - 1) / tq) * nch;
@@ -817,6 +818,7 @@ __global__ __launch_bounds__(256) void plan_count_kernel(Plan P, uint32_t chunk0
     unsigned long long acc[PLAN_LEVELS * 3 + 1];
 #pragma unroll
     for (int i = 0; i < PLAN_LEVELS * 3 + 1; ++i) acc[i] = 0ull;
+    bool big = false;
     for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nl; t += gridDim.x * blockDim.x) {
         const uint32_t n1 = P.p1pos[P.leaf_begin[t + 1]] - P.p1pos[P.leaf_begin[t]], nc = P.leaf_ncand[t];
         if (n1 == 0) continue;
@@ -832,7 +834,9 @@ __global__ __launch_bounds__(256) void plan_count_kernel(Plan P, uint32_t chunk0
             acc[3 * l + 1] += tiles * nch;
         }
         acc[PLAN_LEVELS * 3] += (unsigned long long)n1 * (nc - 1);
+        big |= n1 > SMALL_LEAF;
     }
+    if (__builtin_amdgcn_ballot_w64(big) != 0ull && (threadIdx.x & 63) == 0) P.ctr->n_big = 1u;
 #pragma unroll
     for (int i = 0; i < PLAN_LEVELS * 3 + 1; ++i) {
         unsigned long long v = acc[i];

@@ -235,8 +235,6 @@ struct LdsBits {
 
 constexpr uint32_t SEL_LDS_MAX = 2048;  // leaves up to this size are selected from LDS
 constexpr uint32_t SEL_BATCH_MAX = 1024;  // leaves up to this size: each thread loads its points at once
-constexpr uint32_t SMALL_LEAF = 256;    // leaves up to this size: one wave (4 values per lane), no LDS
-constexpr uint32_t SMALL_PATH_MIN_N = 1u << 20;  // the wave path is used above this many points
 constexpr uint32_t PACKED_OUT_MIN_N = 1u << 20;  // above: outputs scattered as packed records
 
 struct R2Bits {
@@ -312,6 +310,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params p
     __shared__ unsigned long long s_rho[SEL_LDS_MAX];
     __shared__ uint32_t s_list[SEL_BLOCK];
     __shared__ uint32_t s_lscan[SEL_BLOCK / 64 + 1];
+    if (small && P.ctr->n_big == 0u) return;
     const uint32_t nl = P.ctr->n_leaves;
     const int k = prm.k;
     const uint32_t role = blockIdx.x & 1u, bx = blockIdx.x >> 1, gx = gridDim.x >> 1;
@@ -559,8 +558,7 @@ __global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params p
 }
 
 void launch_leaf_select(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
-    // the wave path pays off for the many small leaves of large batches
-    const bool small = P.n > SMALL_PATH_MIN_N;
+    const bool small = small_leaf_path(P.n, prm.leaf_cap);
     const bool sq = prm.alpha == 1.0;
     if (small) {
         unsigned wb = (P.n / 128 + 3) / 4;
@@ -745,9 +743,9 @@ struct CandIdx {
     __device__ uint32_t operator()(uint32_t i) const { return __float_as_uint(cand4[qb + i].w); }
 };
 
-// Optional outputs (single frames, every leaf handled here): keep, score and
-// stage in input order for every point of each leaf, as outputs_kernel
-// writes them, so that pass is not needed.
+// Optional outputs (up to 2^20 points): keep, score and stage in input order
+// for every point of each leaf, as outputs_kernel writes them, so that pass is
+// not needed.
 struct ToplOut {
     uint8_t* keep;
     float* score;
@@ -767,6 +765,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
     __shared__ uint32_t s_idx[SEL_LDS_MAX];
     __shared__ uint32_t s_list[SEL_BLOCK];
     __shared__ uint32_t s_lscan[SEL_BLOCK / 64 + 1];
+    if (small && P.ctr->n_big == 0u) return;
     const uint32_t nl = P.ctr->n_leaves;
     for (uint32_t base = blockIdx.x; base < nl; base += gridDim.x * SEL_BLOCK) {
     const uint32_t nlist = block_leaf_round(P, base, nl, small, s_list, s_lscan, gridDim.x);
@@ -922,16 +921,30 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
 
 // Small leaves: theta = the m-th largest key from a wave sort; keys above it
 // are kept, and among the keys equal to it the `need` smallest indices.
-__global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda) {
+// OUT: the outputs are written here too, those of the points outside P1 among
+// them (their flags and indices are read beside the P1 reads).
+template <bool OUT>
+__global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda, ToplOut out) {
     __shared__ uint32_t s_hist[4][256];
     uint32_t* const hist = s_hist[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wid = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t nl = P.ctr->n_leaves;
     for (uint32_t t = wid; t < nl; t += nw) {
-        const uint32_t qb = P.p1pos[P.leaf_begin[t]], qe = P.p1pos[P.leaf_begin[t + 1]];
+        const uint32_t lb = P.leaf_begin[t], le = P.leaf_begin[t + 1];
+        const uint32_t qb = P.p1pos[lb], qe = P.p1pos[le];
         const uint32_t n1 = qe - qb;
         if (n1 > SMALL_LEAF) continue;
+        const uint32_t nt = le - lb;
+        uint32_t f1[4], of[4];
+        if constexpr (OUT) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t s = lb + min((uint32_t)j * 64u + lane, nt - 1u);
+                f1[j] = P.p1[s];
+                of[j] = P.idx_a[s];
+            }
+        }
         WaveVals kv;
         uint32_t oi[4];
         uint32_t n2 = 0;
@@ -1007,7 +1020,18 @@ __global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda) 
         for (int j = 0; j < 4; ++j) {
             const uint32_t i = (uint32_t)j * 64u + lane;
             const bool kept = m > 0 && (kv.v[j] > theta || (kv.v[j] == theta && (!ties_cut || below[j] < need)));
-            if (i < n1) P.stage_c[qb + i] = p2v[j] ? (kept ? 3 : 2) : 1;
+            if (i < n1) {
+                const uint8_t st = p2v[j] ? (kept ? 3 : 2) : 1;
+                P.stage_c[qb + i] = st;
+                if constexpr (OUT) out.put(ixv[j], st, sv[j]);
+            }
+        }
+        if constexpr (OUT) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((uint32_t)j * 64u + lane < nt && !f1[j]) out.put(of[j], 0, 0.0);
+            for (uint32_t s = lb + 256u + lane; s < le; s += 64u)
+                if (!P.p1[s]) out.put(P.idx_a[s], 0, 0.0);
         }
         if (lane == 0) P.leaf_m[t] = m;
     }
@@ -1044,18 +1068,19 @@ bool launch_topl(const Plan& P, const Params& prm, uint8_t* keep, float* score, 
         hipLaunchKernelGGL(threshold_kernel, dim3(blocks), dim3(256), 0, st, P, prm.log_thr);
         return false;
     }
-    const bool small = P.n > SMALL_PATH_MIN_N;
+    const bool small = small_leaf_path(P.n, prm.leaf_cap);
+    // up to 2^20 points the top-lambda kernels write the outputs too (larger
+    // inputs scatter them as packed records)
+    const bool write = P.n <= PACKED_OUT_MIN_N;
+    const ToplOut out{write ? keep : nullptr, score, stage};
     if (small) {
         unsigned wb = (P.n / 128 + 3) / 4;
         if (wb > 8192) wb = 8192;
-        hipLaunchKernelGGL(topl_small_kernel, dim3(wb), dim3(256), 0, st, P, prm.keep_ratio);
+        hipLaunchKernelGGL(write ? topl_small_kernel<true> : topl_small_kernel<false>, dim3(wb), dim3(256), 0, st, P,
+                           prm.keep_ratio, out);
     }
     unsigned blocks = P.n < 2048 ? P.n : 2048;
     if (blocks == 0) blocks = 1;
-    // up to 2^20 points every leaf passes through topl_kernel, which then
-    // writes the outputs too (large inputs scatter them as packed records)
-    const bool write = !small && P.n <= PACKED_OUT_MIN_N;
-    const ToplOut out{write ? keep : nullptr, score, stage};
     hipLaunchKernelGGL(topl_kernel, dim3(blocks), dim3(SEL_BLOCK), 0, st, P, prm.keep_ratio, small, out);
     return write;
 }

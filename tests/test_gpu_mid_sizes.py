@@ -1,0 +1,36 @@
+"""Single frames between the small- and large-input paths against the oracle
+by the usual parity bar (bit-exact discrete results, scores to 1e-5): one-wave
+selects and top-lambda with the outputs written there (above 3 * 2^16 points at
+leaf caps up to 256, above 2^19 up to 512, with and without leaves of more than
+256 P1 points), and the kNN and voxel kernels of large inputs (above 2^19 points)."""
+import numpy as np
+import pytest
+
+from paper_2512_10386_amd import synth
+from tests.parity import compare, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def crowded(n, seed):
+    """Surfaces with an over-full leaf (copies of one point) and far outliers."""
+    xyz, _ = synth.sphere_plane(seed, n - n // 4 - 4000, n // 4 - 2000, 4000)
+    xyz = np.concatenate([xyz, np.repeat(xyz[:1], 2000, 0)])
+    return xyz[np.random.default_rng(seed).permutation(len(xyz))]
+
+
+@pytest.mark.parametrize("make,k,cap", [
+    (lambda: synth.lidar_frame(seed=3, n_az=3073)[0], 12, 256),      # 196,672 points: just above 3 * 2^16
+    (lambda: crowded(270_001, 4), 16, 256),
+    (lambda: crowded(540_001, 4), 8, 512),
+    (lambda: crowded(196_608, 5), 16, 256),                          # 3 * 2^16: workgroup selects
+    (lambda: synth.lidar_frame(seed=6, n_az=8193)[0], 12, 512)])     # 524,352 points: just above 2^19
+def test_mid_sizes(oracle, make, k, cap):
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz = np.ascontiguousarray(make())
+    ref = oracle.denoise(xyz, k=k, leaf_cap=cap)
+    den = Denoiser(0, k=k, leaf_cap=cap)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
