@@ -101,6 +101,8 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.sort_hist = (uint32_t*)take(sizeof(uint32_t) * SORT_PASSES_MAX * 256);
     P.sort_status = (uint32_t*)take(sizeof(uint32_t) * (size_t)P.sort_passes * P.sort_tiles * 256);
     P.scan_status = (uint32_t*)take(sizeof(uint32_t) * SCAN_SLOTS * (size_t)P.scan_tiles);
+    P.plan_tiles = (uint32_t)((N + 511) / 512);  // 512 leaves per tile
+    P.plan_status = (uint32_t*)take(sizeof(uint32_t) * 3 * (size_t)P.plan_tiles);
     P.deepf = (uint8_t*)take(N);
     P.zero_begin = base ? base + z0 : nullptr;
     P.zero_bytes = off - z0;
@@ -127,7 +129,6 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.p1pos = (uint32_t*)take(4 * (N + 1));
     P.leaf_begin = (uint32_t*)take(4 * (N + 1));
     P.leaf_level = (uint32_t*)take(4 * N);
-    P.leaf_prefix = (uint64_t*)take(8 * N);
     P.leaf_h = (float*)take(4 * N);
     P.leaf_nr = (uint32_t*)take(4 * N);
     P.leaf_ranges = (uint2*)take(sizeof(uint2) * HALO * N);
@@ -138,8 +139,6 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.leaf_plist = (uint32_t*)take(4 * N);
     P.leaf_item = (uint32_t*)take(4 * N);
     P.leaf_rho_med = (double*)take(8 * N);
-    P.leaf_r2cut = (float*)take(4 * N);
-    P.leaf_m = (uint32_t*)take(4 * N);
     P.vox_keys = (uint64_t*)take(16 * N);
     P.vox_cnt = (uint32_t*)take(8 * N);
     P.cand4 = (float4*)take(16 * N);

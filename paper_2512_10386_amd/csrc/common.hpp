@@ -31,7 +31,7 @@ constexpr uint32_t MAX_FRAMES = 4096;         // frames per batched call (frame 
 constexpr int SCAN_BLOCK = 512;                // look-back scan workgroup (fewer tiles to look back over than 256)
 constexpr int SCAN_ITEMS = 16;
 constexpr uint32_t SCAN_SMALL_N = 1u << 20;   // scans up to this size: 4 items per thread
-constexpr int SCAN_SLOTS = 6;                 // scans per call: leaves, P1, keep, 3 kNN plan scans
+constexpr int SCAN_SLOTS = 3;                 // scans per call: leaves, P1, keep
 constexpr int PLAN_LEVELS = 8;                // candidate chunk lengths chunk0 << 0..7 (parallel plan)
 constexpr int KNN_TQ = 16;                    // queries per kNN work item (one wave), at most
 constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^19 points (shorter items, shorter tail)
@@ -72,7 +72,7 @@ struct Counters {
     uint32_t n_kept;
     unsigned long long pairs;
     uint32_t n_chunked_items; // kNN items of chunked leaves (they come first)
-    uint32_t plan_cc;         // chosen kNN chunk length (parallel plan)
+    uint32_t pad;
     uint32_t knn_tq;          // queries per kNN work item (a power of two)
     uint32_t n_big;           // 1: some leaf has more than SMALL_LEAF P1 points
     unsigned long long plan_acc[PLAN_LEVELS][3];  // per candidate chunk length: lists, items, chunked items
@@ -96,9 +96,9 @@ struct GroupBox {
 };
 
 // One kNN work item: queries [q0, q1) of leaf `leaf` against candidate chunk
-// `chunk`; `grp` indexes the arrival counter shared by the chunks of a tile.
-struct KnnItem {
-    uint32_t leaf, q0, q1, chunk, grp, pad;
+// `chunk`.
+struct __align__(16) KnnItem {
+    uint32_t leaf, q0, q1, chunk;
 };
 
 // Leaves of at most SMALL_LEAF P1 points take one wave in the density and
@@ -166,7 +166,8 @@ struct Plan {
     uint32_t* sort_hist;      // [SORT_PASSES_MAX][256]
     uint32_t* sort_status;    // [SORT_PASSES_MAX][sort_tiles][256]
     uint32_t* scan_status;    // [SCAN_SLOTS][scan_tiles]
-    uint32_t sort_tiles, scan_tiles;
+    uint32_t* plan_status;    // [3][plan_tiles] (parallel kNN plan)
+    uint32_t sort_tiles, scan_tiles, plan_tiles;
     uint32_t sort_items;      // keys per thread of the radix passes (4 or 16)
     uint32_t tq_max;          // queries per kNN work item, at most (KNN_TQ_SMALL or KNN_TQ)
     uint8_t* deepf;           // [n] 1 at sorted positions inside deep level-10 cells; between the two
@@ -193,7 +194,6 @@ struct Plan {
     // leaves (at most n)
     uint32_t* leaf_begin;     // [n+1]
     uint32_t* leaf_level;     // [n]
-    uint64_t* leaf_prefix;    // [n]
     float* leaf_h;            // [n]
     uint32_t* leaf_nr;        // [n] number of candidate ranges
     uint2* leaf_ranges;       // [n][HALO] compacted candidate ranges
@@ -204,8 +204,6 @@ struct Plan {
     uint32_t* leaf_plist;     // [n] first partial list of the leaf
     uint32_t* leaf_item;      // [n] queue index of the leaf's first kNN item
     double* leaf_rho_med;     // [n]
-    float* leaf_r2cut;        // [n]
-    uint32_t* leaf_m;         // [n]
     uint64_t* vox_keys;       // [2n] global hash fallback
     uint32_t* vox_cnt;        // [2n]
     // compacted P1 (query/candidate index q)

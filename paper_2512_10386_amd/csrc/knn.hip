@@ -228,9 +228,9 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
             P.tau_c[qi] = b;
             if ((qi - qb) % tq == 0u) {
                 const uint32_t nch = P.leaf_nch[t];
-                const uint32_t grp = P.leaf_item[t] + ((qi - qb) / tq) * nch;
+                const uint32_t first = P.leaf_item[t] + ((qi - qb) / tq) * nch;
                 const uint32_t q1 = min(qe, qi + tq);
-                for (uint32_t c = 0; c < nch; ++c) P.items[grp + c] = KnnItem{t, qi, q1, c, grp, 0u};
+                for (uint32_t c = 0; c < nch; ++c) P.items[first + c] = KnnItem{t, qi, q1, c};
             }
         }
         __syncthreads();

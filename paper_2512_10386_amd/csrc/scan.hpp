@@ -15,6 +15,45 @@
 
 namespace gdn {
 
+// Publishes tile `tile`'s sum and returns the sum of all tiles before it, in
+// every lane (one whole wave calls it): looks back over up to 64 predecessors
+// per round trip (lane l reads tile j - l), adds the ready aggregates nearest
+// first up to and including an inclusive prefix, and stops at one not ready.
+__device__ __forceinline__ uint32_t look_back(uint32_t* status, uint32_t tile, uint32_t agg, uint32_t lane,
+                                              uint32_t* dev_status) {
+    uint32_t* st = status + tile;
+    if (tile == 0) {
+        if (lane == 0) st_relaxed_agent(st, LB_FLAG_PRE | agg);
+        return 0u;
+    }
+    if (lane == 0) st_relaxed_agent(st, LB_FLAG_AGG | agg);
+    uint32_t excl = 0, spins = 0;
+    int j = (int)tile - 1;
+    while (j >= 0) {
+        const int jj = j - (int)lane;
+        const uint32_t w = jj >= 0 ? ld_relaxed_agent(status + jj) : 0u;
+        const unsigned long long nready = __builtin_amdgcn_ballot_w64(jj >= 0 && (w & ~LB_VALUE) == 0u);
+        const unsigned long long pre = __builtin_amdgcn_ballot_w64(jj >= 0 && (w & LB_FLAG_PRE) != 0u);
+        const unsigned long long stop = nready | pre;
+        const uint32_t s = stop ? (uint32_t)__ffsll((long long)stop) - 1u : 64u;
+        const bool done = s < 64u && ((pre >> s) & 1ull);
+        const uint32_t take = (jj >= 0 && (lane < s || (done && lane == s))) ? (w & LB_VALUE) : 0u;
+        excl += wave_sum(take);
+        if (done) break;
+        const uint32_t used = min(s, (uint32_t)(j + 1));
+        j -= (int)used;
+        if (used == 0u) {
+            if (++spins > SPIN_LIMIT) {
+                if (lane == 0) atomicOr(dev_status, DEV_WAIT_LIMIT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    if (lane == 0) st_relaxed_agent(st, LB_FLAG_PRE | ((excl + agg) & LB_VALUE));
+    return excl;
+}
+
 // get(i)          -> value of element i (uint32, sum must stay < 2^30)
 // emit(i, ex, v)  -> called once per element with its exclusive prefix
 // fin(total)      -> called once with the grand total
@@ -103,46 +142,8 @@ __global__ __launch_bounds__(SCAN_BLOCK) void scan_kernel(Get get, Emit emit, Fi
     uint32_t agg;
     const uint32_t ex = block_excl_scan(sum, s_scan, &agg);
     if (threadIdx.x < 64) {
-        // first wave: look back over up to 64 predecessors per round trip
-        // (lane l reads tile j - l); add the ready aggregates nearest first
-        // up to and including an inclusive prefix, stop at one not ready
-        const uint32_t lane = threadIdx.x;
-        uint32_t* st = status + tile;
-        if (tile == 0) {
-            if (lane == 0) {
-                st_relaxed_agent(st, LB_FLAG_PRE | agg);
-                s_excl = 0;
-            }
-        } else {
-            if (lane == 0) st_relaxed_agent(st, LB_FLAG_AGG | agg);
-            uint32_t excl = 0, spins = 0;
-            int j = (int)tile - 1;
-            while (j >= 0) {
-                const int jj = j - (int)lane;
-                const uint32_t w = jj >= 0 ? ld_relaxed_agent(status + jj) : 0u;
-                const unsigned long long nready = __builtin_amdgcn_ballot_w64(jj >= 0 && (w & ~LB_VALUE) == 0u);
-                const unsigned long long pre = __builtin_amdgcn_ballot_w64(jj >= 0 && (w & LB_FLAG_PRE) != 0u);
-                const unsigned long long stop = nready | pre;
-                const uint32_t s = stop ? (uint32_t)__ffsll((long long)stop) - 1u : 64u;
-                const bool done = s < 64u && ((pre >> s) & 1ull);
-                const uint32_t take = (jj >= 0 && (lane < s || (done && lane == s))) ? (w & LB_VALUE) : 0u;
-                excl += wave_sum(take);
-                if (done) break;
-                const uint32_t used = min(s, (uint32_t)(j + 1));
-                j -= (int)used;
-                if (used == 0u) {
-                    if (++spins > SPIN_LIMIT) {
-                        if (lane == 0) atomicOr(dev_status, DEV_WAIT_LIMIT);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-            }
-            if (lane == 0) {
-                st_relaxed_agent(st, LB_FLAG_PRE | ((excl + agg) & LB_VALUE));
-                s_excl = excl;
-            }
-        }
+        const uint32_t excl = look_back(status, tile, agg, threadIdx.x, dev_status);
+        if (threadIdx.x == 0) s_excl = excl;
     }
     __syncthreads();
     uint32_t run = s_excl + ex;
@@ -189,14 +190,10 @@ inline uint32_t scan_tiles_for(uint32_t n_max) {
     return t ? t : 1u;
 }
 
-// max_blocks > 0 caps the grid (workgroups then take several tiles): for
-// scans whose device count is usually far below the host bound n_max.
 template <class Get, class Emit, class Fin>
 inline void launch_scan(Get get, Emit emit, Fin fin, const uint32_t* n_dev, uint32_t n_max,
-                        uint32_t* status, uint32_t* dev_status, hipStream_t st,
-                        uint32_t max_blocks = 0) {
-    uint32_t tiles = scan_tiles_for(n_max);
-    if (max_blocks > 0 && tiles > max_blocks) tiles = max_blocks;
+                        uint32_t* status, uint32_t* dev_status, hipStream_t st) {
+    const uint32_t tiles = scan_tiles_for(n_max);
     if (scan_items_for(n_max) == 4u)
         scan_kernel<4, Get, Emit, Fin><<<dim3(tiles), dim3(SCAN_BLOCK), 0, st>>>(get, emit, fin, n_dev, n_max,
                                                                                  status, dev_status);

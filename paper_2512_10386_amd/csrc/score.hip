@@ -322,10 +322,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params p
         const uint32_t n1 = qe - qb;
         if (small && n1 <= SMALL_LEAF) continue;  // leaf_select_small_kernel
         if (n1 == 0) {
-            if (threadIdx.x == 0) {
-                if (role == 0u) P.leaf_r2cut[t] = 0.0f;
-                else P.leaf_rho_med[t] = 0.0;
-            }
+            if (threadIdx.x == 0 && role == 1u) P.leaf_rho_med[t] = 0.0;
             continue;
         }
         float cut = 0.0f;
@@ -371,7 +368,6 @@ __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params p
                     if (i >= n1) break;
                     P.p2[qb + i] = (kx[u] != NO_NBR && __uint_as_float(s_r2[i]) <= cut) ? 1 : 0;
                 }
-                if (threadIdx.x == 0) P.leaf_r2cut[t] = cut;
             } else {
                 leaf_median(LdsBits<unsigned long long>{s_rho}, n1, &med, s_hist, s_sel);
                 const double den = med * med + prm.eps;
@@ -416,7 +412,6 @@ __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params p
                 const bool insufficient = P.krec[qi].x == NO_NBR;
                 P.p2[qi] = (!insufficient && P.r2k[qi] <= cut) ? 1 : 0;
             }
-            if (threadIdx.x == 0) P.leaf_r2cut[t] = cut;
         } else {
             const double den = med * med + prm.eps;
             const double ha = prm.alpha / 2.0;
@@ -491,7 +486,7 @@ __global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params p
         const uint32_t n1 = qe - qb;
         if (n1 > SMALL_LEAF) continue;
         if (n1 == 0) {
-            if (lane == 0) { P.leaf_rho_med[t] = 0.0; P.leaf_r2cut[t] = 0.0f; }
+            if (lane == 0) P.leaf_rho_med[t] = 0.0;
             continue;
         }
         WaveVals r2v, rhov;
@@ -553,7 +548,7 @@ __global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params p
             P.afac_c[qi] = make_double2(pow_ha<SQRT>(rho / den, ha), 1.0 / (2.0 * sr * sr));
             P.gpow_p[qi] = pow_ha<SQRT>(rho, ha);
         }
-        if (lane == 0) { P.leaf_rho_med[t] = med; P.leaf_r2cut[t] = cut; }
+        if (lane == 0) P.leaf_rho_med[t] = med;
     }
 }
 
@@ -802,7 +797,6 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
         };
         if (n1 == 0) {
             put_outside_p1();
-            if (threadIdx.x == 0) P.leaf_m[t] = 0;
             continue;
         }
         if (n1 <= SEL_BATCH_MAX) {
@@ -865,7 +859,6 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
                 P.stage_c[qb + i] = st;
                 if (out.keep) out.put(ix[u], st, sv[u]);
             }
-            if (threadIdx.x == 0) P.leaf_m[t] = m;
             __syncthreads();
             continue;
         }
@@ -912,7 +905,6 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
             P.stage_c[qi] = st;
             if (out.keep) out.put(__float_as_uint(P.cand4[qi].w), st, st >= 2 ? P.score_c[qi] : 0.0);
         }
-        if (threadIdx.x == 0) P.leaf_m[t] = m;
         __syncthreads();
     }
     __syncthreads();  // s_list is refilled by the next round
@@ -1033,7 +1025,6 @@ __global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda, 
             for (uint32_t s = lb + 256u + lane; s < le; s += 64u)
                 if (!P.p1[s]) out.put(P.idx_a[s], 0, 0.0);
         }
-        if (lane == 0) P.leaf_m[t] = m;
     }
 }
 

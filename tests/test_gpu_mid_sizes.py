@@ -2,7 +2,7 @@
 by the usual parity bar (bit-exact discrete results, scores to 1e-5): one-wave
 selects and top-lambda with the outputs written there (above 3 * 2^16 points at
 leaf caps up to 256, above 2^19 up to 512, with and without leaves of more than
-256 P1 points), and the kNN and voxel kernels of large inputs (above 2^19 points)."""
+256 P1 points), and the kNN, plan and voxel kernels of large inputs (above 2^19 points)."""
 import numpy as np
 import pytest
 
@@ -19,17 +19,17 @@ def crowded(n, seed):
     return xyz[np.random.default_rng(seed).permutation(len(xyz))]
 
 
-@pytest.mark.parametrize("make,k,cap", [
-    (lambda: synth.lidar_frame(seed=3, n_az=3073)[0], 12, 256),      # 196,672 points: just above 3 * 2^16
-    (lambda: crowded(270_001, 4), 16, 256),
-    (lambda: crowded(540_001, 4), 8, 512),
-    (lambda: crowded(196_608, 5), 16, 256),                          # 3 * 2^16: workgroup selects
-    (lambda: synth.lidar_frame(seed=6, n_az=8193)[0], 12, 512)])     # 524,352 points: just above 2^19
-def test_mid_sizes(oracle, make, k, cap):
+@pytest.mark.parametrize("make,k,cap,chunk", [
+    (lambda: synth.lidar_frame(seed=3, n_az=3073)[0], 12, 256, 0),      # 196,672 points: just above 3 * 2^16
+    (lambda: crowded(270_001, 4), 16, 256, 0),
+    (lambda: crowded(540_001, 4), 8, 512, 1500),                     # chunked leaves in the parallel plan
+    (lambda: crowded(196_608, 5), 16, 256, 0),                       # 3 * 2^16: workgroup selects
+    (lambda: synth.lidar_frame(seed=6, n_az=8193)[0], 12, 512, 0)])     # 524,352 points: just above 2^19
+def test_mid_sizes(oracle, make, k, cap, chunk):
     from paper_2512_10386_amd.binding import Denoiser
     xyz = np.ascontiguousarray(make())
     ref = oracle.denoise(xyz, k=k, leaf_cap=cap)
-    den = Denoiser(0, k=k, leaf_cap=cap)
+    den = Denoiser(0, k=k, leaf_cap=cap, knn_chunk=chunk)
     try:
         compare(run_gpu(den, xyz), ref)
     finally:
