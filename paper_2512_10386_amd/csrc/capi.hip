@@ -160,6 +160,11 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.gpow_p = (double*)take(sizeof(double) * N);
     P.items = (KnnItem*)take(sizeof(KnnItem) * (size_t)P.items_max);
     P.plist = (uint64_t*)take(8 * (size_t)P.plist_max * k);
+    static_assert(sizeof(uint64_t) * 3 >= 6 * sizeof(uint32_t), "plist holds [3n] keys at least");
+    P.leaf_box = (uint32_t*)P.plist;
+    P.leaf_theta = (unsigned long long*)P.plist;
+    P.leaf_icut = (uint32_t*)(P.leaf_theta + N);
+    P.leaf_r2cut = (float*)(P.leaf_icut + N);
     P.bytes = off;
     return P;
 }
@@ -361,8 +366,9 @@ static gdn_status run(gdn_ctx* ctx, const gdn_params* p, const float* xyz, int64
     if (!xyz || !keep || !score || !kept_idx) return fail(ctx, GDN_EINVAL, "NULL array argument");
     if (!workspace) return fail(ctx, GDN_EINVAL, "workspace is NULL");
     if (((uintptr_t)workspace & 255u) != 0) return fail(ctx, GDN_EINVAL, "workspace must be 256-byte aligned");
-    const gdn::Plan P = make_plan((uint32_t)n, (uint32_t)nf, p->k, (char*)workspace);
+    gdn::Plan P = make_plan((uint32_t)n, (uint32_t)nf, p->k, (char*)workspace);
     if (workspace_bytes < P.bytes) return fail(ctx, GDN_ENOMEM, "workspace too small");
+    P.big_leaves = gdn::big_leaf_path(P.n, p->leaf_cap);
     const gdn::Params prm = to_params(p);
     CallEvents* ce = nullptr;
     if (record && ctx->timing) {

@@ -110,8 +110,24 @@ struct __align__(16) KnnItem {
 // frames 1014 and 886; at cap 512 250k 355 and 367, 900k 1175 and 1117; 500k
 // at cap 1024 703 and 718.
 constexpr uint32_t SMALL_LEAF = 256;
+constexpr uint32_t SEL_LDS_MAX = 2048;  // leaves up to this size are selected from LDS
 inline bool small_leaf_path(uint32_t n, int32_t leaf_cap) {
     return n > (1u << 20) || (n > (1u << 19) && leaf_cap <= 512) || (n > (3u << 16) && leaf_cap <= 256);
+}
+
+// Leaf caps above SEL_LDS_MAX (the octree switched off, or nearly) leave a
+// frame with few leaves of many points. One workgroup per leaf then holds the
+// whole frame up: one leaf of 20k points took 250 us in the voxel filter, 142
+// in the density select and 201 in top-lambda (now 15, 33 and 27). Such calls
+// run the per-point work of these steps over all positions instead, and only
+// the selects themselves in one (larger) workgroup per leaf. Inputs with many
+// leaves fill the chip with the per-leaf kernels: 500k points at cap 4096 take
+// 1339 us with those, 1387 this way; 120k 490 and 426, 100k in one leaf 3598
+// and 733. (Over-full leaves at the depth limit of smaller caps stay with the
+// per-leaf kernels.)
+inline bool big_leaf_path(uint32_t n, int32_t leaf_cap) {
+    return n > SEL_LDS_MAX && (uint32_t)leaf_cap > SEL_LDS_MAX &&
+           (n <= (1u << 18) || (n <= (1u << 20) && (uint32_t)leaf_cap >= n / 16u));
 }
 
 // Queries per kNN work item of inputs with n1 P1 points. A wave takes an
@@ -169,6 +185,7 @@ struct Plan {
     uint32_t* plan_status;    // [3][plan_tiles] (parallel kNN plan)
     uint32_t sort_tiles, scan_tiles, plan_tiles;
     uint32_t sort_items;      // keys per thread of the radix passes (4 or 16)
+    bool big_leaves;          // leaves of more than SEL_LDS_MAX points are ordinary here (big_leaf_path)
     uint32_t tq_max;          // queries per kNN work item, at most (KNN_TQ_SMALL or KNN_TQ)
     uint8_t* deepf;           // [n] 1 at sorted positions inside deep level-10 cells; between the two
                               // deep-cell kernels, 2 marks the start of a cell to re-sort (zeroed block)
@@ -229,6 +246,11 @@ struct Plan {
     uint32_t items_max;
     uint64_t* plist;          // [plist_max][k] partial top-k keys
     uint32_t plist_max;
+    // big leaves: short-lived arrays inside plist (before the kNN, then after its merge)
+    uint32_t* leaf_box;       // [6n] ordered-uint max of ~min and of max, per leaf
+    unsigned long long* leaf_theta;  // [n] top-lambda cut: key, and the largest index kept at that key
+    uint32_t* leaf_icut;      // [n]
+    float* leaf_r2cut;        // [n] percentile cut
 };
 
 // ------------------------------------------------------------------ helpers

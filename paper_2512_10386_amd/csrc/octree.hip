@@ -3,6 +3,7 @@
 // kNN work plan.
 #include "kernels.hpp"
 #include "scan.hpp"
+#include "voxel.hpp"
 #include "wave.hpp"
 
 namespace gdn {
@@ -104,6 +105,8 @@ __global__ __launch_bounds__(256) void boundary_flag_kernel(Plan P, uint32_t cap
     }
     const XcdPart R = xcd_part(P.n);
     for (uint32_t j = R.first; j < R.end; j += R.step) {
+        if (P.big_leaves)  // the leaf boxes of launch_big_voxel start empty
+            for (uint32_t a = 0; a < 6u; ++a) P.leaf_box[6 * (size_t)j + a] = 0u;
         const uint32_t i = P.idx_a[j];
         P.pos4[j] = make_float4(xyz[3 * (size_t)i], xyz[3 * (size_t)i + 1], xyz[3 * (size_t)i + 2], __uint_as_float(i));
         uint32_t f, fs, fe;
@@ -144,35 +147,6 @@ void launch_leaves(const Plan& P, const Params& prm, const float* xyz, hipStream
 // floor((x - min) / h) per axis in FP64, occupancy n(voxel(p)) by an
 // LDS-private hash (a per-leaf global region for leaves too big for LDS), and
 // P1 = occupancy >= n_v (Eq. 12).
-
-__device__ __forceinline__ uint32_t vox_hash(uint64_t k) {
-    return (uint32_t)((k * 0x9E3779B97F4A7C15ull) >> 32);
-}
-
-__device__ __forceinline__ uint64_t vox_key(float4 p, float mx_, float my_, float mz_, double h) {
-    double v[3] = {floor(((double)p.x - (double)mx_) / h), floor(((double)p.y - (double)my_) / h),
-                   floor(((double)p.z - (double)mz_) / h)};
-    uint64_t k = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        double f = v[a];
-        if (!(f >= 0.0)) f = 0.0;
-        if (f > (double)QMAX) f = (double)QMAX;
-        k |= (uint64_t)f << (21 * a);
-    }
-    return k;
-}
-
-// Leaf voxel size (Eq. 10, 11) from its fp32 bbox: h = beta * cbrt(V / nt)
-// rounded to fp32, 0 for a flat or degenerate leaf.
-__device__ __forceinline__ float leaf_voxel_size(const float* lo, const float* hi, uint32_t nt, double beta) {
-    double H[3];
-    for (int a = 0; a < 3; ++a) H[a] = (double)hi[a] - (double)lo[a];
-    const double V = (H[0] * H[1]) * H[2];
-    float h32 = (float)(beta * cbrt(V / (double)nt));
-    if (!(h32 > 0.0f) || !isfinite(h32)) h32 = 0.0f;
-    return h32;
-}
 
 // Small leaves (at most VOX_WAVE_MAX points) of large batches: one wave per
 // leaf with its own LDS table, no block barriers; every lane computes the
@@ -370,6 +344,10 @@ __global__ __launch_bounds__(VOX_BLOCK) void voxel_kernel(Plan P, double beta, u
 }
 
 void launch_voxel(const Plan& P, const Params& prm, hipStream_t st) {
+    if (P.big_leaves) {
+        launch_big_voxel(P, prm, st);
+        return;
+    }
     // the wave path pays off for the many small leaves of large batches
     const bool small = P.n > VOX_WAVE_MIN_N;
     if (small) {

@@ -4,14 +4,12 @@
 #include <climits>
 #include <cmath>
 
+#include "density.hpp"
 #include "kernels.hpp"
 #include "scan.hpp"
 #include "wave.hpp"
 
 namespace gdn {
-
-constexpr uint32_t NO_NBR = 0xFFFFFFFFu;
-constexpr double PI_D = 3.14159265358979323846;
 
 // ---------------------------------------------------------------- density
 //
@@ -31,88 +29,6 @@ __device__ __forceinline__ uint32_t pow2_at_least(uint32_t k) {
 __device__ __forceinline__ double seg_sum(double v, uint32_t kp) {
     for (uint32_t o = kp >> 1; o > 0; o >>= 1) v += __shfl_xor(v, (int)o, 64);
     return v;
-}
-
-// x^(alpha/2) of the density weight (Eq. 17): the square root for the
-// default alpha = 1 (a few instructions instead of a general FP64 power; the
-// two agree to an ulp), pow otherwise. The select kernels are instantiated
-// for either, so each holds only the code it runs.
-template <bool SQRT>
-__device__ __forceinline__ double pow_ha(double x, double ha) {
-    if constexpr (SQRT) return sqrt(x);
-    else return pow(x, ha);
-}
-
-// Density of P1 query qi. The list is sorted by fp32 d2, and fp32 d2 is
-// within ~6e-7 relative of the exact value, so only the neighbours whose fp32
-// d2 is within 2^-16 of the k-th can hold the FP64 maximum. Usually that is
-// the k-th alone (the (k-1)-th lies below), read from the dense record the
-// kNN writes; otherwise walk the list down from the k-th and stop at the
-// first one below. Stores r^2_K, rho and r densely (the selects run it for
-// their leaf's points, so the density needs no launch of its own).
-struct Dens {
-    float r2;
-    double rho, r64;
-    bool short_list;  // fewer than k candidates
-};
-
-// What the density of a query starts from: its k-th neighbour record and the
-// coordinates of the query and of that neighbour (the query's again when it
-// has none), all loaded at once.
-struct DensIn {
-    uint4 kr;
-    float4 cq, cj;
-};
-__device__ __forceinline__ DensIn density_load(const Plan& P, uint32_t qi) {
-    DensIn d;
-    d.kr = P.krec[qi];
-    d.cq = P.cand4[qi];
-    d.cj = P.cand4[d.kr.x < P.n ? d.kr.x : qi];
-    return d;
-}
-
-__device__ __forceinline__ Dens density_finish(const Plan& P, uint32_t k, uint32_t qi, const DensIn& in) {
-    const uint4 kr = in.kr;
-    const uint32_t jk = kr.x;
-    Dens out;
-    out.r2 = __uint_as_float(kr.z);
-    out.short_list = jk == NO_NBR;
-    if (out.short_list) {
-        out.rho = 0.0;
-        out.r64 = INFINITY;
-    } else {
-        // the query's coordinates: cand4 holds bit copies of the input
-        const double xi = in.cq.x, yi = in.cq.y, zi = in.cq.z;
-        // a neighbour's sorted copy of the input coordinates
-        auto d2_of = [&](const float4 cj) -> double {
-            const double dx = (double)cj.x - xi;
-            const double dy = (double)cj.y - yi;
-            const double dz = (double)cj.z - zi;
-            return dx * dx + dy * dy + dz * dz;
-        };
-        auto d2_to = [&](uint32_t j) -> double { return d2_of(P.cand4[j]); };
-        const float thr = out.r2 * (1.0f - 1.0f / 65536.0f);
-        double m2 = 0.0;
-        if (k == 1u || __uint_as_float(kr.y) < thr) {
-            if (jk < P.n) m2 = fmax(m2, d2_of(in.cj));
-        } else {
-            const uint32_t* nb = P.nbr + (size_t)qi * k;
-            const float* d2 = P.nbr_d2 + (size_t)qi * k;
-            for (int r = (int)k - 1; r >= 0; --r) {
-                if (d2[r] < thr) break;
-                const uint32_t j = nb[r];
-                if (j >= P.n) continue;
-                const double v = d2_to(j);
-                if (v > m2) m2 = v;
-            }
-        }
-        out.r64 = sqrt(m2);
-        out.rho = (double)k / ((4.0 / 3.0) * PI_D * (out.r64 * out.r64 * out.r64));
-    }
-    P.r2k[qi] = out.r2;
-    P.rho_c[qi] = out.rho;
-    P.r64_c[qi] = out.r64;
-    return out;
 }
 
 __device__ __forceinline__ Dens density_at(const Plan& P, const float* __restrict__ xyz, uint32_t k, uint32_t qi) {
@@ -233,7 +149,6 @@ struct LdsBits {
     __device__ T operator()(uint32_t i) const { return v[i]; }
 };
 
-constexpr uint32_t SEL_LDS_MAX = 2048;  // leaves up to this size are selected from LDS
 constexpr uint32_t SEL_BATCH_MAX = 1024;  // leaves up to this size: each thread loads its points at once
 constexpr uint32_t PACKED_OUT_MIN_N = 1u << 20;  // above: outputs scattered as packed records
 
@@ -278,10 +193,7 @@ __device__ uint32_t block_leaf_round(const Plan& P, uint32_t base, uint32_t nl, 
 
 template <class RG>
 __device__ float leaf_cut(RG r2, uint32_t n1, double q, uint32_t* s_hist, uint32_t* s_sel) {
-    double cd = ceil((double)n1 * q / 100.0 + 0.5);
-    if (cd < 1.0) cd = 1.0;
-    if (cd > (double)n1) cd = (double)n1;
-    const uint32_t c = (uint32_t)cd;
+    const uint32_t c = percentile_rank(n1, q);
     return __uint_as_float(block_select<uint32_t>(r2, n1, n1 - c, s_hist, s_sel));
 }
 
@@ -523,10 +435,7 @@ __global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params p
                 shortv[j] = dn.short_list;
             }
         }
-        double cd = ceil((double)n1 * prm.rho_percentile / 100.0 + 0.5);
-        if (cd < 1.0) cd = 1.0;
-        if (cd > (double)n1) cd = (double)n1;
-        const uint32_t c = (uint32_t)cd;
+        const uint32_t c = percentile_rank(n1, prm.rho_percentile);
         const float cut = __uint_as_float((uint32_t)wave_rank_value(r2v, n1, lane, n1 - c, hist));
         double med;
         if (n1 & 1u) {
@@ -553,6 +462,10 @@ __global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params p
 }
 
 void launch_leaf_select(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
+    if (P.big_leaves) {
+        launch_big_select(P, prm, st);
+        return;
+    }
     const bool small = small_leaf_path(P.n, prm.leaf_cap);
     const bool sq = prm.alpha == 1.0;
     if (small) {
@@ -686,11 +599,6 @@ void launch_score(const Plan& P, const Params& prm, hipStream_t st) {
 // original index asc); a NaN score ranks below every number. The m-th largest
 // score key is found by radix select, remaining ties by a select on indices.
 
-__device__ __forceinline__ unsigned long long score_key(bool p2, double f) {
-    if (!p2) return 0ull;
-    if (isnan(f)) return 1ull;
-    return (unsigned long long)__double_as_longlong(f) + 2ull;
-}
 struct ScoreKey {
     const double* score;
     const uint8_t* p2;
@@ -736,20 +644,6 @@ struct CandIdx {
     const float4* cand4;
     uint32_t qb;
     __device__ uint32_t operator()(uint32_t i) const { return __float_as_uint(cand4[qb + i].w); }
-};
-
-// Optional outputs (up to 2^20 points): keep, score and stage in input order
-// for every point of each leaf, as outputs_kernel writes them, so that pass is
-// not needed.
-struct ToplOut {
-    uint8_t* keep;
-    float* score;
-    uint8_t* stage;
-    __device__ void put(uint32_t i, uint8_t st, double sc) const {
-        keep[i] = st == 3;
-        score[i] = st >= 2 ? (float)sc : -1.0f;
-        if (stage) stage[i] = st;
-    }
 };
 
 __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, bool small, ToplOut out) {
@@ -837,11 +731,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
             if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_cnt, c);
             __syncthreads();
             const uint32_t n2 = s_cnt;
-            uint32_t m = 0;
-            if (n2 > 0) {
-                const double mf = ceil(lambda * (double)n2);
-                m = mf >= (double)n2 ? n2 : (uint32_t)mf;
-            }
+            const uint32_t m = topl_count(lambda, n2);
             unsigned long long theta = ~0ull;
             uint32_t idx_cut = 0;
             if (m > 0)
@@ -872,11 +762,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
         if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_cnt, c);
         __syncthreads();
         const uint32_t n2 = s_cnt;
-        uint32_t m = 0;
-        if (n2 > 0) {
-            const double mf = ceil(lambda * (double)n2);
-            m = mf >= (double)n2 ? n2 : (uint32_t)mf;
-        }
+        const uint32_t m = topl_count(lambda, n2);
         const ScoreKey key{P.score_c, P.p2, qb};
         unsigned long long theta = ~0ull;
         uint32_t idx_cut = 0;
@@ -965,11 +851,7 @@ __global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda, 
             oi[j] = in ? ixv[j] : 0xFFFFFFFFu;
             n2 += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in && p2v[j] != 0u));
         }
-        uint32_t m = 0;
-        if (n2 > 0) {
-            const double mf = ceil(lambda * (double)n2);
-            m = mf >= (double)n2 ? n2 : (uint32_t)mf;
-        }
+        const uint32_t m = topl_count(lambda, n2);
         unsigned long long theta = ~0ull;
         uint32_t need = 0;
         bool ties_cut = false;
@@ -1064,6 +946,10 @@ bool launch_topl(const Plan& P, const Params& prm, uint8_t* keep, float* score, 
     // inputs scatter them as packed records)
     const bool write = P.n <= PACKED_OUT_MIN_N;
     const ToplOut out{write ? keep : nullptr, score, stage};
+    if (P.big_leaves) {  // (up to 2^20 points)
+        launch_big_topl(P, prm.keep_ratio, out, st);
+        return true;
+    }
     if (small) {
         unsigned wb = (P.n / 128 + 3) / 4;
         if (wb > 8192) wb = 8192;
