@@ -4,6 +4,7 @@
 // needs, and the whole-key re-sort of deep level-10 cells.
 #include "kernels.hpp"
 #include "radix.hpp"
+#include "wave.hpp"
 
 namespace gdn {
 
@@ -563,6 +564,106 @@ __device__ void sort_cell(const Plan& P, uint32_t a, uint32_t b, bool deep, uint
     __syncthreads();
 }
 
+// The same for a cell of up to SEG_BLOCK * SEG_ITEMS points, in LDS: five
+// passes over key bits 0..39, the points in registers between them, read and
+// written once.
+constexpr int SEG_ITEMS = 4;
+constexpr uint32_t SEG_LDS = (uint32_t)SEG_BLOCK * SEG_ITEMS;
+__device__ void sort_cell_lds(const Plan& P, uint32_t a, uint32_t b, bool deep, uint64_t* s_k, uint32_t* s_v,
+                              uint32_t* s_base, uint32_t (*s_w)[256], uint32_t* s_scan) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const uint32_t n = b - a;
+    uint64_t key[SEG_ITEMS];
+    uint32_t val[SEG_ITEMS];
+    auto at = [&](int i) { return (uint32_t)(wave * 64 * SEG_ITEMS + i * 64 + lane); };
+#pragma unroll
+    for (int i = 0; i < SEG_ITEMS; ++i) {
+        const bool ok = at(i) < n;
+        key[i] = ok ? P.keys_a[a + at(i)] : 0ull;
+        val[i] = ok ? P.idx_a[a + at(i)] : 0u;
+    }
+    for (int shift = 0; shift < 40; shift += 8) {
+#pragma unroll
+        for (int w = 0; w < SEG_BLOCK / 64; ++w) s_w[w][tid] = 0u;
+        __syncthreads();
+        uint32_t dig[SEG_ITEMS], rank[SEG_ITEMS];
+#pragma unroll
+        for (int i = 0; i < SEG_ITEMS; ++i) {
+            const bool ok = at(i) < n;
+            const uint32_t dg = (uint32_t)(key[i] >> shift) & 255u;
+            uint64_t m = __ballot(ok);
+#pragma unroll
+            for (int bt = 0; bt < 8; ++bt) {
+                const bool bit = (dg >> bt) & 1u;
+                const uint64_t bb = __ballot(bit);
+                m &= bit ? bb : ~bb;
+            }
+            const uint32_t before = (uint32_t)__popcll(m & lt_mask);
+            const uint32_t wb = ok ? s_w[wave][dg] : 0u;
+            dig[i] = dg;
+            rank[i] = wb + before;
+            if (ok && (m >> lane) == 1ull) s_w[wave][dg] = wb + (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        uint32_t run = 0;
+#pragma unroll
+        for (int w = 0; w < SEG_BLOCK / 64; ++w) {
+            const uint32_t c = s_w[w][tid];
+            s_w[w][tid] = run;
+            run += c;
+        }
+        uint32_t tot;
+        s_base[tid] = block_excl_scan(run, s_scan, &tot);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SEG_ITEMS; ++i)
+            if (at(i) < n) {
+                const uint32_t o = s_base[dig[i]] + s_w[wave][dig[i]] + rank[i];
+                s_k[o] = key[i];
+                s_v[o] = val[i];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SEG_ITEMS; ++i)
+            if (at(i) < n) {
+                key[i] = s_k[at(i)];
+                val[i] = s_v[at(i)];
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SEG_ITEMS; ++i)
+        if (at(i) < n) {
+            P.keys_a[a + at(i)] = key[i];
+            P.idx_a[a + at(i)] = val[i];
+            if (deep) P.deepf[a + at(i)] = 1u;
+        }
+    if (!deep && tid == 0) P.deepf[a] = 0u;
+}
+
+// The same for a cell of up to 64 points, by one wave: a bitonic sort of the
+// cell's own key bits (0..32) and the position (points of equal keys keep
+// their order).
+__device__ void sort_cell_wave(const Plan& P, uint32_t a, uint32_t b, bool deep, uint32_t lane) {
+    const bool ok = lane < b - a;
+    const uint64_t key = ok ? P.keys_a[a + lane] : 0ull;
+    const uint32_t val = ok ? P.idx_a[a + lane] : 0u;
+    const unsigned long long own = key & ((1ull << CELL_SHIFT) - 1ull);
+    const unsigned long long v = ok ? (own << 6) | lane : ~0ull >> 1;
+    const unsigned long long srt = ~sort64_desc(~v, lane);
+    const int src = (int)((uint32_t)srt & 63u);
+    const uint32_t klo = (uint32_t)__shfl((int)(uint32_t)key, src, 64);
+    const uint32_t khi = (uint32_t)__shfl((int)(uint32_t)(key >> 32), src, 64);
+    const uint32_t vs = (uint32_t)__shfl((int)val, src, 64);
+    if (ok) {
+        P.keys_a[a + lane] = ((uint64_t)khi << 32) | klo;
+        P.idx_a[a + lane] = vs;
+        if (deep) P.deepf[a + lane] = 1u;
+    }
+    if (!deep && lane == 0u) P.deepf[a] = 0u;
+}
+
 // Frame of sorted position s and its range [fs, fe).
 __device__ __forceinline__ uint32_t frame_range(const Plan& P, const uint32_t* s_foff, bool lds, uint32_t s,
                                                 uint32_t* fs, uint32_t* fe) {
@@ -594,10 +695,13 @@ __device__ __forceinline__ uint32_t cell_lower_bound(const uint64_t* keys, uint3
 // its frame's depth limit ("deep"). Its leaves lie below level 10, and so do
 // the halo cells around them, which reach into the 26 level-10 cells next to
 // it: every one of those needs its points in whole-key order too, so that a
-// deeper cell is one contiguous key range. One thread per sorted position: a
-// position that starts a deep cell marks (deepf = 2) the start of that cell
-// and of each non-empty neighbouring cell in its frame. The marks are plain
-// stores of one value, so cells marked twice need no atomics.
+// deeper cell is one contiguous key range. One thread per sorted position
+// finds the positions that start a deep cell; the block then marks (deepf = 2)
+// the start of each such cell and of each non-empty neighbouring cell in its
+// frame, a thread per (cell, neighbour): each is a chain of ~20 dependent
+// loads, and one thread walking all 26 made this 74 us on a 1.2M sweep (11
+// now). The marks are plain stores of one value, so cells marked twice need no
+// atomics.
 // LDS: the frame offsets are staged in LDS (batches of fewer than
 // SORT_FOFF_LDS frames), fixed at compile time so that they are read with LDS
 // or global instructions, not generic ones.
@@ -608,29 +712,52 @@ __global__ __launch_bounds__(SEG_BLOCK) void deep_mark_kernel(Plan P, uint32_t c
     if (lds)
         for (uint32_t i = threadIdx.x; i <= P.nf; i += blockDim.x) s_foff[i] = P.foff[i];
     __syncthreads();
-    for (uint32_t s = blockIdx.x * SEG_BLOCK + threadIdx.x; s < P.n; s += gridDim.x * SEG_BLOCK) {
-        uint32_t fs, fe;
-        const uint32_t f = frame_range(P, s_foff, lds, s, &fs, &fe);
-        const uint64_t c = P.keys_a[s] >> CELL_SHIFT;
-        const bool start = P.fc[f].dmax > SORT_SHORT_LEVEL && (s == fs || (P.keys_a[s - 1] >> CELL_SHIFT) != c) &&
-                           (uint64_t)s + cap < fe && (P.keys_a[s + cap] >> CELL_SHIFT) == c;
-        if (!start) continue;
-        P.deepf[s] = 2u;
-        const int32_t cx = (int32_t)compact3(c), cy = (int32_t)compact3(c >> 1), cz = (int32_t)compact3(c >> 2);
-        const int32_t side = 1 << SORT_SHORT_LEVEL;
-        for (int g = 0; g < 27; ++g) {
-            const int32_t nx = cx + g % 3 - 1, ny = cy + (g / 3) % 3 - 1, nz = cz + g / 9 - 1;
-            if (g == 13 || nx < 0 || ny < 0 || nz < 0 || nx >= side || ny >= side || nz >= side) continue;
+    __shared__ uint32_t s_start[SEG_BLOCK];
+    __shared__ uint32_t s_n;
+    for (uint32_t base = blockIdx.x * SEG_BLOCK; base < P.n; base += gridDim.x * SEG_BLOCK) {
+        if (threadIdx.x == 0) s_n = 0u;
+        __syncthreads();
+        const uint32_t s = base + threadIdx.x;
+        if (s < P.n) {
+            uint32_t fs, fe;
+            const uint32_t f = frame_range(P, s_foff, lds, s, &fs, &fe);
+            const uint64_t c = P.keys_a[s] >> CELL_SHIFT;
+            const bool start = P.fc[f].dmax > SORT_SHORT_LEVEL &&
+                               (s == fs || (P.keys_a[s - 1] >> CELL_SHIFT) != c) && (uint64_t)s + cap < fe &&
+                               (P.keys_a[s + cap] >> CELL_SHIFT) == c;
+            if (start) s_start[atomicAdd(&s_n, 1u)] = s;
+        }
+        __syncthreads();
+        const uint32_t ns = s_n;
+        for (uint32_t e = threadIdx.x; e < ns * 32u; e += SEG_BLOCK) {
+            const uint32_t q0 = s_start[e / 32u];
+            const int g = (int)(e % 32u);
+            if (g >= 27) continue;
+            if (g == 13) {
+                P.deepf[q0] = 2u;
+                continue;
+            }
+            uint32_t fs, fe;
+            (void)frame_range(P, s_foff, lds, q0, &fs, &fe);
+            const uint64_t c = P.keys_a[q0] >> CELL_SHIFT;
+            const int32_t nx = (int32_t)compact3(c) + g % 3 - 1, ny = (int32_t)compact3(c >> 1) + (g / 3) % 3 - 1,
+                          nz = (int32_t)compact3(c >> 2) + g / 9 - 1;
+            const int32_t side = 1 << SORT_SHORT_LEVEL;
+            if (nx < 0 || ny < 0 || nz < 0 || nx >= side || ny >= side || nz >= side) continue;
             const uint64_t nc = morton3((uint32_t)nx, (uint32_t)ny, (uint32_t)nz);
             const uint32_t q = cell_lower_bound(P.keys_a, fs, fe, nc);
             if (q < fe && (P.keys_a[q] >> CELL_SHIFT) == nc) P.deepf[q] = 2u;
         }
+        __syncthreads();  // the list is refilled by the next round
     }
 }
 
 // One thread per sorted position: a marked position starts a cell to re-sort;
 // it finds the cell's end, and the block then sorts the cells that start
-// among its positions (deep ones flagged, the others unmarked). Blocks that
+// among its positions (deep ones flagged, the others unmarked): cells of up to
+// 64 points a wave each, up to SEG_LDS points in LDS, larger ones through
+// memory. (All of them through memory, one after another: 155 us on a 1.2M
+// sweep, 32 now.) Blocks that
 // read keys of a cell another block is sorting compare cell prefixes only,
 // which the sort does not change; a mark is only read by the thread of its
 // own position, and only that cell's block rewrites it.
@@ -641,12 +768,26 @@ __global__ __launch_bounds__(SEG_BLOCK) void deep_cells_kernel(Plan P, uint32_t 
     __shared__ uint32_t s_scan[SEG_BLOCK / 64 + 1];
     __shared__ uint2 s_seg[SEG_BLOCK];
     __shared__ uint8_t s_deep[SEG_BLOCK];
+    __shared__ uint64_t s_k[SEG_LDS];
+    __shared__ uint32_t s_v[SEG_LDS];
     __shared__ uint32_t s_nseg;
     __shared__ uint32_t s_foff[SORT_FOFF_LDS];  // batches of fewer frames search the offsets here
     constexpr bool lds = LDS;
     if (lds)
         for (uint32_t i = threadIdx.x; i <= P.nf; i += blockDim.x) s_foff[i] = P.foff[i];
-    for (uint32_t base = blockIdx.x * SEG_BLOCK; base < P.n; base += gridDim.x * SEG_BLOCK) {
+    // rounds of SEG_BLOCK positions, whose marks are read four rounds ahead:
+    // those without one, nearly all of them, end there
+    constexpr uint32_t U = 4;
+    const uint32_t stride = gridDim.x * SEG_BLOCK;  // (at most 2^20)
+    for (uint32_t base0 = blockIdx.x * SEG_BLOCK; base0 < P.n; base0 += U * stride) {
+    // (four flags per load; they are padded with zeros past n)
+    static_assert(U * SEG_BLOCK == 4 * SEG_BLOCK, "a load per thread covers the rounds");
+    const uint32_t s4 = base0 + threadIdx.x / (SEG_BLOCK / U) * stride + threadIdx.x % (SEG_BLOCK / U) * 4u;
+    const uint32_t f4 = s4 < P.n ? *(const uint32_t*)(P.deepf + s4) : 0u;
+    if (!__syncthreads_or((int)(f4 & 0x02020202u))) continue;
+    for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t base = base0 + u * stride;
+        if (base >= P.n) break;
         if (threadIdx.x == 0) s_nseg = 0u;
         __syncthreads();
         const uint32_t s = base + threadIdx.x;
@@ -654,15 +795,33 @@ __global__ __launch_bounds__(SEG_BLOCK) void deep_cells_kernel(Plan P, uint32_t 
             uint32_t fs, fe;
             const uint32_t f = frame_range(P, s_foff, lds, s, &fs, &fe);
             const uint64_t c = P.keys_a[s] >> CELL_SHIFT;
-            const uint32_t e = cell_lower_bound(P.keys_a, s + 1u, fe, c + 1u);
+            // the cell's end: doubling steps, then a search of the last one
+            uint32_t lo = s, step = 64u;
+            while (fe - lo > step && (P.keys_a[lo + step] >> CELL_SHIFT) == c) {
+                lo += step;
+                step *= 2u;
+            }
+            const uint32_t e = cell_lower_bound(P.keys_a, lo + 1u, fe - lo > step ? lo + step : fe, c + 1u);
             const uint32_t slot = atomicAdd(&s_nseg, 1u);
             s_seg[slot] = make_uint2(s, e);
             s_deep[slot] = (uint8_t)(P.fc[f].dmax > SORT_SHORT_LEVEL && e - s > cap);
         }
         __syncthreads();
         const uint32_t ns = s_nseg;
-        for (uint32_t g = 0; g < ns; ++g) sort_cell(P, s_seg[g].x, s_seg[g].y, s_deep[g] != 0u, s_base, s_w, s_scan);
+        for (uint32_t g = threadIdx.x >> 6; g < ns; g += SEG_BLOCK / 64)
+            if (s_seg[g].y - s_seg[g].x <= 64u)
+                sort_cell_wave(P, s_seg[g].x, s_seg[g].y, s_deep[g] != 0u, threadIdx.x & 63u);
+        for (uint32_t g = 0; g < ns; ++g) {
+            const uint2 r = s_seg[g];
+            if (r.y - r.x <= 64u) continue;
+            if (r.y - r.x <= SEG_LDS)
+                sort_cell_lds(P, r.x, r.y, s_deep[g] != 0u, s_k, s_v, s_base, s_w, s_scan);
+            else
+                sort_cell(P, r.x, r.y, s_deep[g] != 0u, s_base, s_w, s_scan);
+            __syncthreads();
+        }
         __syncthreads();
+    }
     }
 }
 
