@@ -52,6 +52,7 @@ constexpr int PEND = 64;     // pending keys per query
 constexpr int PEND_HALF = 32;  // pending keys a half-wave merge takes (k <= 32)
 constexpr uint32_t KNN_POS_MIN_N = 1u << 19;  // above: pending buffers of positions
 constexpr int KNN_NB = 4;      // needed groups held in registers at a time
+constexpr int DRAIN_N = 4;     // queries whose final lists are sorted side by side
 
 __device__ __forceinline__ float dist2(const float4 q, const float4 c) {
     const float dx = c.x - q.x, dy = c.y - q.y, dz = c.z - q.z;
@@ -263,15 +264,18 @@ constexpr int VMCNT0 = (7 << 4) | (15 << 8);
 // The final lists of a tile's qn queries (in LDS, k keys each), eight
 // queries at a time: their position lookups are issued before any store, so
 // the tile waits for a round trip per eight queries instead of per query.
+// `skip`: bit j, query j is already written.
 __device__ __forceinline__ void write_tile(const Plan& P, const unsigned long long* s_list, uint32_t q0, uint32_t qn,
-                                           uint32_t k, uint32_t lane) {
+                                           uint32_t k, uint32_t lane, uint32_t skip = 0u) {
     constexpr int B = 8;
     for (uint32_t j0 = 0; j0 < qn; j0 += (uint32_t)B) {
         unsigned long long v[B];
         uint32_t pj[B];
 #pragma unroll
         for (int j = 0; j < B; ++j) {
-            v[j] = (j0 + (uint32_t)j < qn && lane < k) ? s_list[(j0 + (uint32_t)j) * k + lane] : KEY_EMPTY;
+            v[j] = (j0 + (uint32_t)j < qn && lane < k && !((skip >> (j0 + (uint32_t)j)) & 1u))
+                       ? s_list[(j0 + (uint32_t)j) * k + lane]
+                       : KEY_EMPTY;
             pj[j] = NONE32;
         }
 #pragma unroll
@@ -285,6 +289,7 @@ __device__ __forceinline__ void write_tile(const Plan& P, const unsigned long lo
 #pragma unroll
         for (int j = 0; j < B; ++j) {
             if (j0 + (uint32_t)j >= qn) break;
+            if ((skip >> (j0 + (uint32_t)j)) & 1u) continue;
             const uint32_t qi = q0 + j0 + (uint32_t)j;
             const bool ok = lane < k && real_entry(v[j]);
             const float d = ok ? __uint_as_float((uint32_t)(v[j] >> 32)) : INFINITY;
@@ -363,6 +368,147 @@ __device__ __forceinline__ unsigned long long sort_keys_desc(unsigned long long 
     const bool near = lane >= 1u && (s >> 6) == (p >> 6) && (s >> 6) != EMPTY_TOP;
     if (__builtin_amdgcn_ballot_w64(near) == 0ull) return shfl64(v, (int)(s & 63u));
     return sort64_desc(v, lane);
+}
+
+// Ascending order of one 32-bit key per lane and query, by counting: a
+// query's pending distances lie between 0 and its bound, spread about evenly
+// (the points of a surface fill its d2 range evenly), so a counting sort over
+// 64 equal buckets of that range leaves the keys almost in order, and
+// exchanges with the neighbouring lanes finish it. `d` the real keys' distances
+// (the others, real = false, end behind them in any order), `scale` buckets per
+// unit of d2, `hist` 64 words of LDS per query. N queries side by side overlap
+// their chains of LDS exchanges. False if a few rounds of exchanges were not
+// enough (many distances in one bucket): the keys are then as they were.
+template <int N>
+__device__ __forceinline__ bool bucket_sort_u32(uint32_t (&key)[N], const float (&d)[N], const bool (&real)[N],
+                                                const float (&scale)[N], uint32_t lane, uint32_t* const (&hist)[N]) {
+    uint32_t hb[N], rank[N], c[N], v[N];
+    unsigned long long rm[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        hb[i] = min((uint32_t)(d[i] * scale[i]), 63u);
+        hist[i][lane] = 0u;
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        rank[i] = 0u;
+        if (real[i]) rank[i] = atomicAdd(&hist[i][hb[i]], 1u);
+        rm[i] = __builtin_amdgcn_ballot_w64(real[i]);
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < N; ++i) c[i] = hist[i][lane];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        // inclusive scan over the wave: row shifts, then row broadcasts
+        uint32_t inc = c[i];
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false);  // row_shr:1
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false);  // row_shr:2
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false);  // row_shr:4
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false);  // row_shr:8
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false);  // row_bcast:15
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false);  // row_bcast:31
+        c[i] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(hb[i] << 2), (int)(inc - c[i]));
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t before =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(rm[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rm[i], 0u));
+        const uint32_t dest = real[i] ? c[i] + rank[i] : (uint32_t)__popcll(rm[i]) + lane - before;
+        v[i] = (uint32_t)__builtin_amdgcn_ds_permute((int)(dest << 2), (int)key[i]);
+    }
+    const bool odd = (lane & 1u) != 0u;
+#pragma nounroll
+    for (int round = 0; round < 4; ++round) {
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            bad = bad || v[i] < (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x138, 0xF, 0xF, false);  // wave_shr:1
+        if (__builtin_amdgcn_ballot_w64(bad) == 0ull) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) key[i] = v[i];
+            return true;
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            v[i] = cx<1>(v[i], lane);
+            // pairs (1, 2), (3, 4), ...
+            const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x138, 0xF, 0xF, false);
+            const uint32_t next =
+                (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v[i], 0x130, 0xF, 0xF, false);  // wave_shl:1
+            v[i] = odd ? min(v[i], next) : max(v[i], prev);
+        }
+    }
+    return false;
+}
+
+// The final lists of N queries whose pending candidates (P1 positions) were
+// never merged into a list, which therefore holds placeholders only (tau,
+// 0xFFFFFFFF) that exceed every pending key: the pending keys in order, at
+// most k of them, written straight from registers. The order is by 32-bit keys
+// (the top 26 bits of d2 and the source lane) and exact unless two real keys
+// among the first k + 1 agree on those bits; then the 64-bit network runs and
+// the positions are looked up again. `scale` 64 over the query's bound, +inf if
+// it has no usable one (the 32-bit network then sorts). The drain is a third of
+// the kernel on large inputs (720 of 2060 us on the 6.2M-point batch at k = 32):
+// written from registers the positions need no lookup by index and no trip
+// through the list (-83 us), the counting sort saves instructions (-30) and
+// four queries side by side hide its chains (-34; eight spill registers, +600).
+template <int N>
+__device__ __forceinline__ void write_pending(const Plan& P, const float4* __restrict__ cand4, uint32_t k,
+                                              uint32_t lane, const uint32_t (&qi)[N], const float4 (&q)[N],
+                                              uint32_t* const (&pend)[N], const uint32_t (&cnt)[N],
+                                              const float (&scale)[N]) {
+    wave_lds_fence();
+    uint32_t pos[N], key[N], idx[N];
+    float d[N];
+    bool real[N], usable = true;
+#pragma unroll
+    for (int i = 0; i < N; ++i) pos[i] = lane < cnt[i] ? pend[i][lane] : qi[i];
+    float4 c[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) c[i] = cand4[pos[i]];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        d[i] = __uint_as_float(__float_as_uint(dist2(q[i], c[i])) & 0x7FFFFFFFu);
+        idx[i] = __float_as_uint(c[i].w);
+        real[i] = pos[i] != qi[i];  // not the query itself
+        key[i] = real[i] ? (__float_as_uint(d[i]) & ~63u) | lane : 0xFFFFFFFFu;
+        usable = usable && scale[i] < INFINITY;
+    }
+    wave_lds_fence();  // the buffers' words count the buckets now
+    if (!usable || !bucket_sort_u32<N>(key, d, real, scale, lane, pend)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) key[i] = sort64_u32<true>(key[i], lane);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t p = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)key[i], 0x138, 0xF, 0xF, false);  // wave_shr:1
+        const bool near = lane <= k && (key[i] >> 6) == (p >> 6) && key[i] != 0xFFFFFFFFu;
+        uint32_t pj, db;
+        if (__builtin_amdgcn_ballot_w64(near) == 0ull) {
+            const int src = (int)(key[i] << 2) & 0xFC;
+            pj = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)pos[i]);
+            db = (uint32_t)__builtin_amdgcn_ds_bpermute(src, __float_as_int(d[i]));
+            if (key[i] == 0xFFFFFFFFu) {
+                pj = NONE32;
+                db = 0x7F800000u;
+            }
+        } else {
+            unsigned long long v = real[i] ? make_key(d[i], idx[i]) : KEY_EMPTY;
+            v = ~sort64_desc(~v, lane);
+            const bool ok = v != KEY_EMPTY;
+            pj = lane < k && ok ? P.inv_p1[(uint32_t)v] : NONE32;
+            db = ok ? (uint32_t)(v >> 32) : 0x7F800000u;
+        }
+        const uint32_t db1 = (uint32_t)__builtin_amdgcn_update_dpp((int)db, (int)db, 0x138, 0xF, 0xF, false);
+        if (lane < k) {
+            P.nbr[(size_t)qi[i] * k + lane] = pj;
+            P.nbr_d2[(size_t)qi[i] * k + lane] = __uint_as_float(db);
+            if (lane == k - 1) P.krec[qi[i]] = make_uint4(pj, db1, db, 0u);
+        }
+    }
 }
 
 // Merge query j's pending candidates into its list, dropping the query's own
@@ -446,7 +592,7 @@ __device__ __forceinline__ void flush_half(unsigned long long* __restrict__ lst0
 // per SIMD, which is what their grid launches anyway; large inputs run 5
 // waves per SIMD and lose more to the lower occupancy than they gain.
 template <bool POS, int Q, bool PREFETCH = !POS>
-__global__ __launch_bounds__(64) void knn_group_kernel(Plan P, const float4* __restrict__ cand4, int kk) {
+__global__ __launch_bounds__(64, POS ? 5 : 4) void knn_group_kernel(Plan P, const float4* __restrict__ cand4, int kk) {
     using PT = typename Pending<POS>::T;
     static_assert(Q <= 32, "tile shape (a query mask per group fits 32 bits)");
     extern __shared__ unsigned long long s_dyn[];
@@ -740,6 +886,55 @@ __global__ __launch_bounds__(64) void knn_group_kernel(Plan P, const float4* __r
                 }
             }
         }
+        uint32_t written = 0;  // bit j: query j's final list is written
+        if constexpr (POS) {
+            // queries whose buffer was never merged go straight to memory, DRAIN_N
+            // at a time; the others, and chunks, through their lists
+            // (buckets over the query's bound, +inf: no usable bound)
+            const float scale = worst > 0.0f && worst < INFINITY ? 64.0f / worst : INFINITY;
+            auto scale_of = [&](uint32_t j) {
+                return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scale), (int)j));
+            };
+            auto cnt_of = [&](uint32_t j) { return (uint32_t)__builtin_amdgcn_readlane((int)pcnt, (int)j); };
+            const uint32_t all = qn < 32u ? (1u << qn) - 1u : 0xFFFFFFFFu;
+            uint32_t direct = nch > 1 ? 0u : all & ~(uint32_t)merged;
+            written = direct;
+            uint32_t rest = all & ~direct;
+            while (direct != 0u) {
+                constexpr int N = DRAIN_N;
+                uint32_t js[N], left = direct;
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    js[i] = left != 0u ? (uint32_t)__ffs((int)left) - 1u : 0u;
+                    left &= left - 1u;
+                }
+                auto pend_of = [&](uint32_t j) { return s_pend + (size_t)j * PEND; };
+                if ((uint32_t)__popc(direct) >= (uint32_t)N) {
+                    static_assert(N == 4, "the lists below");
+                    write_pending<N>(
+                        P, cand4, k, lane, {w.q0 + js[0], w.q0 + js[1], w.q0 + js[2], w.q0 + js[3]},
+                        {query_of(qv, js[0]), query_of(qv, js[1]), query_of(qv, js[2]), query_of(qv, js[3])},
+                        {pend_of(js[0]), pend_of(js[1]), pend_of(js[2]), pend_of(js[3])},
+                        {cnt_of(js[0]), cnt_of(js[1]), cnt_of(js[2]), cnt_of(js[3])},
+                        {scale_of(js[0]), scale_of(js[1]), scale_of(js[2]), scale_of(js[3])});
+                    direct = left;
+                } else {
+                    write_pending<1>(P, cand4, k, lane, {w.q0 + js[0]}, {query_of(qv, js[0])}, {pend_of(js[0])},
+                                     {cnt_of(js[0])}, {scale_of(js[0])});
+                    direct &= direct - 1u;
+                }
+            }
+            while (rest != 0u) {
+                const uint32_t j = (uint32_t)__ffs((int)rest) - 1u;
+                rest &= rest - 1u;
+                const uint32_t cnt = cnt_of(j);
+                const unsigned long long selfkey =
+                    (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(__float_as_int(qv.w), (int)j);
+                if (cnt)
+                    (void)flush<POS>(s_list + (size_t)j * k, s_pend + (size_t)j * PEND, cnt, lane, k, selfkey, cand4,
+                                     query_of(qv, j), ((merged >> j) & 1ull) == 0ull);
+            }
+        } else
         // drain the pending buffers: when k <= 32, two queries per merge if
         // both hold at most 32 pending keys
         if (half) {
@@ -784,7 +979,7 @@ __global__ __launch_bounds__(64) void knn_group_kernel(Plan P, const float4* __r
             for (uint32_t j = 0; j < qn; ++j)
                 if (lane < k) base[((size_t)(w.q0 + j - qb) * nch + w.chunk) * k + lane] = s_list[j * k + lane];
         } else {
-            write_tile(P, s_list, w.q0, qn, k, lane);
+            write_tile(P, s_list, w.q0, qn, k, lane, written);
         }
         wave_lds_fence();
         it = n_items;

@@ -19,6 +19,26 @@ def crowded(n, seed):
     return xyz[np.random.default_rng(seed).permutation(len(xyz))]
 
 
+def tight_clusters(n, seed):
+    """Clusters of 20 points far smaller than their spacing: a query's k = 32
+    distances fall into two narrow bands."""
+    rng = np.random.default_rng(seed)
+    c = rng.uniform(0, 1, (n // 20, 1, 3))
+    return (c + rng.normal(0, 1e-5, (n // 20, 20, 3))).reshape(-1, 3).astype(np.float32)
+
+
+def test_banded_distances(oracle):
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz = tight_clusters(530_000, 8)
+    prm = dict(k=32, leaf_cap=256, stages=6)
+    ref = oracle.denoise(xyz, **prm)
+    den = Denoiser(0, **prm)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
+
+
 @pytest.mark.parametrize("make,k,cap,chunk", [
     (lambda: synth.lidar_frame(seed=3, n_az=3073)[0], 12, 256, 0),      # 196,672 points: just above 3 * 2^16
     (lambda: crowded(270_001, 4), 16, 256, 0),
