@@ -4,6 +4,7 @@
 // needs, and the whole-key re-sort of deep level-10 cells.
 #include "kernels.hpp"
 #include "radix.hpp"
+#include "tree.hpp"
 #include "wave.hpp"
 
 namespace gdn {
@@ -297,35 +298,6 @@ void launch_bbox(const Plan& P, const float* xyz, hipStream_t st, bool clear) {
 
 // ---------------------------------------------------------------- Morton keys
 
-// Root cube: side S = largest bbox extent at the bbox minimum; depth limit from
-// the minimum leaf side. Same FP64 expressions for every consumer.
-__device__ void frame_consts(const FrameStat* c, double min_leaf_side, FrameConst* f) {
-    double S = 0.0;
-    for (int a = 0; a < 3; ++a) {
-        float lo = f32_from_ordered(~c->bbox_nmin[a]);
-        float hi = f32_from_ordered(c->bbox_max[a]);
-        f->lo[a] = lo;
-        double H = (double)hi - (double)lo;
-        if (H > S) S = H;
-    }
-    if (!(S > 0.0) || !(S < INFINITY)) S = 1.0;
-    f->S = S;
-    f->scale = 2097152.0 / S;
-    int d = MORTON_BITS;
-    if (min_leaf_side > 0.0) {
-        d = 0;
-        while (d < MORTON_BITS && ldexp(S, -(d + 1)) >= min_leaf_side) ++d;
-    }
-    f->dmax = d;
-}
-
-__device__ __forceinline__ uint32_t quantise(float x, float lo, double scale) {
-    double q = floor(((double)x - (double)lo) * scale);
-    if (!(q >= 0.0)) q = 0.0;
-    if (q > (double)QMAX) q = (double)QMAX;
-    return (uint32_t)q;
-}
-
 // Frame constants of every frame of a batch (one thread per frame).
 __global__ __launch_bounds__(256) void frame_const_kernel(Plan P, double min_leaf_side) {
     for (uint32_t f = threadIdx.x; f < P.nf; f += blockDim.x) frame_consts(P.fstat + f, min_leaf_side, P.fc + f);
@@ -491,7 +463,6 @@ __global__ __launch_bounds__(SORT_BLOCK) void radix_pass_kernel(const uint64_t* 
 
 // ---------------------------------------------------------------- deep cells
 
-constexpr int CELL_SHIFT = 3 * (MORTON_BITS - SORT_SHORT_LEVEL);  // level-10 prefix = key >> 33
 constexpr int SEG_BLOCK = 256;
 constexpr int SEG_PASSES = 6;  // key bits 0..47; bits 33..62 are the cell's own, and 6 passes end in keys_a
 
@@ -678,17 +649,6 @@ __device__ __forceinline__ uint32_t frame_range(const Plan& P, const uint32_t* s
         *fe = P.foff[f + 1];
     }
     return f;
-}
-
-// First position in [lo, hi) whose level-10 cell prefix is >= c (the keys
-// are in cell order everywhere).
-__device__ __forceinline__ uint32_t cell_lower_bound(const uint64_t* keys, uint32_t lo, uint32_t hi, uint64_t c) {
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if ((keys[mid] >> CELL_SHIFT) < c) lo = mid + 1u;
-        else hi = mid;
-    }
-    return lo;
 }
 
 // A level-10 cell splits when it holds more than `cap` points and lies above

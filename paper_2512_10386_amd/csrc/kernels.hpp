@@ -18,6 +18,10 @@ void launch_bbox(const Plan& P, const float* xyz, hipStream_t st, bool clear = f
 void launch_morton(const Plan& P, const Params& prm, const float* xyz, hipStream_t st);
 void launch_sort(const Plan& P, const Params& prm, hipStream_t st);
 
+// small.hip: everything from the zero-fill to the leaves for one small frame
+bool small_tree(const Plan& P);
+void launch_small_tree(const Plan& P, const Params& prm, const float* xyz, hipStream_t st);
+
 // octree.hip: sorted coordinates and leaves, voxel filter, P1 compaction, halo
 // ranges, kNN plan
 void launch_leaves(const Plan& P, const Params& prm, const float* xyz, hipStream_t st);

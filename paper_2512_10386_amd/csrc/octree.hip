@@ -3,54 +3,17 @@
 // kNN work plan.
 #include "kernels.hpp"
 #include "scan.hpp"
+#include "tree.hpp"
 #include "voxel.hpp"
 #include "wave.hpp"
 
 namespace gdn {
 
-// Number of leading octal digits two 63-bit Morton keys share (21 if equal).
-__device__ __forceinline__ int common_digits(uint64_t a, uint64_t b) {
-    if (a == b) return MORTON_BITS;
-    return (__clzll((long long)(a ^ b)) - 1) / 3;
-}
-
 // ---------------------------------------------------------------- leaves
 //
-// Leaves are the non-empty nodes reached by splitting every node that holds
-// more than leaf_cap points above the depth limit. In the sorted key order a
-// leaf boundary falls between positions j-1 and j exactly when the deepest
-// cell holding both (level l = their common digits) is split, i.e. l < dmax
-// and that cell holds more than leaf_cap points. The cell count is tested
-// with one windowed binary search (window leaf_cap + 1).
-
 // Frame of sorted position j (frames keep their input ranges after the sort).
 __device__ __forceinline__ uint32_t frame_of_sorted(const Plan& P, uint32_t j) {
     return P.nf > 1 ? frame_of(P.foff, P.nf, j) : 0u;
-}
-
-// Boundary test of sorted position j inside its frame [fs, fe): the frame's
-// first point starts a leaf; otherwise the rule above with the frame's depth
-// limit and the search window clipped to the frame.
-// Positions that share a level-10 cell lie in one leaf unless the cell is
-// deep (more than leaf_cap points: it was re-sorted on the whole key, and the
-// test below applies inside it).
-__device__ uint32_t leaf_boundary(const uint64_t* keys, uint32_t j, uint32_t fs, uint32_t fe, int dmax, bool deep,
-                                  uint32_t cap) {
-    if (j == fs) return 1u;
-    const uint64_t a = keys[j - 1], b = keys[j];
-    const int l = common_digits(a, b);
-    if (l >= dmax || (l >= SORT_SHORT_LEVEL && !deep)) return 0u;
-    const int sh = 3 * (MORTON_BITS - l);
-    const uint64_t P = b >> sh;
-    uint32_t lo = (j - 1 - fs > cap) ? j - 1 - cap : fs;
-    uint32_t hi = j - 1;
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if ((keys[mid] >> sh) < P) lo = mid + 1;
-        else hi = mid;
-    }
-    const uint64_t probe = (uint64_t)lo + cap;
-    return (probe < fe && (keys[probe] >> sh) == P) ? 1u : 0u;
 }
 
 struct BoundaryEmit {
