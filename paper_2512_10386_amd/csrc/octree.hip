@@ -318,15 +318,26 @@ void launch_voxel(const Plan& P, const Params& prm, hipStream_t st) {
         if (wb > 8192) wb = 8192;
         hipLaunchKernelGGL(voxel_wave_kernel, dim3(wb), dim3(256), 0, st, P, prm.beta, (uint32_t)prm.min_vox_count);
     }
-    unsigned blocks = P.n / 128;
+    // about a workgroup per leaf: leaves hold a quarter of the cap and more on
+    // surfaces (a workgroup per 128 points: 500 points at cap 64 106 us a
+    // call against 84, 20k at cap 512 158 against 155)
+    const uint32_t per = prm.leaf_cap < 32 ? 8u : prm.leaf_cap < 128 ? (uint32_t)prm.leaf_cap / 4u : 32u;
+    unsigned blocks = (P.n + per - 1) / per;
     if (blocks > (small ? 2048u : 16384u)) blocks = small ? 2048u : 16384u;  // small: only the big leaves remain
-    if (blocks == 0) blocks = 1;
-    if (prm.leaf_cap <= 256)
-        hipLaunchKernelGGL(voxel_kernel<512>, dim3(blocks), dim3(VOX_BLOCK), 0, st, P, prm.beta,
-                           (uint32_t)prm.min_vox_count, small);
-    else
-        hipLaunchKernelGGL(voxel_kernel<VOX_LDS_SLOTS>, dim3(blocks), dim3(VOX_BLOCK), 0, st, P, prm.beta,
-                           (uint32_t)prm.min_vox_count, small);
+    // The smallest table that takes leaves of leaf_cap points from LDS, so
+    // that more workgroups share a CU (200k points at cap 512: 272 us a call
+    // with 4096 slots, 270 with 1024). Where a minimum leaf side makes
+    // over-full leaves ordinary, the largest.
+    const uint32_t slots = prm.leaf_cap <= 256 ? 512u
+                           : prm.min_leaf_side > 0.0 ? (uint32_t)VOX_LDS_SLOTS
+                           : prm.leaf_cap <= 512     ? 1024u
+                           : prm.leaf_cap <= 1024    ? 2048u
+                                                     : (uint32_t)VOX_LDS_SLOTS;
+    auto kern = slots == 512u    ? voxel_kernel<512>
+                : slots == 1024u ? voxel_kernel<1024>
+                : slots == 2048u ? voxel_kernel<2048>
+                                 : voxel_kernel<VOX_LDS_SLOTS>;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(VOX_BLOCK), 0, st, P, prm.beta, (uint32_t)prm.min_vox_count, small);
 }
 
 // ---------------------------------------------------------------- P1 compaction

@@ -54,3 +54,22 @@ def test_mid_sizes(oracle, make, k, cap, chunk):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("n,prm", [
+    (6000, dict(leaf_cap=2)), (6000, dict(leaf_cap=31)), (6000, dict(leaf_cap=33)),
+    (60_000, dict(leaf_cap=256)), (60_000, dict(leaf_cap=257)), (60_000, dict(leaf_cap=512)),
+    (60_000, dict(leaf_cap=513)), (60_000, dict(leaf_cap=1024)), (60_000, dict(leaf_cap=1025)),
+    (60_000, dict(leaf_cap=300, min_leaf_side=0.3))])
+def test_voxel_tables(oracle, n, prm):
+    """The voxel filter's table sizes at the edges of their leaf caps, with
+    over-full leaves (copies of one point; a minimum leaf side)."""
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz = np.ascontiguousarray(crowded(n, n + prm["leaf_cap"]) if n > 8000 else
+                               synth.sphere_plane(prm["leaf_cap"], n - 2000, 1500, 500)[0])
+    ref = oracle.denoise(xyz, **prm)
+    den = Denoiser(0, **prm)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
