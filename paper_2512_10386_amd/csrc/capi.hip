@@ -369,6 +369,7 @@ static gdn_status run(gdn_ctx* ctx, const gdn_params* p, const float* xyz, int64
     gdn::Plan P = make_plan((uint32_t)n, (uint32_t)nf, p->k, (char*)workspace);
     if (workspace_bytes < P.bytes) return fail(ctx, GDN_ENOMEM, "workspace too small");
     P.big_leaves = gdn::big_leaf_path(P.n, p->leaf_cap);
+    P.plan_halo = gdn::plan_in_halo(P.n, p->leaf_cap);
     const gdn::Params prm = to_params(p);
     CallEvents* ce = nullptr;
     if (record && ctx->timing) {

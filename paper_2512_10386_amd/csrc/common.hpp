@@ -32,6 +32,9 @@ constexpr int SCAN_BLOCK = 512;                // look-back scan workgroup (fewe
 constexpr int SCAN_ITEMS = 16;
 constexpr uint32_t SCAN_SMALL_N = 1u << 20;   // scans up to this size: 4 items per thread
 constexpr int SCAN_SLOTS = 3;                 // scans per call: leaves, P1, keep
+constexpr int PLAN_CLASSES = 4;               // queue classes of unchunked leaves
+constexpr int PLAN_COUNTERS = 2 + PLAN_CLASSES;
+constexpr int PLAN_CLASS_SHIFT = 29;          // leaf_item of the halo kernel's plan: counter, place
 constexpr int PLAN_LEVELS = 8;                // candidate chunk lengths chunk0 << 0..7 (parallel plan)
 constexpr int KNN_TQ = 16;                    // queries per kNN work item (one wave), at most
 constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^19 points (shorter items, shorter tail)
@@ -74,6 +77,9 @@ struct Counters {
     uint32_t n_chunked_items; // kNN items of chunked leaves (they come first)
     uint32_t pad;
     uint32_t knn_tq;          // queries per kNN work item (a power of two)
+    // plan of the halo kernel (plan_in_halo): partial lists, items of chunked
+    // leaves, items of each class
+    uint32_t plan_q[PLAN_COUNTERS];
     uint32_t n_big;           // 1: some leaf has more than SMALL_LEAF P1 points
     unsigned long long plan_acc[PLAN_LEVELS][3];  // per candidate chunk length: lists, items, chunked items
     unsigned long long plan_pairs;
@@ -141,6 +147,16 @@ __host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1, uint32_t most)
     return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 40960u ? 4u : most;
 }
 
+// Inputs whose halo kernel plans the kNN items as it goes, each workgroup (8
+// leaves) by additions to six counters that all share, at some 10 ns each.
+// The plan kernel, one workgroup of 1024 leaves a round, takes 8 us for few
+// leaves and 16 for 1500. Thousands of workgroups would wait for the counters
+// longer than that: the line is at some 8000 leaves of a surface, four to the
+// leaf cap.
+inline bool plan_in_halo(uint32_t n, int32_t leaf_cap) {
+    return n <= (1u << 19) && n / 2048u <= (uint32_t)leaf_cap;
+}
+
 // Method parameters as the kernels use them.
 struct Params {
     int32_t k;
@@ -185,6 +201,7 @@ struct Plan {
     uint32_t* plan_status;    // [3][plan_tiles] (parallel kNN plan)
     uint32_t sort_tiles, scan_tiles, plan_tiles;
     uint32_t sort_items;      // keys per thread of the radix passes (4 or 16)
+    bool plan_halo;           // the halo kernel plans the kNN items (plan_in_halo)
     bool big_leaves;          // leaves of more than SEL_LDS_MAX points are ordinary here (big_leaf_path)
     uint32_t tq_max;          // queries per kNN work item, at most (KNN_TQ_SMALL or KNN_TQ)
     uint8_t* deepf;           // [n] 1 at sorted positions inside deep level-10 cells; between the two

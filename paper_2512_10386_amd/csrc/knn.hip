@@ -188,6 +188,19 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
                                                                          int k) {
     __shared__ float4 s_pts[BOUND_Q + 2 * BOUND_MARGIN + 1];
     const uint32_t np1 = P.ctr->n_p1, tq = P.ctr->knn_tq;
+    uint32_t cls[PLAN_COUNTERS];  // first item of each class of the halo kernel's plan
+    {
+        uint32_t items = 0;
+#pragma unroll
+        for (int i = 1; i < PLAN_COUNTERS; ++i) {
+            cls[i] = items;
+            items += P.plan_halo ? P.ctr->plan_q[i] : 0u;
+        }
+        if (items != 0u && blockIdx.x == 0 && threadIdx.x == 0) {
+            P.ctr->n_items = items;
+            P.ctr->n_chunked_items = cls[2];
+        }
+    }
     const uint32_t sub = threadIdx.x % BOUND_SPLIT, ql = threadIdx.x / BOUND_SPLIT;
     for (uint32_t q_first = blockIdx.x * BOUND_Q; q_first < np1; q_first += gridDim.x * BOUND_Q) {
         const uint32_t lo = q_first > (uint32_t)BOUND_MARGIN ? q_first - (uint32_t)BOUND_MARGIN : 0u;
@@ -229,7 +242,14 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
             P.tau_c[qi] = b;
             if ((qi - qb) % tq == 0u) {
                 const uint32_t nch = P.leaf_nch[t];
-                const uint32_t first = P.leaf_item[t] + ((qi - qb) / tq) * nch;
+                uint32_t first = P.leaf_item[t];
+                if (P.plan_halo) {
+                    const uint32_t q = first >> PLAN_CLASS_SHIFT;
+                    first &= (1u << PLAN_CLASS_SHIFT) - 1u;
+#pragma unroll
+                    for (int i = 2; i < PLAN_COUNTERS; ++i) first += (uint32_t)i == q ? cls[i] : 0u;
+                }
+                first += ((qi - qb) / tq) * nch;
                 const uint32_t q1 = min(qe, qi + tq);
                 for (uint32_t c = 0; c < nch; ++c) P.items[first + c] = KnnItem{t, qi, q1, c};
             }

@@ -416,17 +416,38 @@ __device__ __forceinline__ void lower_bound2_u64(const uint64_t* a, uint32_t n, 
 
 constexpr int HALO_LEAVES = 8;  // leaves per 256-thread block (32 threads each, 27 used)
 
+// Candidate chunks of a leaf of n1 queries and nc candidates at chunk length
+// cc, and its class in the kNN queue (the plan below).
+__device__ __forceinline__ uint32_t plan_nch(uint32_t n1, uint32_t nc, uint32_t cc) {
+    if (n1 == 0) return 1u;
+    uint32_t nch = (nc + cc - 1) / cc;
+    if (nch < 1) nch = 1;
+    if (nch > KNN_NCH_MAX) nch = KNN_NCH_MAX;
+    return nch;
+}
+__device__ __forceinline__ uint32_t plan_class(uint32_t n1, uint32_t nc) {
+    const uint32_t q = n1 > 0 ? n1 : 1u;
+    return nc >= 128u * q ? 0u : nc >= 32u * q ? 1u : nc >= 8u * q ? 2u : 3u;
+}
+
 // Per leaf, 27 threads find the key ranges of the 27 same-level cells around
 // it (clipped to the grid and to the frame), then the non-empty ranges are
 // sorted by rank counting and runs of touching ranges merged with ballots;
 // the result is the leaf's candidate ranges in P1 order.
-template <bool LDS>
-__global__ __launch_bounds__(256) void halo_kernel(Plan P, uint32_t cap) {
+// PLAN: the block also plans its leaves' kNN items at the first chunk length:
+// it adds their partial lists and items to the counters plan_q (list count,
+// items of chunked leaves, items of each class), and the counts it finds there
+// are its leaves' places. Where that fits the workspace, no plan kernel has to
+// read the leaves again.
+template <bool LDS, bool PLAN>
+__global__ __launch_bounds__(256) void halo_kernel(Plan P, uint32_t cap, uint32_t chunk0) {
+    __shared__ uint32_t s_cnt[PLAN_COUNTERS][HALO_LEAVES];
+    __shared__ unsigned long long s_pairs[HALO_LEAVES];
     __shared__ uint2 s_r[HALO_LEAVES][32];
     __shared__ uint2 s_s[HALO_LEAVES][32];
     const int tid = threadIdx.x, grp = tid >> 5, g = tid & 31;
     const uint32_t lane = (uint32_t)tid & 63u;
-    const uint32_t nl = P.ctr->n_leaves;
+    const uint32_t nl = P.ctr->n_leaves, tq = P.ctr->knn_tq;
     // this thread's half of the wave
     const unsigned long long half = (lane & 32u) ? 0xFFFFFFFF00000000ull : 0x00000000FFFFFFFFull;
     const unsigned long long below = lane == 0u ? 0ull : (~0ull >> (64u - lane));
@@ -502,17 +523,56 @@ __global__ __launch_bounds__(256) void halo_kernel(Plan P, uint32_t cap) {
             P.leaf_nr[t] = (uint32_t)__popcll(sm);
             P.leaf_ncand[t] = len;
         }
+        if constexpr (PLAN) {
+            uint32_t nch = 1, q = 1;
+            if (g == 0) {
+                // (the leaf's own cell holds its points and no others)
+                const uint32_t n1 = live ? s_r[grp][13].y - s_r[grp][13].x : 0u;
+                nch = plan_nch(n1, len, chunk0);
+                q = nch > 1u ? 1u : 2u + plan_class(n1, len);
+                const uint32_t items = (n1 + tq - 1u) / tq * nch;
+                s_cnt[0][grp] = nch > 1u ? n1 * nch : 0u;
+                for (uint32_t i = 1; i < (uint32_t)PLAN_COUNTERS; ++i) s_cnt[i][grp] = i == q ? items : 0u;
+                s_pairs[grp] = n1 ? (unsigned long long)n1 * (len - 1u) : 0ull;
+                if (n1 > SMALL_LEAF) P.ctr->n_big = 1u;  // (any thread's store of the same value)
+            }
+            __syncthreads();
+            if (tid < PLAN_COUNTERS) {
+                uint32_t sum = 0;
+                for (int i = 0; i < HALO_LEAVES; ++i) sum += s_cnt[tid][i];
+                uint32_t at = sum ? atomicAdd(&P.ctr->plan_q[tid], sum) : 0u;
+                for (int i = 0; i < HALO_LEAVES; ++i) {
+                    const uint32_t v = s_cnt[tid][i];
+                    s_cnt[tid][i] = at;
+                    at += v;
+                }
+            } else if (tid == 64) {
+                unsigned long long sum = 0;
+                for (int i = 0; i < HALO_LEAVES; ++i) sum += s_pairs[i];
+                if (sum) atomicAdd(&P.ctr->pairs, sum);
+            }
+            __syncthreads();
+            if (live && g == 0) {
+                P.leaf_nch[t] = nch;
+                P.leaf_cc[t] = (len + nch - 1u) / nch;
+                P.leaf_plist[t] = s_cnt[0][grp];
+                P.leaf_item[t] = (q << PLAN_CLASS_SHIFT) | s_cnt[q][grp];
+            }
+        }
         __syncthreads();
     }
 }
+
+static uint32_t plan_chunk0(const Params& prm) { return prm.knn_chunk > 0 ? (uint32_t)prm.knn_chunk : (uint32_t)KNN_CC0; }
 
 void launch_halo(const Plan& P, const Params& prm, hipStream_t st) {
     unsigned blocks = (P.n + HALO_LEAVES - 1) / HALO_LEAVES;
     if (blocks > 2048) blocks = 2048;
     if (blocks == 0) blocks = 1;
     const bool lds = P.nf > 1u && P.nf < SORT_FOFF_LDS;
-    hipLaunchKernelGGL(lds ? halo_kernel<true> : halo_kernel<false>, dim3(blocks), dim3(256), 0, st, P,
-                       (uint32_t)prm.leaf_cap);
+    auto kern = P.plan_halo ? (lds ? halo_kernel<true, true> : halo_kernel<false, true>)
+                            : (lds ? halo_kernel<true, false> : halo_kernel<false, false>);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, st, P, (uint32_t)prm.leaf_cap, plan_chunk0(prm));
 }
 
 // ---------------------------------------------------------------- kNN plan
@@ -532,12 +592,6 @@ void launch_halo(const Plan& P, const Params& prm, hipStream_t st) {
 
 constexpr int PLAN_BLOCK = 1024;
 constexpr int PLAN_R = 2;        // leaves per thread whose sizes stay in registers (more are re-read)
-constexpr int PLAN_CLASSES = 4;
-
-__device__ __forceinline__ uint32_t plan_class(uint32_t n1, uint32_t nc) {
-    const uint32_t q = n1 > 0 ? n1 : 1u;
-    return nc >= 128u * q ? 0u : nc >= 32u * q ? 1u : nc >= 8u * q ? 2u : 3u;
-}
 
 // Block exclusive scans of N values per thread at once (one set of
 // barriers); smem needs N * (blockDim / 64 + 1) words.
@@ -578,6 +632,14 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
     __shared__ uint32_t s_scan[NS * (PLAN_BLOCK / 64 + 1)];
     __shared__ uint32_t s_cc, s_done, s_carry[NS], s_base[NS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (P.plan_halo) {
+        // the halo kernel's plan stands if it fits; otherwise this one replaces it
+        unsigned long long items = 0;
+        for (int i = 1; i < PLAN_COUNTERS; ++i) items += P.ctr->plan_q[i];
+        if (P.ctr->plan_q[0] <= P.plist_max && items <= P.items_max) return;
+        __syncthreads();
+        if (tid < PLAN_COUNTERS) P.ctr->plan_q[tid] = 0u;
+    }
     const uint32_t nl = P.ctr->n_leaves, tq = P.ctr->knn_tq;
     // this thread's leaves t = tid + r * PLAN_BLOCK: P1 points and candidates
     uint32_t c_n1[PLAN_R], c_nc[PLAN_R];
@@ -600,13 +662,6 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
         for (uint32_t t = (uint32_t)tid + (uint32_t)PLAN_R * PLAN_BLOCK; t < nl; t += PLAN_BLOCK)
             f(t, P.p1pos[P.leaf_begin[t + 1]] - P.p1pos[P.leaf_begin[t]], P.leaf_ncand[t]);
     };
-    auto nch_of = [](uint32_t n1, uint32_t nc, uint32_t cc) -> uint32_t {
-        if (n1 == 0) return 1u;
-        uint32_t nch = (nc + cc - 1) / cc;
-        if (nch < 1) nch = 1;
-        if (nch > KNN_NCH_MAX) nch = KNN_NCH_MAX;
-        return nch;
-    };
     if (tid == 0) { s_cc = (uint32_t)chunk0; s_done = 0; }
     __syncthreads();
     for (int iter = 0; iter < 40; ++iter) {
@@ -615,7 +670,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
         for_leaves([&](uint32_t, uint32_t n1, uint32_t nc) {
             if (n1 == 0) return;
             if (n1 > SMALL_LEAF) P.ctr->n_big = 1u;  // (any thread's store of the same value)
-            const uint32_t nch = nch_of(n1, nc, cc);
+            const uint32_t nch = plan_nch(n1, nc, cc);
             if (nch > 1) lists += (unsigned long long)n1 * nch;
             items += (unsigned long long)((n1 + tq - 1) / tq) * nch;
             pairs += (unsigned long long)n1 * (nc - 1);
@@ -643,7 +698,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
     const uint32_t cc = s_cc;
     // per leaf: its partial lists, its items (chunked, or in its class)
     auto counts = [&](uint32_t n1, uint32_t nc, uint32_t (&v)[NS], uint32_t& nch) {
-        nch = nch_of(n1, nc, cc);
+        nch = plan_nch(n1, nc, cc);
 #pragma unroll
         for (int i = 0; i < NS; ++i) v[i] = 0;
         const uint32_t ni = n1 ? ((n1 + tq - 1) / tq) * nch : 0u;
@@ -753,14 +808,6 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
 // launches (the pick and a scan per sum, one after another) it took 100 us for
 // 6.2M points, 90 us for 1.2M; as two 27 and 18 us.
 
-__device__ __forceinline__ uint32_t plan_nch(uint32_t n1, uint32_t nc, uint32_t cc) {
-    if (n1 == 0) return 1u;
-    uint32_t nch = (nc + cc - 1) / cc;
-    if (nch < 1) nch = 1;
-    if (nch > KNN_NCH_MAX) nch = KNN_NCH_MAX;
-    return nch;
-}
-
 __global__ __launch_bounds__(256) void plan_count_kernel(Plan P, uint32_t chunk0) {
     __shared__ unsigned long long s_acc[PLAN_LEVELS * 3 + 1];
     for (int i = threadIdx.x; i < PLAN_LEVELS * 3 + 1; i += blockDim.x) s_acc[i] = 0ull;
@@ -867,18 +914,21 @@ __global__ __launch_bounds__(PLAN_SCAN) void plan_scan_kernel(Plan P, uint32_t c
 }
 
 void launch_knn_plan(const Plan& P, const Params& prm, hipStream_t st) {
-    const int chunk0 = prm.knn_chunk > 0 ? prm.knn_chunk : KNN_CC0;
+    const uint32_t chunk0 = plan_chunk0(prm);
+    // the halo kernel's plan holds for sure where no leaf can have more than
+    // two chunks: at most 2 n items and 2 n partial lists
+    if (P.plan_halo && P.n <= 2ull * chunk0) return;
     if (P.n <= (1u << 19)) {
-        hipLaunchKernelGGL(knn_plan_kernel, dim3(1), dim3(PLAN_BLOCK), 0, st, P, chunk0);
+        hipLaunchKernelGGL(knn_plan_kernel, dim3(1), dim3(PLAN_BLOCK), 0, st, P, (int)chunk0);
         return;
     }
     unsigned blocks = (P.n / 8 + 255) / 256;
     if (blocks > 512) blocks = 512;
-    hipLaunchKernelGGL(plan_count_kernel, dim3(blocks), dim3(256), 0, st, P, (uint32_t)chunk0);
+    hipLaunchKernelGGL(plan_count_kernel, dim3(blocks), dim3(256), 0, st, P, chunk0);
     // (far fewer leaves than the points that bound them: a small grid that
     // loops over the tiles)
     hipLaunchKernelGGL(plan_scan_kernel, dim3(P.plan_tiles < 256u ? P.plan_tiles : 256u), dim3(PLAN_SCAN), 0, st, P,
-                       (uint32_t)chunk0);
+                       chunk0);
 }
 
 }  // namespace gdn

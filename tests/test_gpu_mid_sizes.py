@@ -73,3 +73,22 @@ def test_voxel_tables(oracle, n, prm):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("n,prm", [
+    (22_528, dict(leaf_cap=10)), (22_528, dict(leaf_cap=11)),        # the plan kernel, the halo kernel's plan
+    (22_528, dict(leaf_cap=256, knn_chunk=16)),                      # too many partial lists: planned again
+    (22_528, dict(leaf_cap=256, knn_chunk=11_264)),                  # at most two chunks: no plan kernel
+    (22_528, dict(leaf_cap=256, knn_chunk=11_263)),
+    (22_528, dict(leaf_cap=256, knn_chunk=1500)),                    # chunked leaves that fit
+    (4_000, dict(leaf_cap=1, min_vox_count=1)), (4_000, dict(min_vox_count=50))])
+def test_plan_in_halo(oracle, n, prm):
+    """The kNN plan by the halo kernel and where the plan kernel takes over."""
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz = np.ascontiguousarray(synth.sphere_plane(5, n - 3000, 2000, 1000)[0])
+    ref = oracle.denoise(xyz, **{a: v for a, v in prm.items() if a != "knn_chunk"})
+    den = Denoiser(0, **prm)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
