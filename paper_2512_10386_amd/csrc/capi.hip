@@ -102,7 +102,7 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.sort_status = (uint32_t*)take(sizeof(uint32_t) * (size_t)P.sort_passes * P.sort_tiles * 256);
     P.scan_status = (uint32_t*)take(sizeof(uint32_t) * SCAN_SLOTS * (size_t)P.scan_tiles);
     P.plan_tiles = (uint32_t)((N + 511) / 512);  // 512 leaves per tile
-    P.plan_status = (uint32_t*)take(sizeof(uint32_t) * 3 * (size_t)P.plan_tiles);
+    P.plan_status = (uint32_t*)take(sizeof(uint32_t) * PLAN_COUNTERS * (size_t)P.plan_tiles);
     P.deepf = (uint8_t*)take(N);
     P.zero_begin = base ? base + z0 : nullptr;
     P.zero_bytes = off - z0;

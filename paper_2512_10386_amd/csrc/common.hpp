@@ -34,7 +34,16 @@ constexpr uint32_t SCAN_SMALL_N = 1u << 20;   // scans up to this size: 4 items 
 constexpr int SCAN_SLOTS = 3;                 // scans per call: leaves, P1, keep
 constexpr int PLAN_CLASSES = 4;               // queue classes of unchunked leaves
 constexpr int PLAN_COUNTERS = 2 + PLAN_CLASSES;
-constexpr int PLAN_CLASS_SHIFT = 29;          // leaf_item of the halo kernel's plan: counter, place
+constexpr int PLAN_CLASS_SHIFT = 29;          // leaf_item of such plans: counter, place among its items
+// Inputs whose kNN queue is ordered by class. A sweep of 1M points ends on
+// its few heaviest items unless they start first: 1404 us a call in leaf order
+// and 1245 by class (caps 512 and 1024, three seeds each: 3 to 14 % less); nine
+// sweeps of 100k gain up to 3 % at cap 256 and 0 to 1 % above. At 64 sweeps, 6.2M
+// points, the end is short against the rest, and leaf order, where items that
+// run together share their candidates, is ahead: 3992 and 4028 us.
+constexpr uint32_t PLAN_CLASS_MAX_N = 1u << 21;
+static_assert(2ull * PLAN_CLASS_MAX_N + 64 < 1ull << PLAN_CLASS_SHIFT, "a place fits below the class");
+constexpr uint32_t PLAN_ONE_MAX_N = 1u << 19;  // kNN plan: one workgroup up to this size, parallel above
 constexpr int PLAN_LEVELS = 8;                // candidate chunk lengths chunk0 << 0..7 (parallel plan)
 constexpr int KNN_TQ = 16;                    // queries per kNN work item (one wave), at most
 constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^19 points (shorter items, shorter tail)
@@ -77,8 +86,8 @@ struct Counters {
     uint32_t n_chunked_items; // kNN items of chunked leaves (they come first)
     uint32_t pad;
     uint32_t knn_tq;          // queries per kNN work item (a power of two)
-    // plan of the halo kernel (plan_in_halo): partial lists, items of chunked
-    // leaves, items of each class
+    // plans that give each class its own count (halo kernel, parallel plan):
+    // partial lists, items of chunked leaves, items of each class
     uint32_t plan_q[PLAN_COUNTERS];
     uint32_t n_big;           // 1: some leaf has more than SMALL_LEAF P1 points
     unsigned long long plan_acc[PLAN_LEVELS][3];  // per candidate chunk length: lists, items, chunked items
@@ -154,7 +163,7 @@ __host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1, uint32_t most)
 // longer than that: the line is at some 8000 leaves of a surface, four to the
 // leaf cap.
 inline bool plan_in_halo(uint32_t n, int32_t leaf_cap) {
-    return n <= (1u << 19) && n / 2048u <= (uint32_t)leaf_cap;
+    return n <= PLAN_ONE_MAX_N && n / 2048u <= (uint32_t)leaf_cap;
 }
 
 // Method parameters as the kernels use them.
@@ -198,7 +207,7 @@ struct Plan {
     uint32_t* sort_hist;      // [SORT_PASSES_MAX][256]
     uint32_t* sort_status;    // [SORT_PASSES_MAX][sort_tiles][256]
     uint32_t* scan_status;    // [SCAN_SLOTS][scan_tiles]
-    uint32_t* plan_status;    // [3][plan_tiles] (parallel kNN plan)
+    uint32_t* plan_status;    // [PLAN_COUNTERS][plan_tiles] (parallel kNN plan)
     uint32_t sort_tiles, scan_tiles, plan_tiles;
     uint32_t sort_items;      // keys per thread of the radix passes (4 or 16)
     bool plan_halo;           // the halo kernel plans the kNN items (plan_in_halo)
@@ -271,6 +280,15 @@ struct Plan {
 };
 
 // ------------------------------------------------------------------ helpers
+
+// Whether the halo kernel's plan holds: it was made and fits the workspace.
+__device__ __forceinline__ bool halo_plan_stands(const Plan& P) {
+    if (!P.plan_halo) return false;
+    unsigned long long items = 0;
+#pragma unroll
+    for (int i = 1; i < PLAN_COUNTERS; ++i) items += P.ctr->plan_q[i];
+    return P.ctr->plan_q[0] <= P.plist_max && items <= P.items_max;
+}
 
 __device__ __forceinline__ uint32_t f32_ordered(float f) {
     uint32_t u = __float_as_uint(f);

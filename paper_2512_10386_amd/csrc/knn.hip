@@ -188,15 +188,17 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
                                                                          int k) {
     __shared__ float4 s_pts[BOUND_Q + 2 * BOUND_MARGIN + 1];
     const uint32_t np1 = P.ctr->n_p1, tq = P.ctr->knn_tq;
-    uint32_t cls[PLAN_COUNTERS];  // first item of each class of the halo kernel's plan
-    {
+    // first item of each class (halo kernel's plan, parallel plan)
+    const bool classes = P.n > PLAN_ONE_MAX_N ? P.n <= PLAN_CLASS_MAX_N : halo_plan_stands(P);
+    uint32_t cls[PLAN_COUNTERS];
+    if (classes) {
         uint32_t items = 0;
 #pragma unroll
         for (int i = 1; i < PLAN_COUNTERS; ++i) {
             cls[i] = items;
-            items += P.plan_halo ? P.ctr->plan_q[i] : 0u;
+            items += P.ctr->plan_q[i];
         }
-        if (items != 0u && blockIdx.x == 0 && threadIdx.x == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
             P.ctr->n_items = items;
             P.ctr->n_chunked_items = cls[2];
         }
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
             if ((qi - qb) % tq == 0u) {
                 const uint32_t nch = P.leaf_nch[t];
                 uint32_t first = P.leaf_item[t];
-                if (P.plan_halo) {
+                if (classes) {
                     const uint32_t q = first >> PLAN_CLASS_SHIFT;
                     first &= (1u << PLAN_CLASS_SHIFT) - 1u;
 #pragma unroll

@@ -577,7 +577,7 @@ void launch_halo(const Plan& P, const Params& prm, hipStream_t st) {
 
 // ---------------------------------------------------------------- kNN plan
 //
-// One workgroup. Work items are (leaf, tile of up to KNN_TQ queries,
+// Work items are (leaf, tile of up to KNN_TQ queries,
 // candidate chunk). Leaves whose candidate set exceeds the chunk length are
 // split into chunks whose partial top-k lists knn_merge_kernel combines; the
 // chunk length doubles until the partial lists and items fit their
@@ -589,6 +589,12 @@ void launch_halo(const Plan& P, const Params& prm, hipStream_t st) {
 // far k-th neighbours, so its queries test many candidate groups), and
 // starting such items first keeps them out of the kernel's tail. The items
 // themselves are written by the bound kernel, one tile per thread.
+//
+// Up to PLAN_ONE_MAX_N points the halo kernel makes this plan with the first
+// chunk length as it goes (plan_in_halo); the kernel here, one workgroup, makes
+// it where it does not, or where that length asks for more partial lists or
+// items than the workspace holds. It takes 8 us for few leaves and 16 for 1500,
+// 2.5 if it only finds that the plan stands.
 
 constexpr int PLAN_BLOCK = 1024;
 constexpr int PLAN_R = 2;        // leaves per thread whose sizes stay in registers (more are re-read)
@@ -632,14 +638,7 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
     __shared__ uint32_t s_scan[NS * (PLAN_BLOCK / 64 + 1)];
     __shared__ uint32_t s_cc, s_done, s_carry[NS], s_base[NS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (P.plan_halo) {
-        // the halo kernel's plan stands if it fits; otherwise this one replaces it
-        unsigned long long items = 0;
-        for (int i = 1; i < PLAN_COUNTERS; ++i) items += P.ctr->plan_q[i];
-        if (P.ctr->plan_q[0] <= P.plist_max && items <= P.items_max) return;
-        __syncthreads();
-        if (tid < PLAN_COUNTERS) P.ctr->plan_q[tid] = 0u;
-    }
+    if (halo_plan_stands(P)) return;
     const uint32_t nl = P.ctr->n_leaves, tq = P.ctr->knn_tq;
     // this thread's leaves t = tid + r * PLAN_BLOCK: P1 points and candidates
     uint32_t c_n1[PLAN_R], c_nc[PLAN_R];
@@ -802,8 +801,8 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
 // Parallel plan for large inputs (the single workgroup above would walk
 // every leaf several times): one pass counts partial lists, items and chunked
 // items per leaf for each candidate chunk length chunk0 << l; a look-back scan
-// over the leaves then carries three sums at once (partial lists, items of
-// chunked leaves, items of the others), every workgroup picking the first
+// over the leaves then carries six sums at once (partial lists, items of
+// chunked leaves, items of each class), every workgroup picking the first
 // length that fits (else no chunking) from the counts by itself. As five
 // launches (the pick and a scan per sum, one after another) it took 100 us for
 // 6.2M points, 90 us for 1.2M; as two 27 and 18 us.
@@ -853,7 +852,8 @@ __global__ __launch_bounds__(256) void plan_count_kernel(Plan P, uint32_t chunk0
 constexpr int PLAN_SCAN = 512;  // leaves per tile, one per thread
 
 __global__ __launch_bounds__(PLAN_SCAN) void plan_scan_kernel(Plan P, uint32_t chunk0) {
-    constexpr int NS = 3;  // partial lists, chunked items, other items
+    constexpr int NS = PLAN_COUNTERS;  // partial lists, chunked items, items of each class
+    static_assert(NS <= PLAN_SCAN / 64, "a wave per sum");
     __shared__ uint32_t s_scan[NS * (PLAN_SCAN / 64 + 1)];
     __shared__ uint32_t s_base[NS];
     Counters* c = P.ctr;
@@ -871,28 +871,32 @@ __global__ __launch_bounds__(PLAN_SCAN) void plan_scan_kernel(Plan P, uint32_t c
             chunked = (uint32_t)c->plan_acc[f][2];
         }
     }
+    const bool classes = P.n <= PLAN_CLASS_MAX_N;  // otherwise one class, with whole queue positions
     const uint32_t ntiles = (nl + PLAN_SCAN - 1) / PLAN_SCAN;
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const uint32_t t = tile * PLAN_SCAN + threadIdx.x;
-        uint32_t v[NS] = {0u, 0u, 0u}, nch = 1, nc = 0;
+        uint32_t v[NS] = {}, nch = 1, nc = 0, q = 2;
         if (t < nl) {
             const uint32_t n1 = P.p1pos[P.leaf_begin[t + 1]] - P.p1pos[P.leaf_begin[t]];
             nc = P.leaf_ncand[t];
             nch = plan_nch(n1, nc, cc);
+            q = nch > 1u ? 1u : 2u + (classes ? plan_class(n1, nc) : 0u);
             const uint32_t items = n1 ? ((n1 + tq - 1) / tq) * nch : 0u;
             v[0] = nch > 1 ? n1 * nch : 0u;
-            v[1] = nch > 1 ? items : 0u;
-            v[2] = nch > 1 ? 0u : items;
+#pragma unroll
+            for (int i = 1; i < NS; ++i) v[i] = (uint32_t)i == q ? items : 0u;
         }
         uint32_t ex[NS], tot[NS];
         block_excl_scan_n<NS>(v, ex, tot, s_scan);
         // wave w looks back over the tiles' sums w (64 predecessors per round
         // trip, as the element scans); without chunked leaves the first two
-        // are zero everywhere
+        // are zero everywhere, and so are the last three with one class
         if (wave < (uint32_t)NS) {
             uint32_t base = 0;
-            if (wave == 2u || chunked != 0u) {
-                const uint32_t agg = wave == 0u ? tot[0] : wave == 1u ? tot[1] : tot[2];
+            if (wave == 2u || (wave > 2u && classes) || (wave < 2u && chunked != 0u)) {
+                uint32_t agg = 0;
+#pragma unroll
+                for (int i = 0; i < NS; ++i) agg = (uint32_t)i == wave ? tot[i] : agg;
                 base = look_back(P.plan_status + (size_t)wave * P.plan_tiles, tile, agg, lane, &c->status);
             }
             if (lane == 0u) s_base[wave] = base;
@@ -902,11 +906,20 @@ __global__ __launch_bounds__(PLAN_SCAN) void plan_scan_kernel(Plan P, uint32_t c
             P.leaf_nch[t] = nch;
             P.leaf_cc[t] = (nc + nch - 1) / nch;
             P.leaf_plist[t] = s_base[0] + ex[0];
-            P.leaf_item[t] = nch > 1 ? s_base[1] + ex[1] : chunked + s_base[2] + ex[2];
+            uint32_t e = 0;
+#pragma unroll
+            for (int i = 1; i < NS; ++i) e = (uint32_t)i == q ? s_base[i] + ex[i] : e;
+            P.leaf_item[t] = classes ? (q << PLAN_CLASS_SHIFT) | e : (q == 1u ? 0u : chunked) + e;
         }
         if (tile == ntiles - 1 && threadIdx.x == 0) {
+            uint32_t items = 0;
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                c->plan_q[i] = s_base[i] + tot[i];
+                items += i ? s_base[i] + tot[i] : 0u;
+            }
             c->n_chunked_items = chunked;
-            c->n_items = chunked + s_base[2] + tot[2];
+            c->n_items = items;
             c->pairs = c->plan_pairs;
         }
         __syncthreads();  // s_base is reused by the next tile
@@ -918,7 +931,7 @@ void launch_knn_plan(const Plan& P, const Params& prm, hipStream_t st) {
     // the halo kernel's plan holds for sure where no leaf can have more than
     // two chunks: at most 2 n items and 2 n partial lists
     if (P.plan_halo && P.n <= 2ull * chunk0) return;
-    if (P.n <= (1u << 19)) {
+    if (P.n <= PLAN_ONE_MAX_N) {
         hipLaunchKernelGGL(knn_plan_kernel, dim3(1), dim3(PLAN_BLOCK), 0, st, P, (int)chunk0);
         return;
     }

@@ -92,3 +92,32 @@ def test_plan_in_halo(oracle, n, prm):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("nf,chunk", [(10, 0), (11, 0), (11, 20_000)])
+def test_queue_order_sizes(nf, chunk):
+    """Batches on both sides of the size (2^21 points) above which the kNN
+    queue is in leaf order, with and without chunked leaves, against the plain
+    call of each frame."""
+    import torch
+    from paper_2512_10386_amd.binding import BatchDenoiser, Denoiser
+    two = [synth.lidar_frame(seed=s, n_az=3100)[0] for s in (1, 2)]  # 198,400 points each
+    frames = [two[f % 2] for f in range(nf)]
+    off = torch.tensor(np.concatenate([[0], np.cumsum([len(f) for f in frames])]), dtype=torch.int64, device="cuda")
+    x = torch.from_numpy(np.concatenate(frames)).cuda()
+    assert (len(x) > 2 ** 21) == (nf == 11)
+    prm = dict(k=16, leaf_cap=512, knn_chunk=chunk)
+    bd, den = BatchDenoiser(0, **prm), Denoiser(0, **prm)
+    try:
+        out = bd.alloc(len(x), nf)
+        bd(x, off, out)
+        ref = [den(torch.from_numpy(f).cuda()) for f in two]
+        for f in range(nf):
+            a, b, r = int(off[f]), int(off[f + 1]), ref[f % 2]
+            m = int(r.n_kept)
+            assert torch.equal(out.keep[a:b], r.keep) and torch.equal(out.stage[a:b], r.stage)
+            assert torch.equal(out.score[a:b].view(torch.int32), r.score.view(torch.int32))
+            assert int(out.n_kept[f]) == m and torch.equal(out.kept_idx[a:a + m], r.kept_idx[:m])
+    finally:
+        bd.close()
+        den.close()
