@@ -85,10 +85,9 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.k = k;
     P.nf = nf;
     P.sort_passes = SORT_PASSES + (nf > 256u ? 2u : (nf > 1u ? 1u : 0u));
-    P.sort_items = n > SORT_BIG_N ? 16u : 4u;
+    P.sort_tile = sort_tile_for(n);
     P.tq_max = n > KNN_TQ_SMALL_MAX_N ? (uint32_t)KNN_TQ : (uint32_t)KNN_TQ_SMALL;
-    const size_t sort_tile = (size_t)SORT_BLOCK * P.sort_items;
-    P.sort_tiles = (uint32_t)((N + sort_tile - 1) / sort_tile);
+    P.sort_tiles = (uint32_t)((N + P.sort_tile - 1) / P.sort_tile);
     if (P.sort_tiles == 0) P.sort_tiles = 1;
     P.scan_tiles = scan_tiles_for(n);
     // capacities stay below 2^30 (the look-back scans carry 30-bit sums)
@@ -99,7 +98,7 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.ctr = (Counters*)take(sizeof(Counters));  // first: status_word() reads the workspace start
     P.fstat = (FrameStat*)take(sizeof(FrameStat) * (size_t)nf);
     P.sort_hist = (uint32_t*)take(sizeof(uint32_t) * SORT_PASSES_MAX * 256);
-    P.sort_status = (uint32_t*)take(sizeof(uint32_t) * (size_t)P.sort_passes * P.sort_tiles * 256);
+    P.sort_status = (uint32_t*)take(sizeof(uint32_t) * (size_t)(P.sort_passes - SORT_SHORT_FIRST) * P.sort_tiles * 256);
     P.scan_status = (uint32_t*)take(sizeof(uint32_t) * SCAN_SLOTS * (size_t)P.scan_tiles);
     P.plan_tiles = (uint32_t)((N + 511) / 512);  // 512 leaves per tile
     P.plan_status = (uint32_t*)take(sizeof(uint32_t) * PLAN_COUNTERS * (size_t)P.plan_tiles);

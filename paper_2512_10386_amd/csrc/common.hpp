@@ -10,8 +10,6 @@ constexpr int MORTON_BITS = 21;
 constexpr uint32_t QMAX = (1u << MORTON_BITS) - 1u;
 
 // Tile sizes.
-constexpr int SORT_BLOCK = 256;               // radix-sort workgroup
-constexpr uint32_t SORT_BIG_N = 1u << 20;     // above: 16 keys per thread, else 4
 constexpr int SORT_PASSES = 8;                // 8-bit digits over the 63-bit key
 constexpr int SORT_FRAME_PASSES_MAX = 2;      // 8-bit digits of the frame id (batches)
 constexpr int SORT_PASSES_MAX = SORT_PASSES + SORT_FRAME_PASSES_MAX;
@@ -166,6 +164,19 @@ inline bool plan_in_halo(uint32_t n, int32_t leaf_cap) {
     return n <= PLAN_ONE_MAX_N && n / 2048u <= (uint32_t)leaf_cap;
 }
 
+// Keys per workgroup of a radix pass. Below some 100k keys a pass is the
+// latency of one workgroup plus a few round trips of look-back, and few keys
+// per workgroup are read, ranked and written sooner; above, the look-back's
+// traffic (1 KB of status words per tile and round trip) weighs more. Whole
+// calls with tiles of 512 / 1024 / 2048 keys: 10k points 135.9 / 136.9 / 140.5
+// us, 20k 147.5 / 147.7 / 151.1, 80k 226 / 222.8 / 224.6, 120k - / 301.4 /
+// 300.2, 900k - / 875 / 863. 4096 keys, staged in LDS, by 512 threads of 8 keys
+// against 256 of 16 (the same LDS with twice the waves): 1.2M points 1051 and
+// 1042 us, 6.2M 3990 and 3948.
+inline uint32_t sort_tile_for(uint32_t n) {
+    return n <= (1u << 14) ? 512u : n <= (7u << 14) ? 1024u : n <= (1u << 20) ? 2048u : 4096u;
+}
+
 // Method parameters as the kernels use them.
 struct Params {
     int32_t k;
@@ -205,11 +216,11 @@ struct Plan {
     Counters* ctr;
     FrameStat* fstat;         // [nf]
     uint32_t* sort_hist;      // [SORT_PASSES_MAX][256]
-    uint32_t* sort_status;    // [SORT_PASSES_MAX][sort_tiles][256]
+    uint32_t* sort_status;    // [sort_passes - SORT_SHORT_FIRST][sort_tiles][256]
     uint32_t* scan_status;    // [SCAN_SLOTS][scan_tiles]
     uint32_t* plan_status;    // [PLAN_COUNTERS][plan_tiles] (parallel kNN plan)
     uint32_t sort_tiles, scan_tiles, plan_tiles;
-    uint32_t sort_items;      // keys per thread of the radix passes (4 or 16)
+    uint32_t sort_tile;       // keys per workgroup of the radix passes (sort_tile_for)
     bool plan_halo;           // the halo kernel plans the kNN items (plan_in_halo)
     bool big_leaves;          // leaves of more than SEL_LDS_MAX points are ordinary here (big_leaf_path)
     uint32_t tq_max;          // queries per kNN work item, at most (KNN_TQ_SMALL or KNN_TQ)

@@ -278,7 +278,8 @@ struct NnCloud {
 
 struct NnPlan {
     NnCloud c[2];
-    int passes, items;
+    int passes;
+    uint32_t tile;        // keys per workgroup of the radix passes
     int first;            // buffer the first pass reads (the order ends in key[0], idx[0])
     char* zero;           // histograms, look-back words, flag
     size_t zero_bytes;
@@ -297,7 +298,8 @@ NnPlan nn_plan(const float* a, uint32_t na, const float* b, uint32_t nb, char* b
     const uint32_t big = na > nb ? na : nb;
     P.passes = big <= NN_SHORT_N ? 3 : NN_PASSES_MAX;
     P.first = P.passes & 1;
-    P.items = big > SORT_BIG_N ? 16 : 4;
+    P.tile = sort_tile_for(big);
+    if (P.tile < 1024u) P.tile = 1024u;  // (the order and its look-backs are a small part there)
     P.c[0].p = a;
     P.c[0].n = na;
     P.c[1].p = b;
@@ -305,8 +307,7 @@ NnPlan nn_plan(const float* a, uint32_t na, const float* b, uint32_t nb, char* b
     const size_t z0 = off;
     P.flag = (uint32_t*)take(4);
     for (NnCloud& c : P.c) {
-        const uint32_t tile = (uint32_t)SORT_BLOCK * (uint32_t)P.items;
-        c.tiles = (c.n + tile - 1) / tile;
+        c.tiles = (c.n + P.tile - 1) / P.tile;
         c.supers = (c.n + NN_SUP - 1) / NN_SUP;
         c.n_hard = (uint32_t*)take(4);
         c.sbox = (uint32_t*)take(32 * (size_t)c.supers);
@@ -503,15 +504,15 @@ struct NnDigit {
 // One radix pass over both clouds (the first cloud's tiles, then the
 // second's; each looks back over its own). The first pass's payload is the
 // position itself.
-template <int ITEMS, bool FIRST>
-__global__ __launch_bounds__(SORT_BLOCK) void nn_radix_kernel(NnPlan P, int pass) {
+template <int ITEMS, int BLOCK, bool FIRST>
+__global__ __launch_bounds__(BLOCK) void nn_radix_kernel(NnPlan P, int pass) {
     const bool second = blockIdx.x >= P.c[0].tiles;
     const NnCloud& c = P.c[second ? 1 : 0];
     const uint32_t tile = second ? blockIdx.x - P.c[0].tiles : blockIdx.x;
     const int from = (pass + P.first) & 1, to = 1 - from;
-    radix_tile<ITEMS, FIRST>((const uint32_t*)c.key[from], (const uint32_t*)c.idx[from], c.key[to], c.idx[to], c.n,
-                             tile, (const uint32_t*)c.hist + pass * 256, c.status + (size_t)pass * c.tiles * 256,
-                             P.flag, 1u, NnDigit{8 * pass});
+    radix_tile<ITEMS, FIRST, BLOCK>((const uint32_t*)c.key[from], (const uint32_t*)c.idx[from], c.key[to], c.idx[to],
+                                    c.n, tile, (const uint32_t*)c.hist + pass * 256,
+                                    c.status + (size_t)pass * c.tiles * 256, P.flag, 1u, NnDigit{8 * pass});
 }
 
 // Sorted points and the boxes of groups and supers, NN_GATHER points per block.
@@ -950,9 +951,10 @@ void nn_sort(const NnPlan& P, hipStream_t st) {
     hipLaunchKernelGGL(P.passes == 3 ? nn_key_kernel<3> : nn_key_kernel<NN_PASSES_MAX>,
                        dim3(P.c[0].key_blocks + P.c[1].key_blocks), dim3(256), 0, st, P);
     for (int pass = 0; pass < P.passes; ++pass) {
-        auto kern = P.items == 4 ? (pass == 0 ? nn_radix_kernel<4, true> : nn_radix_kernel<4, false>)
-                                 : (pass == 0 ? nn_radix_kernel<16, true> : nn_radix_kernel<16, false>);
-        hipLaunchKernelGGL(kern, dim3(P.c[0].tiles + P.c[1].tiles), dim3(SORT_BLOCK), 0, st, P, pass);
+        auto kern = P.tile == 1024u ? (pass == 0 ? nn_radix_kernel<4, 256, true> : nn_radix_kernel<4, 256, false>)
+                    : P.tile == 2048u ? (pass == 0 ? nn_radix_kernel<4, 512, true> : nn_radix_kernel<4, 512, false>)
+                                      : (pass == 0 ? nn_radix_kernel<8, 512, true> : nn_radix_kernel<8, 512, false>);
+        hipLaunchKernelGGL(kern, dim3(P.c[0].tiles + P.c[1].tiles), dim3(P.tile == 1024u ? 256 : 512), 0, st, P, pass);
     }
     hipLaunchKernelGGL(nn_gather_kernel, dim3((P.c[0].supers + P.c[1].supers) * (unsigned)(NN_SUP / NN_GATHER)),
                        dim3(NN_GATHER), 0, st, P);

@@ -443,8 +443,8 @@ struct FrameDigit {
     }
 };
 
-template <int ITEMS>
-__global__ __launch_bounds__(SORT_BLOCK) void radix_pass_kernel(const uint64_t* __restrict__ kin,
+template <int ITEMS, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void radix_pass_kernel(const uint64_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
                                                                 uint64_t* __restrict__ kout,
                                                                 uint32_t* __restrict__ vout, uint32_t n,
@@ -456,8 +456,8 @@ __global__ __launch_bounds__(SORT_BLOCK) void radix_pass_kernel(const uint64_t* 
     // frame passes of batches with few frames search the offsets in LDS
     const bool foff_lds = pass >= SORT_PASSES && nf < SORT_FOFF_LDS;
     if (foff_lds)
-        for (uint32_t i = threadIdx.x; i <= nf; i += SORT_BLOCK) s_foff[i] = foff[i];
-    radix_tile<ITEMS, false>(kin, vin, kout, vout, n, blockIdx.x, hist, status, dev_status, DEV_WAIT_LIMIT,
+        for (uint32_t i = threadIdx.x; i <= nf; i += BLOCK) s_foff[i] = foff[i];
+    radix_tile<ITEMS, false, BLOCK>(kin, vin, kout, vout, n, blockIdx.x, hist, status, dev_status, DEV_WAIT_LIMIT,
                              FrameDigit{pass, foff, s_foff, foff_lds, nf});
 }
 
@@ -793,10 +793,13 @@ void launch_sort(const Plan& P, const Params& prm, hipStream_t st) {
     uint32_t* vout = P.idx_src == P.idx_a ? P.idx_b : P.idx_a;
     for (uint32_t pass = SORT_SHORT_FIRST; pass < P.sort_passes; ++pass) {
         // small inputs: many small tiles (latency); large: fewer, fuller tiles
-        auto kern = P.sort_items == 4 ? radix_pass_kernel<4> : radix_pass_kernel<16>;
-        hipLaunchKernelGGL(kern, dim3(P.sort_tiles), dim3(SORT_BLOCK), 0, st, kin, vin, kout, vout,
+        auto kern = P.sort_tile == 512u    ? radix_pass_kernel<2, 256>
+                    : P.sort_tile == 1024u ? radix_pass_kernel<4, 256>
+                    : P.sort_tile == 2048u ? radix_pass_kernel<4, 512>
+                                           : radix_pass_kernel<8, 512>;
+        hipLaunchKernelGGL(kern, dim3(P.sort_tiles), dim3(P.sort_tile <= 1024u ? 256 : 512), 0, st, kin, vin, kout, vout,
                            P.n, (int)pass, P.sort_hist + 256 * pass,
-                           P.sort_status + (size_t)pass * P.sort_tiles * 256, &P.ctr->status,
+                           P.sort_status + (size_t)(pass - SORT_SHORT_FIRST) * P.sort_tiles * 256, &P.ctr->status,
                            (const uint32_t*)P.foff, P.nf);
         const uint64_t* tk = kout;
         const uint32_t* tv = vout;

@@ -121,3 +121,43 @@ def test_queue_order_sizes(nf, chunk):
     finally:
         bd.close()
         den.close()
+
+
+@pytest.mark.parametrize("n", [16_383, 16_384, 16_385, 114_687, 114_689, 1_048_575, 1_048_577])
+def test_sort_tiles(n):
+    """The order of the radix passes at the edges of their tile sizes: by key
+    bits 32..62, then by original index."""
+    import torch
+    from paper_2512_10386_amd.binding import Denoiser
+    rng = np.random.default_rng(n)
+    xyz = torch.from_numpy(rng.uniform(0, 1, (n, 3)).astype(np.float32)).cuda()
+    xyz[n // 2:n // 2 + 400] = xyz[0]
+    den = Denoiser(0, k=4, leaf_cap=1024)
+    try:
+        den(xyz)
+        order = den.dump("ORDER", n).cpu().numpy().view(np.uint32)
+        key = den.dump("KEYS", n).cpu().numpy().view(np.uint64)
+        assert int(den.dump("STATUS", n).cpu().numpy()[0]) == 0
+    finally:
+        den.close()
+    assert np.array_equal(order, np.lexsort((np.arange(n), key >> np.uint64(32))))
+
+
+@pytest.mark.parametrize("nf,n", [(2, 30_000), (3, 200_000), (300, 1_050_000)])
+def test_sort_tiles_of_batches(nf, n):
+    """The same with the frame passes of a batch."""
+    import torch
+    from paper_2512_10386_amd.binding import BatchDenoiser
+    rng = np.random.default_rng(nf)
+    xyz = torch.from_numpy(rng.uniform(0, 1, (n, 3)).astype(np.float32)).cuda()
+    cut = np.sort(rng.integers(0, n + 1, nf - 1))
+    off = np.concatenate([[0], cut, [n]])
+    den = BatchDenoiser(0, k=4, leaf_cap=1024)
+    try:
+        den(xyz, torch.tensor(off, dtype=torch.int64, device="cuda"))
+        order = den.dump("ORDER", n).cpu().numpy().view(np.uint32)
+        key = den.dump("KEYS", n).cpu().numpy().view(np.uint64)
+    finally:
+        den.close()
+    frame = np.repeat(np.arange(nf), np.diff(off))
+    assert np.array_equal(order, np.lexsort((np.arange(n), key >> np.uint64(32), frame)))
