@@ -195,6 +195,9 @@ struct Params {
     int32_t stages;           // enabled modules: 1 voxel filter, 2 density filter, 4 score
 };
 
+// First candidate chunk length of the kNN plan.
+inline uint32_t plan_chunk0(const Params& prm) { return prm.knn_chunk > 0 ? (uint32_t)prm.knn_chunk : (uint32_t)KNN_CC0; }
+
 // Parameters of the score fit (loss and gradient of a relaxed ln F threshold).
 struct FitArgs {
     double alpha, sigma, gamma, tau, T, eps;

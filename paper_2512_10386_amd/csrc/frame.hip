@@ -808,6 +808,7 @@ void launch_sort(const Plan& P, const Params& prm, hipStream_t st) {
         kin = tk;
         vin = tv;
     }
+    if (P.n <= (uint32_t)prm.leaf_cap) return;  // no deep cells
     unsigned blocks = (P.n + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     if (blocks == 0) blocks = 1;

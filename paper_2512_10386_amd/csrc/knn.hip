@@ -1153,9 +1153,10 @@ void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st) {
                            knn_lds_bytes(KNN_TQ_SMALL, k, false), st, P, (const float4*)P.cand4, k);
 }
 
-void launch_knn_merge(const Plan& P, int k, int num_cus, hipStream_t st) {
+void launch_knn_merge(const Plan& P, const Params& prm, int num_cus, hipStream_t st) {
+    if (P.n <= plan_chunk0(prm)) return;  // no leaf can have more candidates than one chunk
     const unsigned blocks = (unsigned)(num_cus > 0 ? num_cus : 256) * 8u;
-    hipLaunchKernelGGL(knn_merge_kernel, dim3(blocks), dim3(64), 0, st, P, k);
+    hipLaunchKernelGGL(knn_merge_kernel, dim3(blocks), dim3(64), 0, st, P, prm.k);
 }
 
 }  // namespace gdn

@@ -563,8 +563,6 @@ __global__ __launch_bounds__(256) void halo_kernel(Plan P, uint32_t cap, uint32_
     }
 }
 
-static uint32_t plan_chunk0(const Params& prm) { return prm.knn_chunk > 0 ? (uint32_t)prm.knn_chunk : (uint32_t)KNN_CC0; }
-
 void launch_halo(const Plan& P, const Params& prm, hipStream_t st) {
     unsigned blocks = (P.n + HALO_LEAVES - 1) / HALO_LEAVES;
     if (blocks > 2048) blocks = 2048;

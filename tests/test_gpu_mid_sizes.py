@@ -161,3 +161,19 @@ def test_sort_tiles_of_batches(nf, n):
         den.close()
     frame = np.repeat(np.arange(nf), np.diff(off))
     assert np.array_equal(order, np.lexsort((np.arange(n), key >> np.uint64(32), frame)))
+
+
+@pytest.mark.parametrize("one_point", [False, True])
+@pytest.mark.parametrize("cap,chunk", [(5000, 5000), (5000, 4999), (4999, 5000), (4999, 4999)])
+def test_skipped_launches(oracle, one_point, cap, chunk):
+    """Chunk lengths and leaf caps around the number of points: where no leaf
+    can have two chunks, and no cell more points than a leaf."""
+    from paper_2512_10386_amd.binding import Denoiser
+    rng = np.random.default_rng(7)
+    xyz = np.ones((5000, 3), np.float32) if one_point else rng.normal(size=(5000, 3)).astype(np.float32)
+    ref = oracle.denoise(xyz, leaf_cap=cap, min_vox_count=1)
+    den = Denoiser(0, leaf_cap=cap, min_vox_count=1, knn_chunk=chunk)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
