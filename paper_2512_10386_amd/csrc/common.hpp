@@ -324,21 +324,37 @@ __device__ __forceinline__ void st_relaxed_agent(uint32_t* p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Wave-level inclusive scan (wave64).
+// Wave-level inclusive scan and sum (wave64, every lane active), by DPP: row
+// shifts inside the rows of 16 lanes, then the rows' last lanes broadcast to
+// the rows after them. A step takes the VALU's latency where a shuffle through
+// the LDS unit takes some hundred cycles, and the scans of a workgroup wait for
+// six of them in a row.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15 to rows 1, 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31 to rows 2, 3
     return v;
 }
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
+}
+
+// The lanes of `m` whose digit (8 bits) is this lane's. Per bit one ballot and
+// one three-input logic operation on each half of the mask.
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t m) {
+    uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int b = 0; b < 8; ++b) {
+        const uint32_t s = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);  // all ones where the bit is set
+        const uint64_t bb = __builtin_amdgcn_ballot_w64(s != 0u);
+        lo &= ~((uint32_t)bb ^ s);
+        hi &= ~((uint32_t)(bb >> 32) ^ s);
+    }
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // Block exclusive scan of one value per thread (blockDim multiple of 64, <= 1024).

@@ -498,13 +498,7 @@ __device__ void sort_cell(const Plan& P, uint32_t a, uint32_t b, bool deep, uint
             const uint32_t v = ok ? vs[i] : 0u;
             const uint32_t d = ok ? (uint32_t)(k >> shift) & 255u : 256u;
             // lanes of this wave with the same digit
-            uint64_t m = __ballot(ok);
-#pragma unroll
-            for (int bt = 0; bt < 8; ++bt) {
-                const bool bit = (d >> bt) & 1u;
-                const uint64_t bb = __ballot(bit);
-                m &= bit ? bb : ~bb;
-            }
+            const uint64_t m = match_digit(d, __ballot(ok));
             const uint32_t before = (uint32_t)__popcll(m & lt_mask);
             if (ok && (m >> lane) == 1ull) s_w[wave][d] = (uint32_t)__popcll(m);
             __syncthreads();
@@ -563,13 +557,7 @@ __device__ void sort_cell_lds(const Plan& P, uint32_t a, uint32_t b, bool deep, 
         for (int i = 0; i < SEG_ITEMS; ++i) {
             const bool ok = at(i) < n;
             const uint32_t dg = (uint32_t)(key[i] >> shift) & 255u;
-            uint64_t m = __ballot(ok);
-#pragma unroll
-            for (int bt = 0; bt < 8; ++bt) {
-                const bool bit = (dg >> bt) & 1u;
-                const uint64_t bb = __ballot(bit);
-                m &= bit ? bb : ~bb;
-            }
+            const uint64_t m = match_digit(dg, __ballot(ok));
             const uint32_t before = (uint32_t)__popcll(m & lt_mask);
             const uint32_t wb = ok ? s_w[wave][dg] : 0u;
             dig[i] = dg;

@@ -60,13 +60,7 @@ __device__ __forceinline__ void radix_tile(const K* __restrict__ kin, const uint
     for (int i = 0; i < ITEMS; ++i) {
         const uint32_t d = dig[i];
         const bool ok = d < 256u;
-        uint64_t m = __ballot(ok);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            bool bit = (d >> b) & 1u;
-            uint64_t bb = __ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = match_digit(d, __ballot(ok));
         uint32_t before = __popcll(m & lt_mask);
         uint32_t cnt = __popcll(m);
         uint32_t wb = ok ? s_w[wave][d & 255u] : 0u;

@@ -32,13 +32,7 @@ __device__ __forceinline__ void small_pass(uint64_t (&key)[ITEMS], uint32_t (&va
     for (int i = 0; i < ITEMS; ++i) {
         const bool ok = at(i) < n;
         const uint32_t d = digit(key[i], val[i]);
-        uint64_t m = __ballot(ok);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = __ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = match_digit(d, __ballot(ok));
         const uint32_t before = ok ? s_w[wave][d] : 0u;
         dig[i] = d;
         rank[i] = before + (uint32_t)__popcll(m & below);
