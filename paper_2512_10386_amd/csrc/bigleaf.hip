@@ -208,12 +208,6 @@ struct BigShared {
     unsigned long long val;
 };
 
-template <class T>
-__device__ __forceinline__ T wave_shfl_xor(T v, int o) {
-    if constexpr (sizeof(T) == 8) return (T)__shfl_xor((long long)v, o, 64);
-    else return (T)__shfl_xor((int)v, o, 64);
-}
-
 // Value of ascending rank r (0-based, r < n). Radix select: the bits all
 // values share are fixed first (otherwise every value would land in one bin of
 // the first histograms), then digits of up to 8 bits from the highest
@@ -226,10 +220,8 @@ __device__ T big_select(const Vals& vals, uint32_t r, BigShared& sh) {
         a &= v;
         o |= v;
     });
-    for (int off = 32; off > 0; off >>= 1) {
-        a &= wave_shfl_xor(a, off);
-        o |= wave_shfl_xor(o, off);
-    }
+    a = wave_and(a);
+    o = wave_or(o);
     __syncthreads();
     if (lane == 0u) {
         sh.red[wave][0] = a;
@@ -296,10 +288,7 @@ __device__ T big_next_rank(const Vals& vals, uint32_t r, T a, BigShared& sh) {
         else if (v < mn) mn = v;
     });
     le = wave_sum(le);
-    for (int off = 32; off > 0; off >>= 1) {
-        const T x = wave_shfl_xor(mn, off);
-        mn = x < mn ? x : mn;
-    }
+    mn = wave_umin(mn);
     __syncthreads();
     if (lane == 0u) {
         sh.red[wave][0] = le;

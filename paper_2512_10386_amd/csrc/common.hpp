@@ -343,6 +343,68 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
 }
 
+// Inclusive running maximum (every lane active).
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
+    auto step = [&](uint32_t o) { v = o > v ? o : v; };
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));
+    return v;
+}
+
+// Any associative, commutative f over the wave (every lane active) the same
+// way, 32- or 64-bit values, result in every lane; f(ident, v) = v.
+template <int CTRL, int ROWS, class T>
+__device__ __forceinline__ T dpp_from(T v, T ident) {
+    uint32_t a[sizeof(T) / 4], b[sizeof(T) / 4];
+    __builtin_memcpy(a, &v, sizeof(T));
+    __builtin_memcpy(b, &ident, sizeof(T));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i)
+        a[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)b[i], (int)a[i], CTRL, ROWS, 0xF, false);
+    __builtin_memcpy(&v, a, sizeof(T));
+    return v;
+}
+template <class T, class F>
+__device__ __forceinline__ T wave_reduce(T v, T ident, F f) {
+    v = f(v, dpp_from<0x111, 0xF>(v, ident));
+    v = f(v, dpp_from<0x112, 0xF>(v, ident));
+    v = f(v, dpp_from<0x114, 0xF>(v, ident));
+    v = f(v, dpp_from<0x118, 0xF>(v, ident));
+    v = f(v, dpp_from<0x142, 0xA>(v, ident));
+    v = f(v, dpp_from<0x143, 0xC>(v, ident));
+    uint32_t a[sizeof(T) / 4];
+    __builtin_memcpy(a, &v, sizeof(T));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) a[i] = (uint32_t)__builtin_amdgcn_readlane((int)a[i], 63);
+    __builtin_memcpy(&v, a, sizeof(T));
+    return v;
+}
+__device__ __forceinline__ float wave_fmin(float v) {
+    return wave_reduce(v, INFINITY, [](float a, float b) { return fminf(a, b); });
+}
+__device__ __forceinline__ float wave_fmax(float v) {
+    return wave_reduce(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
+    return wave_reduce(v, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+template <class T>
+__device__ __forceinline__ T wave_umin(T v) {
+    return wave_reduce(v, (T)~(T)0, [](T a, T b) { return a < b ? a : b; });
+}
+template <class T>
+__device__ __forceinline__ T wave_and(T v) {
+    return wave_reduce(v, (T)~(T)0, [](T a, T b) { return (T)(a & b); });
+}
+template <class T>
+__device__ __forceinline__ T wave_or(T v) {
+    return wave_reduce(v, (T)0, [](T a, T b) { return (T)(a | b); });
+}
+
 // The lanes of `m` whose digit (8 bits) is this lane's. Per bit one ballot and
 // one three-input logic operation on each half of the mask.
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t m) {
@@ -380,20 +442,16 @@ __device__ __forceinline__ XcdPart xcd_part(uint32_t n) {
 inline unsigned xcd_grid(unsigned blocks) { return (blocks + N_XCD - 1u) / N_XCD * N_XCD; }
 
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* smem, uint32_t* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    uint32_t inc = wave_incl_scan(v);
-    if (lane == 63) smem[wave] = inc;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const uint32_t inc = wave_incl_scan(v);
+    if (lane == 63u) smem[wave] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int w = 0; w < nw; ++w) { uint32_t t = smem[w]; smem[w] = run; run += t; }
-        smem[nw] = run;
-    }
+    // every wave scans the wave totals
+    const uint32_t t = wave_incl_scan(lane < nw ? smem[lane] : 0u);
+    const uint32_t before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)t, (int)wave - 1) : 0u;
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)t, 63);
     __syncthreads();
-    uint32_t ex = smem[wave] + inc - v;
-    *total = smem[nw];
-    __syncthreads();
-    return ex;
+    return before + inc - v;
 }
 
 // 3D bit interleave (x in the lowest bit), magic-number spreading.

@@ -37,7 +37,7 @@ void launch_zero(const Plan& P, hipStream_t st) {
 // with the repaired table (memory-safe, results unspecified).
 __global__ __launch_bounds__(256) void frames_kernel(const int64_t* __restrict__ in, uint32_t nf, uint32_t n,
                                                      uint32_t* foff, Counters* c) {
-    __shared__ uint32_t s_max[256];
+    __shared__ uint32_t s_max[4];
     constexpr uint32_t PER = (MAX_FRAMES + 1 + 255) / 256;
     const uint32_t t = threadIdx.x, b0 = t * PER;
     uint32_t v[PER];
@@ -57,18 +57,13 @@ __global__ __launch_bounds__(256) void frames_kernel(const int64_t* __restrict__
         m = x > m ? x : m;
         v[i] = m;  // running max within this thread's entries
     }
-    s_max[t] = m;
+    // max over earlier threads: of this wave by a scan, of the waves before it
+    const uint32_t inc = wave_incl_max(m);
+    if ((t & 63u) == 63u) s_max[t >> 6] = inc;
     __syncthreads();
-    if (t == 0) {
-        uint32_t run = 0;
-        for (int i = 0; i < 256; ++i) {
-            const uint32_t x = s_max[i];
-            s_max[i] = run;  // max over earlier threads
-            run = x > run ? x : run;
-        }
-    }
-    __syncthreads();
-    const uint32_t pre = s_max[t];
+    uint32_t pre = (uint32_t)__shfl_up((int)inc, 1, 64);
+    if ((t & 63u) == 0u) pre = 0u;
+    for (uint32_t w = 0; w < (t >> 6); ++w) pre = s_max[w] > pre ? s_max[w] : pre;
 #pragma unroll
     for (uint32_t i = 0; i < PER; ++i) {
         const uint32_t f = b0 + i;
@@ -99,14 +94,11 @@ constexpr uint32_t BBOX_CHUNK = 1024;
 
 __device__ __forceinline__ void bbox_reduce_wave(float* mn, float* mx, uint32_t& bad) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            mn[a] = fminf(mn[a], __shfl_xor(mn[a], o, 64));
-            mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], o, 64));
-        }
-        bad += __shfl_xor(bad, o, 64);
+    for (int a = 0; a < 3; ++a) {
+        mn[a] = wave_fmin(mn[a]);
+        mx[a] = wave_fmax(mx[a]);
     }
+    bad = wave_sum(bad);
 }
 
 // Adds the points [lo, hi) to a lane's box (non-finite points are counted
@@ -254,11 +246,8 @@ __global__ __launch_bounds__(256) void bbox_fold_kernel(Plan P) {
             v[6] += part[6];
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-            for (int a = 0; a < 6; ++a) v[a] = max(v[a], (uint32_t)__shfl_xor((int)v[a], o, 64));
-            v[6] += (uint32_t)__shfl_xor((int)v[6], o, 64);
-        }
+        for (int a = 0; a < 6; ++a) v[a] = wave_umax(v[a]);
+        v[6] = wave_sum(v[6]);
         FrameStat* st = P.fstat + f;
         if (lane < 3u) {
             if (v[lane]) atomicMax(&st->bbox_nmin[lane], v[lane]);
@@ -327,11 +316,8 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
             v[6] += part[6];
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-            for (int a = 0; a < 6; ++a) v[a] = max(v[a], (uint32_t)__shfl_xor((int)v[a], o, 64));
-            v[6] += (uint32_t)__shfl_xor((int)v[6], o, 64);
-        }
+        for (int a = 0; a < 6; ++a) v[a] = wave_umax(v[a]);
+        v[6] = wave_sum(v[6]);
         if (lane == 0) {
             for (int a = 0; a < 3; ++a) {
                 s_stat.bbox_nmin[a] = v[a];

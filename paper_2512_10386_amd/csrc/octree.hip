@@ -144,12 +144,10 @@ __global__ __launch_bounds__(256) void voxel_wave_kernel(Plan P, double beta, ui
             }
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                mn[a] = fminf(mn[a], __shfl_xor(mn[a], o, 64));
-                mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], o, 64));
-            }
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = wave_fmin(mn[a]);
+            mx[a] = wave_fmax(mx[a]);
+        }
         const float h32 = leaf_voxel_size(mn, mx, nt, beta);
         if (lane == 0u) P.leaf_h[t] = h32;
         if (h32 == 0.0f) {
@@ -231,12 +229,10 @@ __global__ __launch_bounds__(VOX_BLOCK) void voxel_kernel(Plan P, double beta, u
             mn[2] = fminf(mn[2], p.z); mx[2] = fmaxf(mx[2], p.z);
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                mn[a] = fminf(mn[a], __shfl_xor(mn[a], o, 64));
-                mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], o, 64));
-            }
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = wave_fmin(mn[a]);
+            mx[a] = wave_fmax(mx[a]);
+        }
         if (lane == 0)
             for (int a = 0; a < 3; ++a) { s_red[a][wave] = mn[a]; s_red[3 + a][wave] = mx[a]; }
         __syncthreads();
@@ -517,8 +513,9 @@ __global__ __launch_bounds__(256) void halo_kernel(Plan P, uint32_t cap, uint32_
             const uint2 own = s_r[grp][13];
             if (own.y > own.x && run.x <= own.x && own.x < run.y) P.leaf_own[t] = run;
         }
-        uint32_t len = (uint32_t)g < m ? cur.y - cur.x : 0u;
-        for (int o = 16; o > 0; o >>= 1) len += (uint32_t)__shfl_xor((int)len, o, 32);
+        const uint32_t lens = wave_incl_scan((uint32_t)g < m ? cur.y - cur.x : 0u);
+        const uint32_t len0 = (uint32_t)__builtin_amdgcn_readlane((int)lens, 31);
+        const uint32_t len = (lane & 32u) ? (uint32_t)__builtin_amdgcn_readlane((int)lens, 63) - len0 : len0;
         if (live && g == 0) {
             P.leaf_nr[t] = (uint32_t)__popcll(sm);
             P.leaf_ncand[t] = len;
@@ -611,21 +608,11 @@ __device__ __forceinline__ void block_excl_scan_n(const uint32_t (&v)[N], uint32
         for (int i = 0; i < N; ++i) smem[i * (nw + 1) + wave] = inc[i];
     }
     __syncthreads();
-    if (threadIdx.x < (unsigned)N) {
-        uint32_t* row = smem + threadIdx.x * (nw + 1);
-        uint32_t run = 0;
-        for (int w = 0; w < nw; ++w) {
-            const uint32_t t = row[w];
-            row[w] = run;
-            run += t;
-        }
-        row[nw] = run;
-    }
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        ex[i] = smem[i * (nw + 1) + wave] + inc[i] - v[i];
-        tot[i] = smem[i * (nw + 1) + nw];
+        const uint32_t t = wave_incl_scan(lane < nw ? smem[i * (nw + 1) + lane] : 0u);
+        ex[i] = (wave ? (uint32_t)__builtin_amdgcn_readlane((int)t, wave - 1) : 0u) + inc[i] - v[i];
+        tot[i] = (uint32_t)__builtin_amdgcn_readlane((int)t, 63);
     }
     __syncthreads();
 }
@@ -672,11 +659,10 @@ __global__ __launch_bounds__(PLAN_BLOCK) void knn_plan_kernel(Plan P, int chunk0
             items += (unsigned long long)((n1 + tq - 1) / tq) * nch;
             pairs += (unsigned long long)n1 * (nc - 1);
         });
-        for (int o = 32; o > 0; o >>= 1) {
-            lists += __shfl_xor(lists, o, 64);
-            items += __shfl_xor(items, o, 64);
-            pairs += __shfl_xor(pairs, o, 64);
-        }
+        const auto add = [](unsigned long long a, unsigned long long b) { return a + b; };
+        lists = wave_reduce(lists, 0ull, add);
+        items = wave_reduce(items, 0ull, add);
+        pairs = wave_reduce(pairs, 0ull, add);
         if (lane == 0) { s_red[wave][0] = lists; s_red[wave][1] = items; s_red[wave][2] = pairs; }
         __syncthreads();
         if (tid == 0) {
@@ -835,7 +821,7 @@ __global__ __launch_bounds__(256) void plan_count_kernel(Plan P, uint32_t chunk0
 #pragma unroll
     for (int i = 0; i < PLAN_LEVELS * 3 + 1; ++i) {
         unsigned long long v = acc[i];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        v = wave_reduce(v, 0ull, [](unsigned long long a, unsigned long long b) { return a + b; });
         if ((threadIdx.x & 63) == 0 && v) atomicAdd(&s_acc[i], v);
     }
     __syncthreads();

@@ -121,11 +121,8 @@ __device__ T block_next_rank(Get get, uint32_t cnt, uint32_t r, T a, uint32_t* s
         if (v <= a) ++le;
         else if (v < mn) mn = v;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        le += (uint32_t)__shfl_xor((int)le, o, 64);
-        const T x = (T)__shfl_xor(mn, o, 64);
-        mn = x < mn ? x : mn;
-    }
+    le = wave_sum(le);
+    mn = wave_umin(mn);
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         s_le[w] = le;
@@ -376,11 +373,7 @@ __device__ __forceinline__ unsigned long long wave_next_rank(const WaveVals& w, 
         le += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in && w.v[j] <= a));
         if (in && w.v[j] > a && w.v[j] < mn) mn = w.v[j];
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long x = (unsigned long long)__shfl_xor((long long)mn, off, 64);
-        mn = x < mn ? x : mn;
-    }
+    mn = wave_umin(mn);
     return le > r + 1u ? a : mn;
 }
 

@@ -136,11 +136,8 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
         bad += in && !fin ? 1u : 0u;
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-        for (int a = 0; a < 6; ++a) b[a] = fminf(b[a], __shfl_xor(b[a], o, 64));
-        bad += __shfl_xor(bad, o, 64);
-    }
+    for (int a = 0; a < 6; ++a) b[a] = wave_fmin(b[a]);
+    bad = wave_sum(bad);
     if (lane == 0u) {
 #pragma unroll
         for (int a = 0; a < 6; ++a) s_box[a][wave] = b[a];
@@ -151,13 +148,10 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
         const uint32_t w = lane & (SMALL_WAVES - 1u);
 #pragma unroll
         for (int a = 0; a < 6; ++a) b[a] = s_box[a][w];
-        bad = s_bad[w];
+        bad = lane < (uint32_t)SMALL_WAVES ? s_bad[w] : 0u;
 #pragma unroll
-        for (int o = SMALL_WAVES / 2; o > 0; o >>= 1) {
-#pragma unroll
-            for (int a = 0; a < 6; ++a) b[a] = fminf(b[a], __shfl_xor(b[a], o, 64));
-            bad += __shfl_xor(bad, o, 64);
-        }
+        for (int a = 0; a < 6; ++a) b[a] = wave_fmin(b[a]);
+        bad = wave_sum(bad);
         if (lane == 0u) {
             FrameStat fs;
             for (int a = 0; a < 3; ++a) {

@@ -208,11 +208,8 @@ __device__ __forceinline__ unsigned long long wave_select(const unsigned long lo
             a &= v[j];
             o |= v[j];
         }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        a &= (unsigned long long)__shfl_xor((long long)a, off, 64);
-        o |= (unsigned long long)__shfl_xor((long long)o, off, 64);
-    }
+    a = wave_and(a);
+    o = wave_or(o);
     if (a == o) return a;
     int top = 63 - __builtin_clzll(a ^ o);
     unsigned long long mask = top >= 63 ? 0ull : (~0ull << (top + 1));
