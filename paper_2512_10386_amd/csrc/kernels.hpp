@@ -18,7 +18,7 @@ void launch_bbox(const Plan& P, const float* xyz, hipStream_t st, bool clear = f
 void launch_morton(const Plan& P, const Params& prm, const float* xyz, hipStream_t st);
 void launch_sort(const Plan& P, const Params& prm, hipStream_t st);
 
-// small.hip: everything from the zero-fill to the leaves for one small frame
+// small.hip: everything from the zero-fill to the P1 compaction for one small frame
 bool small_tree(const Plan& P);
 void launch_small_tree(const Plan& P, const Params& prm, const float* xyz, hipStream_t st);
 

@@ -1,8 +1,9 @@
 // The octree of a small frame in one workgroup: bounding box, Morton keys,
-// their sort and the leaves, held in registers and LDS from the first load to
-// the last store.
+// their sort and the leaves, then the voxel filter and P1, held in registers
+// and LDS from the first load to the last store.
 #include "kernels.hpp"
 #include "tree.hpp"
+#include "voxel.hpp"
 
 namespace gdn {
 
@@ -83,21 +84,42 @@ __device__ __forceinline__ void small_pass(uint64_t (&key)[ITEMS], uint32_t (&va
         }
 }
 
+// One step of the running minima m[0..2] and maxima m[3..5] over the lanes of
+// one leaf (leaves are runs of lanes), in the manner of wave_incl_scan.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void run_step(uint32_t leaf, float (&m)[6]) {
+    const bool same = dpp_from<CTRL, ROWS>(leaf, ~leaf) == leaf;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        const float v = dpp_from<CTRL, ROWS>(m[a], m[a]);
+        m[a] = same ? (a < 3 ? fminf(m[a], v) : fmaxf(m[a], v)) : m[a];
+    }
+}
+
 // n <= SMALL_BLOCK * ITEMS points of one frame. Latency bounds it: at these
 // sizes each kernel of the general path (box, keys, four sort passes, two for
 // deep cells, leaf borders, their scan) takes the few microseconds that any
 // launch and its first loads take, so one workgroup that keeps the points on
 // chip is faster than ten launches over the whole chip. Whole calls, general
 // path and this one: 65 points 90 and 69 us, 500 101 and 78, 1501 112 and 89.
-template <int ITEMS>
+// Most of it is the sort: a pass is six barriers over 16 waves, 3 us.
+// P1: the voxel filter and the P1 compaction too, by all threads over the
+// points (leaf boxes, then hash tables, in the LDS that the sort is done with):
+// 500 points 63.6 us a call without and 56.4 with it, 1501 74.2 and 71.3, but
+// 4096, where a workgroup per leaf does more at once, 98.1 and 101.0.
+template <int ITEMS, bool P1>
 __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __restrict__ xyz, Plan P,
-                                                                 double min_leaf_side, uint32_t cap) {
-    __shared__ uint64_t s_key[SMALL_BLOCK * ITEMS];
-    __shared__ uint32_t s_val[SMALL_BLOCK * ITEMS];
-    __shared__ uint32_t s_w[SMALL_WAVES][256];
+                                                                 double min_leaf_side, uint32_t cap, double beta,
+                                                                 uint32_t nv) {
+    constexpr uint32_t N = SMALL_BLOCK * ITEMS;
+    constexpr uint32_t SORT_BYTES = 13u * N + 4u * SMALL_WAVES * 256u, P1_BYTES = P1 ? 32u * N + 16u : 0u;
+    __shared__ __align__(16) char s_raw[SORT_BYTES > P1_BYTES ? SORT_BYTES : P1_BYTES];
+    uint64_t* const s_key = (uint64_t*)s_raw;
+    uint32_t* const s_val = (uint32_t*)(s_raw + 8u * N);
+    uint32_t(*const s_w)[256] = (uint32_t(*)[256])(s_raw + 12u * N);
+    uint8_t* const s_mark = (uint8_t*)(s_raw + 12u * N + 4u * SMALL_WAVES * 256u);
     __shared__ uint32_t s_part[4][256];
     __shared__ uint32_t s_scan[SMALL_WAVES + 1];
-    __shared__ uint8_t s_mark[SMALL_BLOCK * ITEMS];
     __shared__ float s_box[6][SMALL_WAVES];
     __shared__ uint32_t s_bad[SMALL_WAVES];
     __shared__ FrameConst s_fc;
@@ -256,23 +278,164 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
         base += w < wave ? c : 0u;
         total += c;
     }
+    float4 p[ITEMS];
+    uint32_t leaf[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const size_t o = at(i) < n ? val[i] & SMALL_IDX : 0u;
+        p[i] = make_float4(xyz[3 * o], xyz[3 * o + 1], xyz[3 * o + 2], __uint_as_float((uint32_t)o));
+    }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const uint32_t s = at(i);
+        const uint32_t e = base + ex[i];
+        leaf[i] = s < n ? e + (flag[i] ? 1u : 0u) - 1u : ~0u;
         if (s < n) {
-            const uint32_t o = val[i] & SMALL_IDX, e = base + ex[i];
             P.keys_a[s] = key[i];
-            P.idx_a[s] = o;
-            P.pos4[s] = make_float4(xyz[3 * (size_t)o], xyz[3 * (size_t)o + 1], xyz[3 * (size_t)o + 2], __uint_as_float(o));
-            P.leaf_of[s] = e + (flag[i] ? 1u : 0u) - 1u;
+            P.idx_a[s] = __float_as_uint(p[i].w);
+            P.pos4[s] = p[i];
+            P.leaf_of[s] = leaf[i];
             if (flag[i]) P.leaf_begin[e] = s;
-            if (P.big_leaves)  // the leaf boxes of launch_big_voxel start empty
+            if (!P1 && P.big_leaves)  // the leaf boxes of launch_big_voxel start empty
                 for (uint32_t a = 0; a < 6u; ++a) P.leaf_box[6 * (size_t)s + a] = 0u;
         }
     }
     if (tid == 0) {
         P.ctr->n_leaves = total;
         P.leaf_begin[total] = n;
+    }
+    if constexpr (P1) {
+        // first points and boxes of the leaves (ordered-uint minima, maxima)
+        uint32_t* const s_lbox = (uint32_t*)s_raw;           // [6][N]
+        uint32_t* const s_begin = (uint32_t*)s_raw + 6u * N;  // [N + 1]
+        float* const s_h = (float*)s_raw + 7u * N + 1u;       // [N]
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (flag[i]) s_begin[leaf[i]] = at(i);
+        if (tid == 0) s_begin[total] = n;
+        for (uint32_t t = tid; t < total; t += SMALL_BLOCK)
+#pragma unroll
+            for (uint32_t a = 0; a < 6u; ++a) s_lbox[a * N + t] = f32_ordered(a < 3u ? INFINITY : -INFINITY);
+        __syncthreads();
+        // a leaf's run of lanes is reduced into its last lane, which adds it to
+        // the leaf's box
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const float c[3] = {p[i].x, p[i].y, p[i].z};
+            float m[6];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                m[a] = fminf(c[a], INFINITY);
+                m[3 + a] = fmaxf(c[a], -INFINITY);
+            }
+            run_step<0x111, 0xF>(leaf[i], m);
+            run_step<0x112, 0xF>(leaf[i], m);
+            run_step<0x114, 0xF>(leaf[i], m);
+            run_step<0x118, 0xF>(leaf[i], m);
+            run_step<0x142, 0xA>(leaf[i], m);
+            run_step<0x143, 0xC>(leaf[i], m);
+            const uint32_t next = (uint32_t)__shfl_down((int)leaf[i], 1, 64);
+            if (leaf[i] != ~0u && (lane == 63u || next != leaf[i])) {
+#pragma unroll
+                for (uint32_t a = 0; a < 6u; ++a) {
+                    if (a < 3u) atomicMin(&s_lbox[a * N + leaf[i]], f32_ordered(m[a]));
+                    else atomicMax(&s_lbox[a * N + leaf[i]], f32_ordered(m[a]));
+                }
+            }
+        }
+        __syncthreads();
+        for (uint32_t t = tid; t < total; t += SMALL_BLOCK) {
+            float lo[3], hi[3];
+#pragma unroll
+            for (uint32_t a = 0; a < 3u; ++a) {
+                lo[a] = f32_from_ordered(s_lbox[a * N + t]);
+                hi[a] = f32_from_ordered(s_lbox[(3u + a) * N + t]);
+            }
+            const float h = leaf_voxel_size(lo, hi, s_begin[t + 1u] - s_begin[t], beta);
+            s_h[t] = h;
+            P.leaf_h[t] = h;
+        }
+        __syncthreads();
+        uint64_t vk[ITEMS];
+        float h[ITEMS];
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t t = min(leaf[i], total - 1u);
+            h[i] = s_h[t];
+            vk[i] = h[i] == 0.0f ? 0ull
+                                 : vox_key(p[i], f32_from_ordered(s_lbox[t]), f32_from_ordered(s_lbox[N + t]),
+                                           f32_from_ordered(s_lbox[2u * N + t]), (double)h[i]);
+        }
+        __syncthreads();  // the boxes have been read
+        // occupancy: an open-addressing table of 2 nt slots per leaf
+        constexpr unsigned long long EMPTY = ~0ull;
+        unsigned long long* const s_tk = (unsigned long long*)s_raw;  // [2 N], 16 N bytes
+        uint32_t* const s_tc = (uint32_t*)(s_raw + 16u * N);          // [2 N], up to byte 24 N
+        for (uint32_t j = tid; j < 2u * n; j += SMALL_BLOCK) {
+            s_tk[j] = EMPTY;
+            s_tc[j] = 0u;
+        }
+        __syncthreads();
+        uint32_t slot[ITEMS], nt[ITEMS];
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            if (leaf[i] == ~0u) continue;
+            const uint32_t lb = s_begin[leaf[i]];
+            nt[i] = s_begin[leaf[i] + 1u] - lb;
+            if (h[i] == 0.0f) continue;
+            const uint32_t slots = 2u * nt[i];
+            uint32_t r = __umulhi(vox_hash(vk[i]), slots);
+            for (uint32_t probe = 0; probe < slots; ++probe) {
+                const unsigned long long prev = atomicCAS(&s_tk[2u * lb + r], EMPTY, (unsigned long long)vk[i]);
+                if (prev == EMPTY || prev == vk[i]) break;
+                r = r + 1u == slots ? 0u : r + 1u;
+            }
+            slot[i] = 2u * lb + r;
+            atomicAdd(&s_tc[slot[i]], 1u);
+        }
+        __syncthreads();
+        // P1 and its places
+        bool in1[ITEMS];
+        cnt = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t s = at(i);
+            in1[i] = false;
+            if (s < n) {
+                const uint32_t occ = h[i] == 0.0f ? nt[i] : s_tc[slot[i]];
+                in1[i] = occ >= nv;
+                P.occ[s] = occ;
+                P.p1[s] = in1[i];
+            }
+            const uint64_t m = __ballot(in1[i]);
+            ex[i] = cnt + (uint32_t)__popcll(m & below);
+            cnt += (uint32_t)__popcll(m);
+        }
+        if (lane == 0u) s_scan[wave] = cnt;
+        __syncthreads();
+        base = 0;
+        total = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < (uint32_t)SMALL_WAVES; ++w) {
+            const uint32_t c = s_scan[w];
+            base += w < wave ? c : 0u;
+            total += c;
+        }
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t s = at(i), q = base + ex[i];
+            if (s < n) P.p1pos[s] = q;
+            if (in1[i]) {
+                P.cand4[q] = p[i];
+                P.cand_leaf[q] = leaf[i];
+                P.inv_p1[__float_as_uint(p[i].w)] = q;
+            }
+        }
+        if (tid == 0) {
+            P.ctr->n_p1 = total;
+            P.ctr->knn_tq = knn_tile_queries(total, P.tq_max);
+            P.p1pos[n] = total;
+        }
     }
 }
 
@@ -282,10 +445,15 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
 bool small_tree(const Plan& P) { return P.nf == 1 && P.n <= 4u * SMALL_BLOCK; }
 
 void launch_small_tree(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
-    auto kern = P.n <= (uint32_t)SMALL_BLOCK       ? small_tree_kernel<1>
-                : P.n <= 2u * (uint32_t)SMALL_BLOCK ? small_tree_kernel<2>
-                                                    : small_tree_kernel<4>;
-    hipLaunchKernelGGL(kern, dim3(1), dim3(SMALL_BLOCK), 0, st, xyz, P, prm.min_leaf_side, (uint32_t)prm.leaf_cap);
+    auto kern = P.n <= (uint32_t)SMALL_BLOCK        ? small_tree_kernel<1, true>
+                : P.n <= 2u * (uint32_t)SMALL_BLOCK ? small_tree_kernel<2, true>
+                                                    : small_tree_kernel<4, false>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(SMALL_BLOCK), 0, st, xyz, P, prm.min_leaf_side, (uint32_t)prm.leaf_cap,
+                       prm.beta, (uint32_t)prm.min_vox_count);
+    if (P.n > 2u * (uint32_t)SMALL_BLOCK) {
+        launch_voxel(P, prm, st);
+        launch_p1_compact(P, st);
+    }
 }
 
 }  // namespace gdn
