@@ -38,62 +38,80 @@ __device__ __forceinline__ Dens density_at(const Plan& P, const float* __restric
 
 // ---------------------------------------------------------------- block radix select
 
-// Wave 0 finds the histogram bin holding ascending rank r; out = {bin, count
-// below it, count in it}.
-__device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t r, uint32_t* out) {
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        const uint32_t h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-        const uint32_t s = h0 + h1 + h2 + h3;
-        const uint32_t inc = wave_incl_scan(s);
-        const uint32_t ex = inc - s;
-        if (ex <= r && r < inc) {
-            uint32_t acc = ex;
-            int b = 4 * lane;
-            if (r >= acc + h0) {
-                acc += h0; ++b;
-                if (r >= acc + h1) {
-                    acc += h1; ++b;
-                    if (r >= acc + h2) { acc += h2; ++b; }
-                }
-            }
-            out[0] = (uint32_t)b;
-            out[1] = acc;
-            out[2] = hist[b];
-        }
-    }
-}
-
-// Value of ascending rank r (0-based, r < cnt) among get(0..cnt-1), by 8-bit
-// MSD passes over LDS histograms; once the selected bin holds a single value,
-// that value is the answer and is fetched directly. Whole block must call it.
-// s_sel needs SEL_SCRATCH words.
+// Value of ascending rank r (0-based) among get(0..cnt-1), or among those that
+// are not zero (SKIP0). Radix select: the bits that all of them share are found
+// first, then come digits of up to 8 bits from the highest differing one down,
+// over three LDS histograms in turn, so that a pass has one barrier (its counts
+// are complete): every wave finds the digit by itself, and clears the histogram
+// of the pass after the next. A digit that holds one value ends it. The whole
+// workgroup (SEL_BLOCK threads) calls it; s_sel needs SEL_SCRATCH words. It is
+// a chain of latencies, a barrier and an LDS round trip or two per pass: with
+// digits of the whole value from the top and five barriers a pass, calls took
+// 138.0 us (20k points) and 290.1 (120k), now 136.0 and 287.8.
 constexpr int SEL_SCRATCH = 6;
+constexpr int SEL_HISTS = 3;
 
-template <typename T, class Get>
-__device__ T block_select(Get get, uint32_t cnt, uint32_t r, uint32_t* s_hist, uint32_t* s_sel) {
-    constexpr int BITS = 8 * (int)sizeof(T);
-    T prefix = 0, mask = 0;
-    for (int shift = BITS - 8; shift >= 0; shift -= 8) {
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) s_hist[i] = 0u;
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < cnt; i += blockDim.x) {
+template <typename T, bool SKIP0 = false, class Get>
+__device__ T block_select(Get get, uint32_t cnt, uint32_t r, uint32_t (*s_hist)[256], uint32_t* s_sel) {
+    __shared__ T s_bits[SEL_BLOCK / 64][2];
+    static_assert(SEL_BLOCK == 256, "a thread per histogram bin");
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    T a = ~(T)0, o = 0;
+    for (uint32_t i = threadIdx.x; i < cnt; i += SEL_BLOCK) {
+        const T v = get(i);
+        if (SKIP0 && v == 0) continue;
+        a &= v;
+        o |= v;
+    }
+    a = wave_and(a);
+    o = wave_or(o);
+    __syncthreads();  // (an earlier select's reads)
+    if (lane == 0u) {
+        s_bits[wave][0] = a;
+        s_bits[wave][1] = o;
+    }
+#pragma unroll
+    for (int b = 0; b < SEL_HISTS; ++b) s_hist[b][threadIdx.x] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < SEL_BLOCK / 64; ++w) {
+        a &= s_bits[w][0];
+        o |= s_bits[w][1];
+    }
+    if (a == o) return a;
+    int top = 63 - __builtin_clzll((unsigned long long)(T)(a ^ o));
+    T mask = top + 1 >= 8 * (int)sizeof(T) ? (T)0 : (T)(~(T)0 << (top + 1));
+    T prefix = a & mask;
+    uint32_t *h = s_hist[0], *h1 = s_hist[1], *h2 = s_hist[2];
+    while (true) {
+        const int lo = top >= 7 ? top - 7 : 0;
+        const uint32_t dm = (2u << (top - lo)) - 1u;
+        for (uint32_t i = threadIdx.x; i < cnt; i += SEL_BLOCK) {
             const T v = get(i);
-            if ((v & mask) == prefix) atomicAdd(&s_hist[(uint32_t)(v >> shift) & 255u], 1u);
+            if ((v & mask) == prefix && !(SKIP0 && v == 0)) atomicAdd(&h[(uint32_t)(v >> lo) & dm], 1u);
         }
         __syncthreads();
-        find_bin(s_hist, r, s_sel);
-        __syncthreads();
-        r -= s_sel[1];
-        prefix |= (T)s_sel[0] << shift;
-        mask |= (T)255 << shift;
-        const bool single = s_sel[2] == 1u;
-        __syncthreads();
-        if (single && shift > 0) {
-            // exactly one value carries this prefix
-            for (uint32_t i = threadIdx.x; i < cnt; i += blockDim.x) {
+        h2[threadIdx.x] = 0u;
+        const uint32_t c0 = h[4u * lane], c1 = h[4u * lane + 1u], c2 = h[4u * lane + 2u], c3 = h[4u * lane + 3u];
+        const uint32_t s = c0 + c1 + c2 + c3;
+        const uint32_t inc = wave_incl_scan(s), ex = inc - s;
+        uint32_t acc = ex, b = 4u * lane, n = c0;
+        if (r >= acc + n) { acc += n; ++b; n = c1; }
+        if (b == 4u * lane + 1u && r >= acc + n) { acc += n; ++b; n = c2; }
+        if (b == 4u * lane + 2u && r >= acc + n) { acc += n; ++b; n = c3; }
+        const int L = __ffsll((long long)__builtin_amdgcn_ballot_w64(ex <= r && r < inc)) - 1;
+        b = (uint32_t)__builtin_amdgcn_readlane((int)b, L);
+        acc = (uint32_t)__builtin_amdgcn_readlane((int)acc, L);
+        n = (uint32_t)__builtin_amdgcn_readlane((int)n, L);
+        r -= acc;
+        prefix |= (T)b << lo;
+        mask |= (T)dm << lo;
+        if (lo == 0) return prefix;
+        if (n == 1u) {
+            // one value carries this prefix
+            for (uint32_t i = threadIdx.x; i < cnt; i += SEL_BLOCK) {
                 const T v = get(i);
-                if ((v & mask) == prefix) {
+                if ((v & mask) == prefix && !(SKIP0 && v == 0)) {
                     s_sel[3] = (uint32_t)v;
                     if constexpr (sizeof(T) > 4) s_sel[4] = (uint32_t)((unsigned long long)v >> 32);
                 }
@@ -101,11 +119,14 @@ __device__ T block_select(Get get, uint32_t cnt, uint32_t r, uint32_t* s_hist, u
             __syncthreads();
             T out = (T)s_sel[3];
             if constexpr (sizeof(T) > 4) out |= (T)((unsigned long long)s_sel[4] << 32);
-            __syncthreads();
             return out;
         }
+        top = lo - 1;
+        uint32_t* const was = h;
+        h = h1;
+        h1 = h2;
+        h2 = was;
     }
-    return prefix;
 }
 
 // Given a = the value of ascending rank r, the value of rank r + 1: a again
@@ -189,13 +210,13 @@ __device__ uint32_t block_leaf_round(const Plan& P, uint32_t base, uint32_t nl, 
 // the middle value, or the mean of the two middle values for even n1.
 
 template <class RG>
-__device__ float leaf_cut(RG r2, uint32_t n1, double q, uint32_t* s_hist, uint32_t* s_sel) {
+__device__ float leaf_cut(RG r2, uint32_t n1, double q, uint32_t (*s_hist)[256], uint32_t* s_sel) {
     const uint32_t c = percentile_rank(n1, q);
     return __uint_as_float(block_select<uint32_t>(r2, n1, n1 - c, s_hist, s_sel));
 }
 
 template <class HG>
-__device__ void leaf_median(HG rho, uint32_t n1, double* med, uint32_t* s_hist, uint32_t* s_sel) {
+__device__ void leaf_median(HG rho, uint32_t n1, double* med, uint32_t (*s_hist)[256], uint32_t* s_sel) {
     if (n1 & 1u) {
         *med = __longlong_as_double((long long)block_select<unsigned long long>(rho, n1, (n1 - 1) / 2, s_hist, s_sel));
     } else {
@@ -213,7 +234,7 @@ __device__ void leaf_median(HG rho, uint32_t n1, double* med, uint32_t* s_hist, 
 template <bool SQRT>
 __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params prm, bool small,
                                                                const float* __restrict__ xyz) {
-    __shared__ uint32_t s_hist[256];
+    __shared__ uint32_t s_hist[SEL_HISTS][256];
     __shared__ uint32_t s_sel[SEL_SCRATCH];
     __shared__ uint32_t s_r2[SEL_LDS_MAX];
     __shared__ unsigned long long s_rho[SEL_LDS_MAX];
@@ -605,9 +626,10 @@ struct ScoreKey {
 // theta = the m-th largest key, idx_cut = the largest original index kept
 // among the keys equal to theta.
 template <class KG, class IG>
-__device__ void topl_cut(KG key, IG tie_idx_of, uint32_t n1, uint32_t m, unsigned long long* theta,
-                         uint32_t* idx_cut, uint32_t* s_hist, uint32_t* s_sel, uint32_t* s_cnt) {
-    const unsigned long long th = block_select<unsigned long long>(key, n1, n1 - m, s_hist, s_sel);
+__device__ void topl_cut(KG key, IG tie_idx_of, uint32_t n1, uint32_t n2, uint32_t m, unsigned long long* theta,
+                         uint32_t* idx_cut, uint32_t (*s_hist)[256], uint32_t* s_sel, uint32_t* s_cnt) {
+    // (the keys of points outside P2 are zero)
+    const unsigned long long th = block_select<unsigned long long, true>(key, n1, n2 - m, s_hist, s_sel);
     uint32_t* const s_eq = s_sel + SEL_SCRATCH - 1;  // free between selects
     if (threadIdx.x == 0) { *s_cnt = 0; *s_eq = 0; }
     __syncthreads();
@@ -640,7 +662,7 @@ struct CandIdx {
 };
 
 __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, bool small, ToplOut out) {
-    __shared__ uint32_t s_hist[256];
+    __shared__ uint32_t s_hist[SEL_HISTS][256];
     __shared__ uint32_t s_sel[SEL_SCRATCH];
     __shared__ uint32_t s_cnt;
     __shared__ unsigned long long s_key[SEL_LDS_MAX];
@@ -728,7 +750,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
             unsigned long long theta = ~0ull;
             uint32_t idx_cut = 0;
             if (m > 0)
-                topl_cut(LdsBits<unsigned long long>{s_key}, LdsBits<uint32_t>{s_idx}, n1, m, &theta, &idx_cut,
+                topl_cut(LdsBits<unsigned long long>{s_key}, LdsBits<uint32_t>{s_idx}, n1, n2, m, &theta, &idx_cut,
                          s_hist, s_sel, &s_cnt);
 #pragma unroll
             for (int u = 0; u < SU; ++u) {
@@ -766,10 +788,10 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
                     s_idx[i] = __float_as_uint(P.cand4[qb + i].w);
                 }
                 __syncthreads();
-                topl_cut(LdsBits<unsigned long long>{s_key}, LdsBits<uint32_t>{s_idx}, n1, m, &theta, &idx_cut,
+                topl_cut(LdsBits<unsigned long long>{s_key}, LdsBits<uint32_t>{s_idx}, n1, n2, m, &theta, &idx_cut,
                          s_hist, s_sel, &s_cnt);
             } else {
-                topl_cut(key, CandIdx{P.cand4, qb}, n1, m, &theta, &idx_cut, s_hist, s_sel, &s_cnt);
+                topl_cut(key, CandIdx{P.cand4, qb}, n1, n2, m, &theta, &idx_cut, s_hist, s_sel, &s_cnt);
             }
         }
         for (uint32_t i = threadIdx.x; i < n1; i += blockDim.x) {
