@@ -9,34 +9,16 @@
 
 namespace gdn {
 
-// ---------------------------------------------------------------- zero fill
+// ---------------------------------------------------------------- zero fill, frame table
 
-__global__ void zero_kernel(uint4* p, size_t n16, uint32_t* foff, uint32_t n, uint32_t one_frame) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (one_frame && blockIdx.x == 0 && threadIdx.x == 0) {
-        foff[0] = 0u;
-        foff[1] = n;
-    }
-}
-
-void launch_zero(const Plan& P, hipStream_t st) {
-    size_t n16 = P.zero_bytes / 16;
-    unsigned blocks = (unsigned)((n16 + 255) / 256);
-    if (blocks > 2048) blocks = 2048;
-    if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, (uint4*)P.zero_begin, n16, P.foff, P.n,
-                       P.nf == 1 ? 1u : 0u);
-}
-
-// ---------------------------------------------------------------- frame table
-//
 // Checked copy of the caller's frame offsets (int64[nf+1]): clamped to [0, n]
 // and made non-decreasing (a running maximum), with foff[0] = 0 and
 // foff[nf] = n. Any repair sets DEV_BAD_FRAMES; the batch is then processed
-// with the repaired table (memory-safe, results unspecified).
-__global__ __launch_bounds__(256) void frames_kernel(const int64_t* __restrict__ in, uint32_t nf, uint32_t n,
-                                                     uint32_t* foff, Counters* c) {
+// with the repaired table (memory-safe, results unspecified). One workgroup;
+// it also writes the first 16 bytes of the counters, the status word among
+// them, which are otherwise zero.
+__device__ __forceinline__ void frame_table(const int64_t* __restrict__ in, uint32_t nf, uint32_t n, uint32_t* foff,
+                                            Counters* c) {
     __shared__ uint32_t s_max[4];
     constexpr uint32_t PER = (MAX_FRAMES + 1 + 255) / 256;
     const uint32_t t = threadIdx.x, b0 = t * PER;
@@ -74,11 +56,38 @@ __global__ __launch_bounds__(256) void frames_kernel(const int64_t* __restrict__
             foff[f] = x;
         }
     }
-    if (bad) atomicOr(&c->status, DEV_BAD_FRAMES);
+    const int any = __syncthreads_or((int)bad);
+    static_assert(offsetof(Counters, status) == 0, "the status word opens the counters");
+    if (t == 0) *(uint4*)c = make_uint4(any ? DEV_BAD_FRAMES : 0u, 0u, 0u, 0u);
 }
 
-void launch_frames(const Plan& P, const int64_t* frame_off, hipStream_t st) {
-    hipLaunchKernelGGL(frames_kernel, dim3(1), dim3(256), 0, st, frame_off, P.nf, P.n, P.foff, P.ctr);
+// Clears the zeroed block (the counters first). A batch's frame table is made
+// beside it by workgroup 0 (as a launch of its own it took 5 us of a batch of
+// 12 objects' 232).
+template <bool BATCH>
+__global__ __launch_bounds__(256) void zero_kernel(Plan P, uint4* p, size_t n16, const int64_t* __restrict__ frame_off) {
+    if (BATCH && blockIdx.x == 0) {
+        frame_table(frame_off, P.nf, P.n, P.foff, P.ctr);
+        return;
+    }
+    constexpr size_t B = BATCH ? 1 : 0;  // blocks and words that are the table's
+    for (size_t i = B + (blockIdx.x - B) * (size_t)blockDim.x + threadIdx.x; i < n16; i += (gridDim.x - B) * (size_t)blockDim.x)
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (!BATCH && blockIdx.x == 0 && threadIdx.x == 0) {
+        P.foff[0] = 0u;
+        P.foff[1] = P.n;
+    }
+}
+
+void launch_zero(const Plan& P, const int64_t* frame_off, hipStream_t st) {
+    size_t n16 = P.zero_bytes / 16;
+    unsigned blocks = (unsigned)((n16 + 255) / 256);
+    if (blocks > 2048) blocks = 2048;
+    if (blocks == 0) blocks = 1;
+    if (frame_off)
+        hipLaunchKernelGGL(zero_kernel<true>, dim3(blocks + 1), dim3(256), 0, st, P, (uint4*)P.zero_begin, n16, frame_off);
+    else
+        hipLaunchKernelGGL(zero_kernel<false>, dim3(blocks), dim3(256), 0, st, P, (uint4*)P.zero_begin, n16, frame_off);
 }
 
 // ---------------------------------------------------------------- bbox
@@ -287,7 +296,9 @@ void launch_bbox(const Plan& P, const float* xyz, hipStream_t st, bool clear) {
 
 // ---------------------------------------------------------------- Morton keys
 
-// Frame constants of every frame of a batch (one thread per frame).
+// Frame constants of every frame of a large batch (one thread per frame); with
+// up to FC_LDS frames each block of the key kernel computes them itself.
+constexpr uint32_t FC_LDS = 64;
 __global__ __launch_bounds__(256) void frame_const_kernel(Plan P, double min_leaf_side) {
     for (uint32_t f = threadIdx.x; f < P.nf; f += blockDim.x) frame_consts(P.fstat + f, min_leaf_side, P.fc + f);
 }
@@ -299,14 +310,23 @@ constexpr uint32_t MORTON_U = 8;
 // nparts > 0: a single frame whose box is in nparts per-block records of
 // bbox_one_kernel, folded here by every block (block 0 also stores the
 // frame's statistics and constants and flags non-finite input).
+// FRAMES: 1 for a single frame, otherwise FC_LDS or MAX_FRAMES, the most there
+// can be.
+template <uint32_t FRAMES>
 __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ xyz, Plan P, double min_leaf_side,
                                                      uint32_t nparts) {
+    constexpr bool one = FRAMES == 1, fc_lds = FRAMES == FC_LDS;
     __shared__ FrameConst s_fc;
+    __shared__ FrameConst s_fcs[fc_lds ? FC_LDS : 1];
     __shared__ FrameStat s_stat;
+    if (fc_lds && threadIdx.x < P.nf) {
+        frame_consts(P.fstat + threadIdx.x, min_leaf_side, s_fcs + threadIdx.x);
+        if (blockIdx.x == 0) P.fc[threadIdx.x] = s_fcs[threadIdx.x];
+    }
     __shared__ uint32_t s_hist[SORT_PASSES_MAX][256];
-    const uint32_t n = P.n, nf = P.nf, nh = P.sort_passes;
+    const uint32_t n = P.n, nh = P.sort_passes;
     for (uint32_t i = threadIdx.x; i < nh * 256u; i += blockDim.x) (&s_hist[0][0])[i] = 0u;
-    if (nf == 1 && nparts > 0 && threadIdx.x < 64u) {
+    if (one && nparts > 0 && threadIdx.x < 64u) {
         const uint32_t lane = threadIdx.x;
         uint32_t v[7] = {0u, 0u, 0u, 0u, 0u, 0u, 0u};
         for (uint32_t c = lane; c < nparts; c += 64u) {
@@ -332,7 +352,7 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
                 if (v[6]) atomicOr(&P.ctr->status, DEV_NONFINITE);
             }
         }
-    } else if (nf == 1 && threadIdx.x == 0) {
+    } else if (one && threadIdx.x == 0) {
         frame_consts(P.fstat, min_leaf_side, &s_fc);
         if (blockIdx.x == 0) *P.fc = s_fc;
     }
@@ -352,13 +372,19 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
             x[u] = xyz[3 * (size_t)j];
             y[u] = xyz[3 * (size_t)j + 1];
             z[u] = xyz[3 * (size_t)j + 2];
-            f[u] = nf > 1 ? P.fid[j] : 0u;
+            f[u] = one ? 0u : P.fid[j];
         }
         float l0[MORTON_U], l1[MORTON_U], l2[MORTON_U];
         double sc[MORTON_U];
 #pragma unroll
         for (int u = 0; u < MORTON_U; ++u) {
-            if (nf > 1) {
+            if (fc_lds) {
+                const FrameConst& fc = s_fcs[f[u]];
+                l0[u] = fc.lo[0];
+                l1[u] = fc.lo[1];
+                l2[u] = fc.lo[2];
+                sc[u] = fc.scale;
+            } else if (!one) {
                 const FrameConst& fc = P.fc[f[u]];
                 l0[u] = fc.lo[0];
                 l1[u] = fc.lo[1];
@@ -400,11 +426,12 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
 }
 
 void launch_morton(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
-    if (P.nf > 1) hipLaunchKernelGGL(frame_const_kernel, dim3(1), dim3(256), 0, st, P, prm.min_leaf_side);
+    if (P.nf > FC_LDS) hipLaunchKernelGGL(frame_const_kernel, dim3(1), dim3(256), 0, st, P, prm.min_leaf_side);
     unsigned blocks = (P.n + 2047) / 2048;
     if (blocks > 512) blocks = 512;
     const uint32_t nparts = bbox_one_frame(P) ? bbox_blocks(P) : 0u;
-    hipLaunchKernelGGL(morton_kernel, dim3(blocks), dim3(256), 0, st, xyz, P, prm.min_leaf_side, nparts);
+    auto kern = P.nf == 1 ? morton_kernel<1> : P.nf <= FC_LDS ? morton_kernel<FC_LDS> : morton_kernel<MAX_FRAMES>;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, st, xyz, P, prm.min_leaf_side, nparts);
 }
 
 // ---------------------------------------------------------------- radix sort

@@ -9,8 +9,7 @@ namespace gdn {
 
 // frame.hip: zero-fill, frame table, frame bboxes, Morton keys, radix sort (and
 // the re-sort of deep level-10 cells)
-void launch_zero(const Plan& P, hipStream_t st);
-void launch_frames(const Plan& P, const int64_t* frame_off, hipStream_t st);
+void launch_zero(const Plan& P, const int64_t* frame_off, hipStream_t st);
 // A single frame of up to 2^20 points: one box kernel that can also clear
 // the zeroed block (clear: the fill launch is skipped).
 bool bbox_one_frame(const Plan& P);

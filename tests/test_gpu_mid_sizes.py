@@ -177,3 +177,34 @@ def test_skipped_launches(oracle, one_point, cap, chunk):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("nf", [1, 2, 64, 65, 300])
+def test_frame_counts(nf):
+    """Batches at the edges of the key kernel's frame counts, with empty frames,
+    against the plain call of each frame."""
+    import torch
+    from paper_2512_10386_amd.binding import BatchDenoiser, Denoiser
+    rng = np.random.default_rng(nf)
+    sizes = rng.integers(0, 300, nf)
+    sizes[-1] = 5000
+    frames = [(rng.normal(size=(m, 3)) * rng.uniform(0.1, 9)).astype(np.float32) for m in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    x = torch.from_numpy(np.concatenate(frames)).cuda()
+    prm = dict(k=8, leaf_cap=64, min_vox_count=2)
+    bd, den = BatchDenoiser(0, **prm), Denoiser(0, **prm)
+    try:
+        out = bd.alloc(len(x), nf)
+        bd(x, torch.tensor(off, dtype=torch.int64, device="cuda"), out)
+        assert int(bd.dump("STATUS", len(x)).cpu().numpy()[0]) == 0
+        for f in range(nf):
+            if not sizes[f]:
+                assert int(out.n_kept[f]) == 0
+                continue
+            r = den(x[off[f]:off[f + 1]].contiguous())
+            assert torch.equal(out.keep[off[f]:off[f + 1]], r.keep)
+            assert torch.equal(out.score[off[f]:off[f + 1]].view(torch.int32), r.score.view(torch.int32))
+            assert int(out.n_kept[f]) == int(r.n_kept)
+    finally:
+        bd.close()
+        den.close()
