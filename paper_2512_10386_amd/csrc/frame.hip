@@ -2,6 +2,8 @@
 // bounding box (the octree root cube, Sec. 3 with Eq. 2), 63-bit Morton keys,
 // the stable LSD radix sort of (key, original index) on the digits the octree
 // needs, and the whole-key re-sort of deep level-10 cells.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "radix.hpp"
 #include "tree.hpp"
@@ -303,9 +305,9 @@ __global__ __launch_bounds__(256) void frame_const_kernel(Plan P, double min_lea
     for (uint32_t f = threadIdx.x; f < P.nf; f += blockDim.x) frame_consts(P.fstat + f, min_leaf_side, P.fc + f);
 }
 
-// Keys (quantised with the point's own frame constants), the identity
-// payload and the digit histograms of the sort: key digits 4..7, then the
-// frame id digits of a batch. A single frame computes its constants per block.
+// Keys (quantised with the point's own frame constants) and the digit
+// histograms of the sort: key digits 4..7, then the frame id digits of a batch
+// (from the frame table). A single frame computes its constants per block.
 constexpr uint32_t MORTON_U = 8;
 // nparts > 0: a single frame whose box is in nparts per-block records of
 // bbox_one_kernel, folded here by every block (block 0 also stores the
@@ -325,6 +327,24 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
     }
     __shared__ uint32_t s_hist[SORT_PASSES_MAX][256];
     const uint32_t n = P.n, nh = P.sort_passes;
+    // MORTON_U points per thread at a time, their loads issued before any is
+    // used (a point past n reads the last one and is dropped), the first ones
+    // beside the fold of the boxes
+    const uint32_t stride = gridDim.x * blockDim.x;
+    uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x;
+    float x[MORTON_U], y[MORTON_U], z[MORTON_U];
+    uint32_t f[MORTON_U];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < MORTON_U; ++u) {
+            const uint32_t j = min(i0 + (uint32_t)u * stride, n - 1u);
+            x[u] = xyz[3 * (size_t)j];
+            y[u] = xyz[3 * (size_t)j + 1];
+            z[u] = xyz[3 * (size_t)j + 2];
+            f[u] = one ? 0u : P.fid[j];
+        }
+    };
+    load();
     for (uint32_t i = threadIdx.x; i < nh * 256u; i += blockDim.x) (&s_hist[0][0])[i] = 0u;
     if (one && nparts > 0 && threadIdx.x < 64u) {
         const uint32_t lane = threadIdx.x;
@@ -357,23 +377,15 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
         if (blockIdx.x == 0) *P.fc = s_fc;
     }
     __syncthreads();
-    // MORTON_U points per thread at a time, their loads (and a batch's frame
-    // constants) issued before any is used (a point past n reads the last
-    // one and is dropped)
-    const uint32_t stride = gridDim.x * blockDim.x;
+    if (!one && blockIdx.x == 0)  // a frame's points all count to its own digits
+        for (uint32_t g = threadIdx.x; g < P.nf; g += blockDim.x) {
+            const uint32_t m = P.foff[g + 1] - P.foff[g];
+            for (uint32_t p = SORT_PASSES; m != 0u && p < nh; ++p)
+                atomicAdd(&P.sort_hist[256u * p + ((g >> (8 * (p - SORT_PASSES))) & 255u)], m);
+        }
     const float c0 = s_fc.lo[0], c1 = s_fc.lo[1], c2 = s_fc.lo[2];
     const double csc = s_fc.scale;
-    for (uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += MORTON_U * stride) {
-        float x[MORTON_U], y[MORTON_U], z[MORTON_U];
-        uint32_t f[MORTON_U];
-#pragma unroll
-        for (int u = 0; u < MORTON_U; ++u) {
-            const uint32_t j = min(i0 + (uint32_t)u * stride, n - 1u);
-            x[u] = xyz[3 * (size_t)j];
-            y[u] = xyz[3 * (size_t)j + 1];
-            z[u] = xyz[3 * (size_t)j + 2];
-            f[u] = one ? 0u : P.fid[j];
-        }
+    while (i0 < n) {
         float l0[MORTON_U], l1[MORTON_U], l2[MORTON_U];
         double sc[MORTON_U];
 #pragma unroll
@@ -410,13 +422,12 @@ __global__ __launch_bounds__(256) void morton_kernel(const float* __restrict__ x
             const uint32_t qz = quantise(z[u], l2[u], sc[u]);
             const uint64_t key = morton3(qx, qy, qz);
             P.keys_src[i] = key;
-            P.idx_src[i] = i;
 #pragma unroll
             for (int p = SORT_SHORT_FIRST; p < SORT_PASSES; ++p)
                 atomicAdd(&s_hist[p][(key >> (8 * p)) & 255u], 1u);
-            for (uint32_t p = SORT_PASSES; p < nh; ++p)
-                atomicAdd(&s_hist[p][(f[u] >> (8 * (p - SORT_PASSES))) & 255u], 1u);
         }
+        i0 += MORTON_U * stride;
+        if (i0 < n) load();
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < nh * 256u; i += blockDim.x) {
@@ -456,7 +467,8 @@ struct FrameDigit {
     }
 };
 
-template <int ITEMS, int BLOCK>
+// FIRST: the payload is the position itself.
+template <int ITEMS, int BLOCK, bool FIRST>
 __global__ __launch_bounds__(BLOCK) void radix_pass_kernel(const uint64_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
                                                                 uint64_t* __restrict__ kout,
@@ -470,7 +482,7 @@ __global__ __launch_bounds__(BLOCK) void radix_pass_kernel(const uint64_t* __res
     const bool foff_lds = pass >= SORT_PASSES && nf < SORT_FOFF_LDS;
     if (foff_lds)
         for (uint32_t i = threadIdx.x; i <= nf; i += BLOCK) s_foff[i] = foff[i];
-    radix_tile<ITEMS, false, BLOCK>(kin, vin, kout, vout, n, blockIdx.x, hist, status, dev_status, DEV_WAIT_LIMIT,
+    radix_tile<ITEMS, FIRST, BLOCK>(kin, vin, kout, vout, n, blockIdx.x, hist, status, dev_status, DEV_WAIT_LIMIT,
                              FrameDigit{pass, foff, s_foff, foff_lds, nf});
 }
 
@@ -794,10 +806,14 @@ void launch_sort(const Plan& P, const Params& prm, hipStream_t st) {
     uint32_t* vout = P.idx_src == P.idx_a ? P.idx_b : P.idx_a;
     for (uint32_t pass = SORT_SHORT_FIRST; pass < P.sort_passes; ++pass) {
         // small inputs: many small tiles (latency); large: fewer, fuller tiles
-        auto kern = P.sort_tile == 512u    ? radix_pass_kernel<2, 256>
-                    : P.sort_tile == 1024u ? radix_pass_kernel<4, 256>
-                    : P.sort_tile == 2048u ? radix_pass_kernel<4, 512>
-                                           : radix_pass_kernel<8, 512>;
+        auto pick = [&](auto first) {
+            constexpr bool F = decltype(first)::value;
+            return P.sort_tile == 512u    ? radix_pass_kernel<2, 256, F>
+                   : P.sort_tile == 1024u ? radix_pass_kernel<4, 256, F>
+                   : P.sort_tile == 2048u ? radix_pass_kernel<4, 512, F>
+                                          : radix_pass_kernel<8, 512, F>;
+        };
+        auto kern = pass == SORT_SHORT_FIRST ? pick(std::true_type{}) : pick(std::false_type{});
         hipLaunchKernelGGL(kern, dim3(P.sort_tiles), dim3(P.sort_tile <= 1024u ? 256 : 512), 0, st, kin, vin, kout, vout,
                            P.n, (int)pass, P.sort_hist + 256 * pass,
                            P.sort_status + (size_t)(pass - SORT_SHORT_FIRST) * P.sort_tiles * 256, &P.ctr->status,
