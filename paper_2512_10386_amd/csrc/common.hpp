@@ -43,10 +43,18 @@ constexpr uint32_t PLAN_CLASS_MAX_N = 1u << 21;
 static_assert(2ull * PLAN_CLASS_MAX_N + 64 < 1ull << PLAN_CLASS_SHIFT, "a place fits below the class");
 constexpr uint32_t PLAN_ONE_MAX_N = 1u << 19;  // kNN plan: one workgroup up to this size, parallel above
 constexpr int PLAN_LEVELS = 8;                // candidate chunk lengths chunk0 << 0..7 (parallel plan)
+// Default initial candidate chunk: in effect none (lengths double up to 2^30
+// from here). A query tests few of a leaf's culling groups, so a split walks
+// the group boxes sooner at the price of a partial list per chunk, their merge
+// and a weaker bound in each. Whole calls with chunks of 8192 / 32768 / none:
+// 120k sweep at cap 1024 309 / 288 / 276 us, 250k 446 / 423 / 416, 100k at cap
+// 4096 442 / 392 / 338, 300k in one leaf - / 3647 / 3252, 20k objects 138 / 135
+// / 135. Up to this size the merge and the plan's check are not launched.
+constexpr int KNN_CC0 = 1 << 23;
+static_assert((long long)KNN_CC0 << (PLAN_LEVELS - 1) <= 1ll << 30, "the candidate chunk lengths are 32-bit");
 constexpr int KNN_TQ = 16;                    // queries per kNN work item (one wave), at most
 constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^19 points (shorter items, shorter tail)
 constexpr uint32_t KNN_TQ_SMALL_MAX_N = 1u << 19;
-constexpr int KNN_CC0 = 32768;                // default initial candidate chunk
 constexpr int KNN_NCH_MAX = 32;               // max candidate chunks per leaf
 constexpr int KNN_GRP = 64;                   // P1 positions per culling group of the kNN (one per lane)
 constexpr uint32_t KNN_STREAMS = 64;          // kNN work-queue streams (cursors)
