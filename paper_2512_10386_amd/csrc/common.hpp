@@ -162,6 +162,17 @@ __host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1, uint32_t most)
     return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 40960u ? 4u : most;
 }
 
+// Queries per kNN item of a leaf in counter q of the plan (1: chunked, 2 .. the
+// classes). A leaf of the first class has 128 candidates and more per query:
+// few isolated points, whose far neighbours make a query test many groups. As
+// items of several such queries they set the run of a small input; alone they
+// spread over the chip: 200k points at caps 512 / 1024 232 / 301 us a call with
+// whole items, 219 / 243 so. Above 2^18 points there is enough other work to
+// fill in (1.2M 1016 and 1022 us, 400k at cap 4096 860 and 872).
+__host__ __device__ inline uint32_t knn_leaf_tile(uint32_t q, uint32_t tq, uint32_t n) {
+    return q == 2u && n <= (1u << 18) ? 1u : tq;
+}
+
 // Inputs whose halo kernel plans the kNN items as it goes, each workgroup (8
 // leaves) by additions to six counters that all share, at some 10 ns each.
 // The plan kernel, one workgroup of 1024 leaves a round, takes 8 us for few

@@ -242,17 +242,18 @@ __global__ __launch_bounds__(BOUND_Q * BOUND_SPLIT) void knn_bound_kernel(Plan P
         const float b = query_bound(StagedPts{s_pts, lo}, rb, re, qi, k, sub, live);
         if (live && sub == 0u) {
             P.tau_c[qi] = b;
-            if ((qi - qb) % tq == 0u) {
-                const uint32_t nch = P.leaf_nch[t];
-                uint32_t first = P.leaf_item[t];
-                if (classes) {
-                    const uint32_t q = first >> PLAN_CLASS_SHIFT;
-                    first &= (1u << PLAN_CLASS_SHIFT) - 1u;
+            uint32_t first = P.leaf_item[t], tl = tq;
+            if (classes) {
+                const uint32_t q = first >> PLAN_CLASS_SHIFT;
+                first &= (1u << PLAN_CLASS_SHIFT) - 1u;
 #pragma unroll
-                    for (int i = 2; i < PLAN_COUNTERS; ++i) first += (uint32_t)i == q ? cls[i] : 0u;
-                }
-                first += ((qi - qb) / tq) * nch;
-                const uint32_t q1 = min(qe, qi + tq);
+                for (int i = 2; i < PLAN_COUNTERS; ++i) first += (uint32_t)i == q ? cls[i] : 0u;
+                tl = knn_leaf_tile(q, tq, P.n);
+            }
+            if ((qi - qb) % tl == 0u) {
+                const uint32_t nch = P.leaf_nch[t];
+                first += ((qi - qb) / tl) * nch;
+                const uint32_t q1 = min(qe, qi + tl);
                 for (uint32_t c = 0; c < nch; ++c) P.items[first + c] = KnnItem{t, qi, q1, c};
             }
         }

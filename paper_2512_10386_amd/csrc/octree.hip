@@ -527,7 +527,8 @@ __global__ __launch_bounds__(256) void halo_kernel(Plan P, uint32_t cap, uint32_
                 const uint32_t n1 = live ? s_r[grp][13].y - s_r[grp][13].x : 0u;
                 nch = plan_nch(n1, len, chunk0);
                 q = nch > 1u ? 1u : 2u + plan_class(n1, len);
-                const uint32_t items = (n1 + tq - 1u) / tq * nch;
+                const uint32_t tl = knn_leaf_tile(q, tq, P.n);
+                const uint32_t items = (n1 + tl - 1u) / tl * nch;
                 s_cnt[0][grp] = nch > 1u ? n1 * nch : 0u;
                 for (uint32_t i = 1; i < (uint32_t)PLAN_COUNTERS; ++i) s_cnt[i][grp] = i == q ? items : 0u;
                 s_pairs[grp] = n1 ? (unsigned long long)n1 * (len - 1u) : 0ull;

@@ -26,3 +26,23 @@ def test_tile_sizes(oracle, n, k, cap, chunk):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("n", [50_000, 262_144, 262_145])
+def test_isolated_leaves(oracle, n):
+    """Leaves of a few points beside dense ones (128 candidates and more per
+    query): their queries are items of their own up to 2^18 points."""
+    import numpy as np
+    from paper_2512_10386_amd.binding import Denoiser
+    rng = np.random.default_rng(n)
+    m = n // 2000
+    lone = rng.uniform(-1, 2, (m, 1, 3)) + rng.normal(0, 0.02, (m, 7, 3))
+    dense = rng.uniform(0, 1, (n - 7 * m, 3)) * (1, 1, 0.02)
+    xyz = np.concatenate([dense, lone.reshape(-1, 3)])[rng.permutation(n)].astype(np.float32)
+    prm = dict(k=12, leaf_cap=1024, stages=6)
+    ref = oracle.denoise(xyz, **prm)
+    den = Denoiser(0, **prm)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
