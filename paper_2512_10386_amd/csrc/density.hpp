@@ -96,14 +96,19 @@ __device__ __forceinline__ unsigned long long score_key(bool p2, double f) {
     if (isnan(f)) return 1ull;
     return (unsigned long long)__double_as_longlong(f) + 2ull;
 }
-// Optional outputs (up to 2^20 points): keep, score and stage in input order
-// for every point of each leaf, as outputs_kernel writes them, so that pass is
-// not needed.
+// Outputs in input order for every point of each leaf: keep, score and stage
+// as outputs_kernel writes them, or (rec) packed records as outputs_pack_kernel
+// does, so that those passes are not needed.
 struct ToplOut {
+    uint2* rec;
     uint8_t* keep;
     float* score;
     uint8_t* stage;
     __device__ void put(uint32_t i, uint8_t st, double sc) const {
+        if (rec) {
+            rec[i] = make_uint2(__float_as_uint(st >= 2 ? (float)sc : -1.0f), st);
+            return;
+        }
         keep[i] = st == 3;
         score[i] = st >= 2 ? (float)sc : -1.0f;
         if (stage) stage[i] = st;

@@ -684,7 +684,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
         // the P1 reads below, and written once those are in
         constexpr int NU = 4;
         const uint32_t nt = le - lb;
-        const bool outs_b = out.keep && nt <= (uint32_t)NU * SEL_BLOCK;
+        const bool outs_b = nt <= (uint32_t)NU * SEL_BLOCK;
         uint32_t f1[NU], oi[NU];
         if (outs_b) {
 #pragma unroll
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
 #pragma unroll
                 for (int u = 0; u < NU; ++u)
                     if (threadIdx.x + (uint32_t)u * SEL_BLOCK < nt && !f1[u]) out.put(oi[u], 0, 0.0);
-            } else if (out.keep) {
+            } else {
                 for (uint32_t s = lb + threadIdx.x; s < le; s += SEL_BLOCK)
                     if (!P.p1[s]) out.put(P.idx_a[s], 0, 0.0);
             }
@@ -762,7 +762,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
                     st = kept ? 3 : 2;
                 }
                 P.stage_c[qb + i] = st;
-                if (out.keep) out.put(ix[u], st, sv[u]);
+                out.put(ix[u], st, sv[u]);
             }
             __syncthreads();
             continue;
@@ -804,7 +804,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
                 st = kept ? 3 : 2;
             }
             P.stage_c[qi] = st;
-            if (out.keep) out.put(__float_as_uint(P.cand4[qi].w), st, st >= 2 ? P.score_c[qi] : 0.0);
+            out.put(__float_as_uint(P.cand4[qi].w), st, st >= 2 ? P.score_c[qi] : 0.0);
         }
         __syncthreads();
     }
@@ -814,29 +814,28 @@ __global__ __launch_bounds__(SEL_BLOCK) void topl_kernel(Plan P, double lambda, 
 
 // Small leaves: theta = the m-th largest key from a wave sort; keys above it
 // are kept, and among the keys equal to it the `need` smallest indices.
-// OUT: the outputs are written here too, those of the points outside P1 among
-// them (their flags and indices are read beside the P1 reads).
-template <bool OUT>
+// The outputs are written here too, those of the points outside P1 among them
+// (their flags and indices are read beside the P1 reads). Each XCD takes one
+// eighth of the leaves, so that the records of a frame are written whole in
+// one XCD's L2.
 __global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda, ToplOut out) {
     __shared__ uint32_t s_hist[4][256];
     uint32_t* const hist = s_hist[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wid = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t nl = P.ctr->n_leaves;
-    for (uint32_t t = wid; t < nl; t += nw) {
+    const uint32_t nl = P.ctr->n_leaves, per = (nl + N_XCD - 1u) / N_XCD, first = (blockIdx.x % N_XCD) * per;
+    const uint32_t last = min(nl, first + per), nw = (gridDim.x / N_XCD) * 4u;
+    for (uint32_t t = first + (blockIdx.x / N_XCD) * 4u + (threadIdx.x >> 6); t < last; t += nw) {
         const uint32_t lb = P.leaf_begin[t], le = P.leaf_begin[t + 1];
         const uint32_t qb = P.p1pos[lb], qe = P.p1pos[le];
         const uint32_t n1 = qe - qb;
         if (n1 > SMALL_LEAF) continue;
         const uint32_t nt = le - lb;
         uint32_t f1[4], of[4];
-        if constexpr (OUT) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t s = lb + min((uint32_t)j * 64u + lane, nt - 1u);
-                f1[j] = P.p1[s];
-                of[j] = P.idx_a[s];
-            }
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t s = lb + min((uint32_t)j * 64u + lane, nt - 1u);
+            f1[j] = P.p1[s];
+            of[j] = P.idx_a[s];
         }
         WaveVals kv;
         uint32_t oi[4];
@@ -912,16 +911,14 @@ __global__ __launch_bounds__(256) void topl_small_kernel(Plan P, double lambda, 
             if (i < n1) {
                 const uint8_t st = p2v[j] ? (kept ? 3 : 2) : 1;
                 P.stage_c[qb + i] = st;
-                if constexpr (OUT) out.put(ixv[j], st, sv[j]);
+                out.put(ixv[j], st, sv[j]);
             }
         }
-        if constexpr (OUT) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if ((uint32_t)j * 64u + lane < nt && !f1[j]) out.put(of[j], 0, 0.0);
-            for (uint32_t s = lb + 256u + lane; s < le; s += 64u)
-                if (!P.p1[s]) out.put(P.idx_a[s], 0, 0.0);
-        }
+        for (int j = 0; j < 4; ++j)
+            if ((uint32_t)j * 64u + lane < nt && !f1[j]) out.put(of[j], 0, 0.0);
+        for (uint32_t s = lb + 256u + lane; s < le; s += 64u)
+            if (!P.p1[s]) out.put(P.idx_a[s], 0, 0.0);
     }
 }
 
@@ -957,10 +954,9 @@ bool launch_topl(const Plan& P, const Params& prm, uint8_t* keep, float* score, 
         return false;
     }
     const bool small = small_leaf_path(P.n, prm.leaf_cap);
-    // up to 2^20 points the top-lambda kernels write the outputs too (larger
-    // inputs scatter them as packed records)
-    const bool write = P.n <= PACKED_OUT_MIN_N;
-    const ToplOut out{write ? keep : nullptr, score, stage};
+    // the top-lambda kernels write the outputs too (large inputs' as packed
+    // records, which the keep scan turns into the three arrays)
+    const ToplOut out{P.n > PACKED_OUT_MIN_N ? P.outrec : nullptr, keep, score, stage};
     if (P.big_leaves) {  // (up to 2^20 points)
         launch_big_topl(P, prm.keep_ratio, out, st);
         return true;
@@ -968,13 +964,12 @@ bool launch_topl(const Plan& P, const Params& prm, uint8_t* keep, float* score, 
     if (small) {
         unsigned wb = (P.n / 128 + 3) / 4;
         if (wb > 8192) wb = 8192;
-        hipLaunchKernelGGL(write ? topl_small_kernel<true> : topl_small_kernel<false>, dim3(wb), dim3(256), 0, st, P,
-                           prm.keep_ratio, out);
+        hipLaunchKernelGGL(topl_small_kernel, dim3(xcd_grid(wb)), dim3(256), 0, st, P, prm.keep_ratio, out);
     }
     unsigned blocks = P.n < 2048 ? P.n : 2048;
     if (blocks == 0) blocks = 1;
     hipLaunchKernelGGL(topl_kernel, dim3(blocks), dim3(SEL_BLOCK), 0, st, P, prm.keep_ratio, small, out);
-    return write;
+    return true;
 }
 
 // ---------------------------------------------------------------- outputs
@@ -1089,7 +1084,7 @@ void launch_outputs(const Plan& P, uint8_t* keep, float* score, uint8_t* stage, 
     if (blocks > 4096) blocks = 4096;
     uint32_t* const sstat = P.scan_status + 2 * (size_t)P.scan_tiles;
     if (P.n > PACKED_OUT_MIN_N) {
-        hipLaunchKernelGGL(outputs_pack_kernel, dim3(xcd_grid(blocks)), dim3(256), 0, st, P);
+        if (!written) hipLaunchKernelGGL(outputs_pack_kernel, dim3(xcd_grid(blocks)), dim3(256), 0, st, P);
         const PackedKeepGet get{P.outrec, keep, score, stage};
         if (P.nf == 1)
             launch_scan(get, KeepEmit{kept_idx}, KeepFin{P.ctr, n_kept}, nullptr, P.n, sstat, &P.ctr->status, st);
