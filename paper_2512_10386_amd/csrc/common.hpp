@@ -153,13 +153,14 @@ inline bool big_leaf_path(uint32_t n, int32_t leaf_cap) {
 
 // Queries per kNN work item of inputs with n1 P1 points. A wave takes an
 // item's queries in turn, so few points make short items to fill the chip's
-// 4096 waves, and many points long ones, which share the walk over the leaf's
-// groups. Whole calls with 8 / 4 / 2 / 1 queries: 914 points 131 / 120 / 115 /
-// 112 us; 12.2k 180 / 161 / 157 / 164; 35.6k 309 / 272 / 264 / 291; 52k 248 /
-// 245 / 258 / 297; 96k 307 / 313 / 353 / 442.
+// waves, and many points long ones, which share the walk over the leaf's
+// groups. Whole calls with 8 / 4 / 2 / 1 queries (and four waves per SIMD): 914
+// points 131 / 120 / 115 / 112 us; 12.2k 180 / 161 / 157 / 164; 35.6k 309 / 272
+// / 264 / 291; 52k 248 / 245 / 258 / 297; 96k 307 / 313 / 353 / 442. With five
+// waves 52k take 222 / 217, 96k 268.4 / 268.7.
 __host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1, uint32_t most) {
     if (most > (uint32_t)KNN_TQ_SMALL) return most;  // large inputs
-    return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 40960u ? 4u : most;
+    return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 65536u ? 4u : most;
 }
 
 // Queries per kNN item of a leaf in counter q of the plan (1: chunked, 2 .. the

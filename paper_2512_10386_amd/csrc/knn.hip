@@ -606,16 +606,18 @@ __device__ __forceinline__ void flush_half(unsigned long long* __restrict__ lst0
 // same fp32 operations as dist2: a query skips a group whose box distance
 // exceeds its bound, so the group holds no candidate with d2 <= that bound.
 // Lane u then holds group u's mask of the queries that need it; a group is
-// loaded only if some query needs it, four at a time (with PREFETCH the next
-// four are fetched while these are evaluated). Positions of a group outside
+// loaded only if some query needs it, four at a time. Positions of a group outside
 // the range's part in this chunk are not candidates: they get NaN coordinates
 // (d2 <= bound never holds). Groups of the range holding the tile come first,
 // from the tile's group outwards, then the other ranges in order.
-// PREFETCH (single frames): the extra registers drop the kernel to 4 waves
-// per SIMD, which is what their grid launches anyway; large inputs run 5
-// waves per SIMD and lose more to the lower occupancy than they gain.
-template <bool POS, int Q, bool PREFETCH = !POS>
-__global__ __launch_bounds__(64, POS ? 5 : 4) void knn_group_kernel(Plan P, const float4* __restrict__ cand4, int kk) {
+// WAVES per SIMD: what its registers must fit, and what the grid launches. An
+// item is a chain of loads, box tests, sorts and merges, which other waves
+// cover better than more registers do: four waves that fetched the next groups
+// while these were evaluated took 277 us a call for a 120k sweep, 224 for a
+// batch of 12 objects and 660 for 500k points; five without 268, 217 and 623,
+// and with the loads at the top of the loop 264, 213 and (six) 592.
+template <bool POS, int Q, int WAVES>
+__global__ __launch_bounds__(64, WAVES) void knn_group_kernel(Plan P, const float4* __restrict__ cand4, int kk) {
     using PT = typename Pending<POS>::T;
     static_assert(Q <= 32, "tile shape (a query mask per group fits 32 bits)");
     extern __shared__ unsigned long long s_dyn[];
@@ -782,17 +784,10 @@ __global__ __launch_bounds__(64, POS ? 5 : 4) void knn_group_kernel(Plan P, cons
                     }
                 }
             };
-            float4 c[KNN_NB];
-            uint32_t gb[KNN_NB], mk[KNN_NB];
-            load_batch(0u, c, gb, mk);
             for (uint32_t i0 = 0; i0 < nn; i0 += (uint32_t)KNN_NB) {
-                // PREFETCH: the next batch's candidates are loaded while this
-                // one is evaluated (a long item needs many batches in turn)
-                float4 cn[KNN_NB];
-                uint32_t gbn[KNN_NB], mkn[KNN_NB];
-                if constexpr (PREFETCH) {
-                    if (i0 + (uint32_t)KNN_NB < nn) load_batch(i0 + (uint32_t)KNN_NB, cn, gbn, mkn);
-                }
+                float4 c[KNN_NB];
+                uint32_t gb[KNN_NB], mk[KNN_NB];
+                load_batch(i0, c, gb, mk);
                 uint32_t qany = 0;
 #pragma unroll
                 for (int b = 0; b < KNN_NB; ++b) qany |= mk[b];
@@ -894,18 +889,6 @@ __global__ __launch_bounds__(64, POS ? 5 : 4) void knn_group_kernel(Plan P, cons
                         if (mj) merged |= 1ull << j;
                     }
                     if (lane == j) pcnt = cnt;
-                }
-                if (i0 + (uint32_t)KNN_NB < nn) {
-                    if constexpr (PREFETCH) {
-#pragma unroll
-                        for (int b = 0; b < KNN_NB; ++b) {
-                            c[b] = cn[b];
-                            gb[b] = gbn[b];
-                            mk[b] = mkn[b];
-                        }
-                    } else {
-                        load_batch(i0 + (uint32_t)KNN_NB, c, gb, mk);
-                    }
                 }
             }
         }
@@ -1137,21 +1120,25 @@ size_t knn_lds_bytes(uint32_t q, int k, bool pos) {
 }
 
 void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st) {
-    const unsigned blocks = (unsigned)(num_cus > 0 ? num_cus : 256) * (P.n > KNN_POS_MIN_N ? 20u : 16u);
     // Large inputs run long enough for occupancy to pay (positions); a smaller
     // input's run is set by its longest items, where a gather per merge costs
     // more (keys). Whole calls, keys against positions: 250k points 368 and
     // 390 us, 500k 608 and 616, 1M 1193 and 1131, 900k in nine frames 1013 and
     // 992.
+    // Six waves per SIMD cost some spilled registers: 500k points 623 us with
+    // five and 601 with six, 250k 299.3 and 294.7, but eight frames of 20k 284
+    // and 287.5.
+    constexpr uint32_t KNN_SIX_WAVES_MIN_N = 3u << 16;
     // The plan's tile size goes with the pending-buffer kind: tiles of
     // KNN_TQ_SMALL queries exactly for the inputs that keep keys.
     static_assert(KNN_TQ_SMALL_MAX_N == KNN_POS_MIN_N, "tile size and buffer kind switch together");
-    if (P.n > KNN_POS_MIN_N)
-        hipLaunchKernelGGL((knn_group_kernel<true, KNN_TQ>), dim3(blocks), dim3(64), knn_lds_bytes(KNN_TQ, k, true),
-                           st, P, (const float4*)P.cand4, k);
-    else
-        hipLaunchKernelGGL((knn_group_kernel<false, KNN_TQ_SMALL>), dim3(blocks), dim3(64),
-                           knn_lds_bytes(KNN_TQ_SMALL, k, false), st, P, (const float4*)P.cand4, k);
+    auto launch = [&](auto kern, int tq, bool pos, unsigned waves) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(num_cus > 0 ? num_cus : 256) * 4u * waves), dim3(64),
+                           knn_lds_bytes((uint32_t)tq, k, pos), st, P, (const float4*)P.cand4, k);
+    };
+    if (P.n > KNN_POS_MIN_N) launch(knn_group_kernel<true, KNN_TQ, 5>, KNN_TQ, true, 5u);
+    else if (P.n > KNN_SIX_WAVES_MIN_N) launch(knn_group_kernel<false, KNN_TQ_SMALL, 6>, KNN_TQ_SMALL, false, 6u);
+    else launch(knn_group_kernel<false, KNN_TQ_SMALL, 5>, KNN_TQ_SMALL, false, 5u);
 }
 
 void launch_knn_merge(const Plan& P, const Params& prm, int num_cus, hipStream_t st) {

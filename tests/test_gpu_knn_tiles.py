@@ -46,3 +46,17 @@ def test_isolated_leaves(oracle, n):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("n,k", [(65_536, 16), (65_537, 16), (196_608, 32), (196_609, 32), (196_609, 64)])
+def test_waves_per_simd(oracle, n, k):
+    """The edges of the four-query tiles and of the kernel for six waves."""
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz, _ = synth.uniform_cube(n, n)
+    prm = dict(k=k, leaf_cap=512, stages=6)
+    ref = oracle.denoise(xyz, **prm)
+    den = Denoiser(0, **prm)
+    try:
+        compare(run_gpu(den, xyz), ref)
+    finally:
+        den.close()
