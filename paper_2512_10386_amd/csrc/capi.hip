@@ -86,7 +86,6 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     P.nf = nf;
     P.sort_passes = SORT_PASSES + (nf > 256u ? 2u : (nf > 1u ? 1u : 0u));
     P.sort_tile = sort_tile_for(n);
-    P.tq_max = n > KNN_TQ_SMALL_MAX_N ? (uint32_t)KNN_TQ : (uint32_t)KNN_TQ_SMALL;
     P.sort_tiles = (uint32_t)((N + P.sort_tile - 1) / P.sort_tile);
     if (P.sort_tiles == 0) P.sort_tiles = 1;
     P.scan_tiles = scan_tiles_for(n);

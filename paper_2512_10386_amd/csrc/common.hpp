@@ -52,9 +52,7 @@ constexpr int PLAN_LEVELS = 8;                // candidate chunk lengths chunk0 
 // / 135. Up to this size the merge and the plan's check are not launched.
 constexpr int KNN_CC0 = 1 << 23;
 static_assert((long long)KNN_CC0 << (PLAN_LEVELS - 1) <= 1ll << 30, "the candidate chunk lengths are 32-bit");
-constexpr int KNN_TQ = 16;                    // queries per kNN work item (one wave), at most
-constexpr int KNN_TQ_SMALL = 8;               // ... for inputs of up to 2^19 points (shorter items, shorter tail)
-constexpr uint32_t KNN_TQ_SMALL_MAX_N = 1u << 19;
+constexpr int KNN_TQ = 8;                     // queries per kNN work item (one wave), at most
 constexpr int KNN_NCH_MAX = 32;               // max candidate chunks per leaf
 constexpr int KNN_GRP = 64;                   // P1 positions per culling group of the kNN (one per lane)
 constexpr uint32_t KNN_STREAMS = 64;          // kNN work-queue streams (cursors)
@@ -157,10 +155,11 @@ inline bool big_leaf_path(uint32_t n, int32_t leaf_cap) {
 // groups. Whole calls with 8 / 4 / 2 / 1 queries (and four waves per SIMD): 914
 // points 131 / 120 / 115 / 112 us; 12.2k 180 / 161 / 157 / 164; 35.6k 309 / 272
 // / 264 / 291; 52k 248 / 245 / 258 / 297; 96k 307 / 313 / 353 / 442. With five
-// waves 52k take 222 / 217, 96k 268.4 / 268.7.
-__host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1, uint32_t most) {
-    if (most > (uint32_t)KNN_TQ_SMALL) return most;  // large inputs
-    return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 65536u ? 4u : most;
+// waves 52k take 222 / 217, 96k 268.4 / 268.7. Tiles of 16 need more LDS than
+// six waves per SIMD have: 1.2M points 1009 us with 16 (five waves) and 941 with
+// 8, 64 sweeps 3860 and 3697, with 4 1002 and 4028.
+__host__ __device__ inline uint32_t knn_tile_queries(uint32_t n1) {
+    return n1 <= 4096u ? 1u : n1 <= 20480u ? 2u : n1 <= 65536u ? 4u : (uint32_t)KNN_TQ;
 }
 
 // Queries per kNN item of a leaf in counter q of the plan (1: chunked, 2 .. the
@@ -246,7 +245,6 @@ struct Plan {
     uint32_t sort_tile;       // keys per workgroup of the radix passes (sort_tile_for)
     bool plan_halo;           // the halo kernel plans the kNN items (plan_in_halo)
     bool big_leaves;          // leaves of more than SEL_LDS_MAX points are ordinary here (big_leaf_path)
-    uint32_t tq_max;          // queries per kNN work item, at most (KNN_TQ_SMALL or KNN_TQ)
     uint8_t* deepf;           // [n] 1 at sorted positions inside deep level-10 cells; between the two
                               // deep-cell kernels, 2 marks the start of a cell to re-sort (zeroed block)
     // frames

@@ -1,9 +1,9 @@
 // Leaf-local brute-force kNN with halo candidates (Sec. 3: N_K(i), d_ij and
 // r_K,i on the voxel-filtered set P1).
 //
-// Work item = (leaf, a tile of 1 to 8 queries by the number of P1 points (16
-// above 2^19 input points), candidate chunk), one wave each. The candidates are the P1 positions of the leaf's
-// merged halo ranges; they are visited in aligned groups of 64 positions (one
+// Work item = (leaf, a tile of 1 to 8 queries by the number of P1 points,
+// candidate chunk), one wave each. The candidates are the P1 positions of the
+// leaf's merged halo ranges; they are visited in aligned groups of 64 positions (one
 // per lane), whose bounding boxes the bound kernel writes. Up to 64 groups at
 // a time are box-tested against every query of the tile (a query mask per
 // group) and ordered nearest-first; the needed groups are then taken four at
@@ -634,7 +634,7 @@ __global__ __launch_bounds__(64, WAVES) void knn_group_kernel(Plan P, const floa
     // Cursors are device-scope atomics, which one address takes one after
     // another: with eight streams, each also tried by every wave at its end,
     // the tail of every launch was 15-40 us of them (a 1.5k-point frame of 114
-    // items: 76 -> 29 us here; 120k points 132 -> 118 us). A stream's 64 or 80
+    // items: 76 -> 29 us here; 120k points 132 -> 118 us). A stream's 80 or 96
     // waves and their items, interleaved over the queue, are alike enough
     // that taking from other streams at the end gains nothing (1, 2 or 4
     // tries: 307.0, 307.7, 308.9 us for the 120k frame).
@@ -1120,25 +1120,22 @@ size_t knn_lds_bytes(uint32_t q, int k, bool pos) {
 }
 
 void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st) {
-    // Large inputs run long enough for occupancy to pay (positions); a smaller
-    // input's run is set by its longest items, where a gather per merge costs
-    // more (keys). Whole calls, keys against positions: 250k points 368 and
-    // 390 us, 500k 608 and 616, 1M 1193 and 1131, 900k in nine frames 1013 and
-    // 992.
+    // Buffers of positions halve the LDS of a wave, and large inputs' final
+    // lists are written from them; a smaller input's run is set by its longest
+    // items, where rebuilding the keys costs as much. Whole calls, keys against
+    // positions: 250k points 292.6 and 296.8 us, 500k 464 and 465, 900k in
+    // nine frames 742 and 735, 1.2M 941 and 942, 64 sweeps 3714 and 3697.
     // Six waves per SIMD cost some spilled registers: 500k points 623 us with
     // five and 601 with six, 250k 299.3 and 294.7, but eight frames of 20k 284
     // and 287.5.
     constexpr uint32_t KNN_SIX_WAVES_MIN_N = 3u << 16;
-    // The plan's tile size goes with the pending-buffer kind: tiles of
-    // KNN_TQ_SMALL queries exactly for the inputs that keep keys.
-    static_assert(KNN_TQ_SMALL_MAX_N == KNN_POS_MIN_N, "tile size and buffer kind switch together");
-    auto launch = [&](auto kern, int tq, bool pos, unsigned waves) {
+    auto launch = [&](auto kern, bool pos, unsigned waves) {
         hipLaunchKernelGGL(kern, dim3((unsigned)(num_cus > 0 ? num_cus : 256) * 4u * waves), dim3(64),
-                           knn_lds_bytes((uint32_t)tq, k, pos), st, P, (const float4*)P.cand4, k);
+                           knn_lds_bytes((uint32_t)KNN_TQ, k, pos), st, P, (const float4*)P.cand4, k);
     };
-    if (P.n > KNN_POS_MIN_N) launch(knn_group_kernel<true, KNN_TQ, 5>, KNN_TQ, true, 5u);
-    else if (P.n > KNN_SIX_WAVES_MIN_N) launch(knn_group_kernel<false, KNN_TQ_SMALL, 6>, KNN_TQ_SMALL, false, 6u);
-    else launch(knn_group_kernel<false, KNN_TQ_SMALL, 5>, KNN_TQ_SMALL, false, 5u);
+    if (P.n > KNN_POS_MIN_N) launch(knn_group_kernel<true, KNN_TQ, 6>, true, 6u);
+    else if (P.n > KNN_SIX_WAVES_MIN_N) launch(knn_group_kernel<false, KNN_TQ, 6>, false, 6u);
+    else launch(knn_group_kernel<false, KNN_TQ, 5>, false, 5u);
 }
 
 void launch_knn_merge(const Plan& P, const Params& prm, int num_cus, hipStream_t st) {

@@ -366,17 +366,17 @@ struct P1Emit {
 struct P1Fin {
     Counters* c;
     uint32_t* p1pos;
-    uint32_t n, tq_max;
+    uint32_t n;
     __device__ void operator()(uint32_t total) const {
         c->n_p1 = total;
-        c->knn_tq = knn_tile_queries(total, tq_max);
+        c->knn_tq = knn_tile_queries(total);
         p1pos[n] = total;
     }
 };
 
 void launch_p1_compact(const Plan& P, hipStream_t st) {
     launch_scan(P1Get{P.p1}, P1Emit{P.p1pos, P.pos4, P.leaf_of, P.cand4, P.cand_leaf, P.inv_p1},
-                P1Fin{P.ctr, P.p1pos, P.n, P.tq_max}, nullptr, P.n, P.scan_status + P.scan_tiles,
+                P1Fin{P.ctr, P.p1pos, P.n}, nullptr, P.n, P.scan_status + P.scan_tiles,
                 &P.ctr->status, st);
 }
 

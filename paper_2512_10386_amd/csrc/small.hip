@@ -433,7 +433,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
         }
         if (tid == 0) {
             P.ctr->n_p1 = total;
-            P.ctr->knn_tq = knn_tile_queries(total, P.tq_max);
+            P.ctr->knn_tq = knn_tile_queries(total);
             P.p1pos[n] = total;
         }
     }
