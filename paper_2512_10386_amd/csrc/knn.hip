@@ -6,7 +6,7 @@
 // leaf's merged halo ranges; they are visited in aligned groups of 64 positions (one
 // per lane), whose bounding boxes the bound kernel writes. Up to 64 groups at
 // a time are box-tested against every query of the tile (a query mask per
-// group) and ordered nearest-first; the needed groups are then taken four at
+// group) and ordered nearest-first; the needed groups are then taken three at
 // a time into registers, and each query that needs any of them computes its
 // squared distances to their 64 candidates, in fp32 as (dx*dx + dy*dy) + dz*dz
 // without contraction, so the neighbour sets are exact. A skipped group holds
@@ -51,7 +51,7 @@ constexpr int QPW = KNN_TQ;  // queries per wave item
 constexpr int PEND = 64;     // pending keys per query
 constexpr int PEND_HALF = 32;  // pending keys a half-wave merge takes (k <= 32)
 constexpr uint32_t KNN_POS_MIN_N = 1u << 19;  // above: pending buffers of positions
-constexpr int KNN_NB = 4;      // needed groups held in registers at a time
+constexpr int KNN_NB = 3;      // needed groups held in registers at a time
 constexpr int DRAIN_N = 4;     // queries whose final lists are sorted side by side
 
 __device__ __forceinline__ float dist2(const float4 q, const float4 c) {
@@ -606,7 +606,7 @@ __device__ __forceinline__ void flush_half(unsigned long long* __restrict__ lst0
 // same fp32 operations as dist2: a query skips a group whose box distance
 // exceeds its bound, so the group holds no candidate with d2 <= that bound.
 // Lane u then holds group u's mask of the queries that need it; a group is
-// loaded only if some query needs it, four at a time. Positions of a group outside
+// loaded only if some query needs it, three at a time. Positions of a group outside
 // the range's part in this chunk are not candidates: they get NaN coordinates
 // (d2 <= bound never holds). Groups of the range holding the tile come first,
 // from the tile's group outwards, then the other ranges in order.
@@ -615,7 +615,9 @@ __device__ __forceinline__ void flush_half(unsigned long long* __restrict__ lst0
 // cover better than more registers do: four waves that fetched the next groups
 // while these were evaluated took 277 us a call for a 120k sweep, 224 for a
 // batch of 12 objects and 660 for 500k points; five without 268, 217 and 623,
-// and with the loads at the top of the loop 264, 213 and (six) 592.
+// and with the loads at the top of the loop 264, 213 and (six) 592. Three groups
+// at a time leave room for one wave more: four and two of them with seven waves
+// 64 sweeps 3708 and 3656 us, three 3623.
 template <bool POS, int Q, int WAVES>
 __global__ __launch_bounds__(64, WAVES) void knn_group_kernel(Plan P, const float4* __restrict__ cand4, int kk) {
     using PT = typename Pending<POS>::T;
@@ -634,7 +636,7 @@ __global__ __launch_bounds__(64, WAVES) void knn_group_kernel(Plan P, const floa
     // Cursors are device-scope atomics, which one address takes one after
     // another: with eight streams, each also tried by every wave at its end,
     // the tail of every launch was 15-40 us of them (a 1.5k-point frame of 114
-    // items: 76 -> 29 us here; 120k points 132 -> 118 us). A stream's 80 or 96
+    // items: 76 -> 29 us here; 120k points 132 -> 118 us). A stream's 80 to 112
     // waves and their items, interleaved over the queue, are alike enough
     // that taking from other streams at the end gains nothing (1, 2 or 4
     // tries: 307.0, 307.7, 308.9 us for the 120k frame).
@@ -1125,15 +1127,17 @@ void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st) {
     // items, where rebuilding the keys costs as much. Whole calls, keys against
     // positions: 250k points 292.6 and 296.8 us, 500k 464 and 465, 900k in
     // nine frames 742 and 735, 1.2M 941 and 942, 64 sweeps 3714 and 3697.
-    // Six waves per SIMD cost some spilled registers: 500k points 623 us with
-    // five and 601 with six, 250k 299.3 and 294.7, but eight frames of 20k 284
-    // and 287.5.
-    constexpr uint32_t KNN_SIX_WAVES_MIN_N = 3u << 16;
+    // Six waves per SIMD cost some spilled registers, which small inputs, whose
+    // waves are few, only lose by: 1501 points 69.2 us with five and 70.1 with
+    // six, 20k 132.1 and 131.2, 120k 264.6 and 261.3 (cap 256: 210.5 and 207.0).
+    // Large inputs with six / seven / eight (positions): 1.2M points 945 / 925 /
+    // 944 us, 64 sweeps 3709 / 3623 / 3696.
+    constexpr uint32_t KNN_SIX_WAVES_MIN_N = 1u << 14;
     auto launch = [&](auto kern, bool pos, unsigned waves) {
         hipLaunchKernelGGL(kern, dim3((unsigned)(num_cus > 0 ? num_cus : 256) * 4u * waves), dim3(64),
                            knn_lds_bytes((uint32_t)KNN_TQ, k, pos), st, P, (const float4*)P.cand4, k);
     };
-    if (P.n > KNN_POS_MIN_N) launch(knn_group_kernel<true, KNN_TQ, 6>, true, 6u);
+    if (P.n > KNN_POS_MIN_N) launch(knn_group_kernel<true, KNN_TQ, 7>, true, 7u);
     else if (P.n > KNN_SIX_WAVES_MIN_N) launch(knn_group_kernel<false, KNN_TQ, 6>, false, 6u);
     else launch(knn_group_kernel<false, KNN_TQ, 5>, false, 5u);
 }

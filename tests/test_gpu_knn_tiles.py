@@ -48,7 +48,7 @@ def test_isolated_leaves(oracle, n):
         den.close()
 
 
-@pytest.mark.parametrize("n,k", [(65_536, 16), (65_537, 16), (196_608, 32), (196_609, 32), (196_609, 64)])
+@pytest.mark.parametrize("n,k", [(16_384, 64), (16_385, 64), (65_536, 16), (65_537, 16), (196_608, 32), (196_609, 64)])
 def test_waves_per_simd(oracle, n, k):
     """The edges of the four-query tiles and of the kernel for six waves."""
     from paper_2512_10386_amd.binding import Denoiser
