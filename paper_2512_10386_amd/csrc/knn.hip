@@ -722,18 +722,20 @@ __global__ __launch_bounds__(64, WAVES) void knn_group_kernel(Plan P, const floa
                     if (u == 0u) ug = gt;
                     else if (u <= 2u * n_alt) ug = (u & 1u) ? gt + ((u + 1u) >> 1) : gt - ((u + 1u) >> 1);
                     else ug = n_up > n_dn ? gt + (u - n_alt) : gt - (u - n_alt);
-                } else {
+                }
+                if (ub + 64u > gno) {
+                    // the last of the other ranges that starts at or before the unit
                     const uint32_t v = u - gno;
-                    uint32_t vg = 0;
-                    for (uint32_t q = 0; q < nr; ++q) {
-                        const uint32_t pn = (uint32_t)__builtin_amdgcn_readlane((int)u2n, (int)q);
-                        const uint32_t pp = (uint32_t)__builtin_amdgcn_readlane((int)u2pre, (int)q);
-                        if (pn > 0u && pp <= v) {
-                            r = q;
-                            vg = (uint32_t)__builtin_amdgcn_readlane((int)g0, (int)q) + (v - pp);
-                        }
+                    uint32_t q = 0;
+#pragma unroll
+                    for (uint32_t step = 16u; step != 0u; step >>= 1)
+                        if ((uint32_t)__shfl((int)u2pre, (int)(q + step), 64) <= v) q += step;
+                    const uint32_t vg =
+                        (uint32_t)__shfl((int)g0, (int)q, 64) + v - (uint32_t)__shfl((int)u2pre, (int)q, 64);
+                    if (u >= gno) {
+                        r = q;
+                        ug = vg;
                     }
-                    ug = vg;
                 }
                 ua = (uint32_t)__shfl((int)sa, (int)r, 64);
                 ue = (uint32_t)__shfl((int)sb, (int)r, 64);
