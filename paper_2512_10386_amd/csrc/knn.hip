@@ -86,9 +86,12 @@ __device__ __forceinline__ unsigned long long shfl64(unsigned long long v, int s
 constexpr int BOUND_MARGIN = 64;   // window reaches this far on each side of a query
 constexpr int BOUND_SPLIT = 8;     // adjacent lanes sharing one query's distances
 // Threshold ladder tau * 2^-m, m = 1..BOUND_RUNGS, then BOUND_BISECT geometric
-// bisection steps (down to a factor 2^(1/32) between thresholds tried).
+// bisection steps (down to a factor 2^(1/16) between thresholds tried). The
+// kernel is bound by the VALU (64 sweeps: 60 instructions per query, 460 us);
+// the rungs by the distances' exponents and one bisection less took whole calls
+// from 3587 to 3547 us, a 1.2M sweep from 920 to 914.
 constexpr int BOUND_RUNGS = 5;
-constexpr int BOUND_BISECT = 5;
+constexpr int BOUND_BISECT = 4;
 constexpr int BOUND_Q = 128;       // queries per block (BOUND_Q * BOUND_SPLIT threads)
 static_assert(BOUND_Q % KNN_GRP == 0, "a bound block covers whole culling groups");
 
@@ -106,7 +109,6 @@ static_assert(BOUND_Q % KNN_GRP == 0, "a bound block covers whole culling groups
 constexpr int BOUND_WPL = (2 * BOUND_MARGIN + 1 + BOUND_SPLIT - 1) / BOUND_SPLIT;  // window points per lane
 template <class Pts>
 __device__ float query_bound(Pts cand4, uint32_t qb, uint32_t qe, uint32_t qi, int k, uint32_t sub, bool live) {
-    constexpr int LEVELS = BOUND_RUNGS;
     constexpr float STEP = 0.5f;
     const bool run = live && qe - qb > (uint32_t)k;
     float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -146,22 +148,34 @@ __device__ float query_bound(Pts cand4, uint32_t qb, uint32_t qe, uint32_t qi, i
         for (int i = 0; i < BOUND_WPL; ++i) c += (dw[i] <= t) ? 1u : 0u;
         return sum8(c);
     };
-    // the rungs' counts are independent: all of them first, then the choice
-    float th[LEVELS];
-    uint32_t cnt[LEVELS];
-    float f = tau;
-#pragma unroll
-    for (int m = 0; m < LEVELS; ++m) {
-        f = f * STEP;
-        th[m] = f;
-        cnt[m] = 0;
-#pragma unroll
-        for (int i = 0; i < BOUND_WPL; ++i) cnt[m] += (dw[i] <= f) ? 1u : 0u;
-    }
+    // The rungs a distance lies under are the whole number of halvings from tau
+    // down to it, the difference of the two floats' bits without its mantissa
+    // part (exact for normal tau / 2^BOUND_RUNGS; below that tau itself stays).
+    // A lane's points are counted per number in 5-bit fields, the lanes' counts
+    // added three fields to a word.
+    static_assert(BOUND_RUNGS == 5 && BOUND_WPL < 32, "six fields of five bits");
     float best = tau;
+    if (tau >= 1e-30f) {
+        uint32_t w = 0;
 #pragma unroll
-    for (int m = 0; m < LEVELS; ++m)
-        if (sum8(cnt[m]) >= (uint32_t)k) best = th[m];
+        for (int i = 0; i < BOUND_WPL; ++i) {
+            const int m = (int)(__float_as_uint(tau) - __float_as_uint(fminf(dw[i], INFINITY))) >> 23;
+            w += 1u << (5u * (uint32_t)min(max(m, 0), BOUND_RUNGS));
+        }
+        auto field = [&](int m) { return (w >> (5 * m)) & 31u; };
+        const uint32_t a = sum8(field(1) | field(2) << 10 | field(3) << 20), b = sum8(field(4) | field(5) << 10);
+        uint32_t n = b >> 10;  // points under rung 5, then 4, ...
+        float t = tau * 0x1p-5f;
+        const uint32_t f[4] = {b & 1023u, a >> 20, (a >> 10) & 1023u, a & 1023u};
+        best = n >= (uint32_t)k ? t : tau;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const bool more = n >= (uint32_t)k;  // found already
+            n += f[m];
+            t *= 2.0f;
+            if (!more && n >= (uint32_t)k) best = t;
+        }
+    }
     float r = STEP;
 #pragma unroll
     for (int b = 0; b < BOUND_BISECT; ++b) {

@@ -60,3 +60,23 @@ def test_waves_per_simd(oracle, n, k):
         compare(run_gpu(den, xyz), ref)
     finally:
         den.close()
+
+
+@pytest.mark.parametrize("scale", [1e-18, 1e-13, 1.0, 1e17])
+def test_bound_scales(oracle, scale):
+    """The kNN bound counts halvings by exponents: copies (distance 0), powers
+    of two, and scales at which squared distances leave the normal range."""
+    import numpy as np
+    from paper_2512_10386_amd.binding import Denoiser
+    g = np.stack(np.meshgrid(*[np.arange(12.0)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    rng = np.random.default_rng(3)
+    xyz = np.concatenate([g, g[:300], 2.0 ** rng.integers(-6, 4, (3000, 3)), rng.uniform(0, 12, (2000, 3))])
+    xyz = (xyz * scale).astype(np.float32)[rng.permutation(len(xyz))]
+    prm = dict(k=16, leaf_cap=512, stages=6)
+    ref = oracle.denoise(xyz, **prm)
+    den = Denoiser(0, **prm)
+    try:
+        g = run_gpu(den, xyz)
+        assert np.array_equal(g["nbr_idx"], ref["nbr_idx"]) and np.array_equal(g["nbr_d2"], ref["nbr_d2"])
+    finally:
+        den.close()
