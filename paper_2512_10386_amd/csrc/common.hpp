@@ -125,9 +125,8 @@ struct __align__(16) KnnItem {
 // has so many of them that a workgroup per leaf runs in many rounds: above
 // 2^20 points, above 2^19 with a leaf cap of at most 512, or above 3 * 2^16
 // with one of at most 256. Whole calls, workgroups against waves: 120k points
-// at cap 256 249 and 252 us, 250k 368 and 347, 500k 608 and 547, 900k in nine
-// frames 1014 and 886; at cap 512 250k 355 and 367, 900k 1175 and 1117; 500k
-// at cap 1024 703 and 718.
+// at cap 256 206 and 209 us, 250k 299.5 and 289, 500k 495 and 458, 200k on a
+// torus 205.5 and 196.7; at cap 512 900k in nine frames 936 and 926.
 constexpr uint32_t SMALL_LEAF = 256;
 constexpr uint32_t SEL_LDS_MAX = 2048;  // leaves up to this size are selected from LDS
 inline bool small_leaf_path(uint32_t n, int32_t leaf_cap) {

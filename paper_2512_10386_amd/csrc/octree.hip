@@ -307,8 +307,10 @@ void launch_voxel(const Plan& P, const Params& prm, hipStream_t st) {
         launch_big_voxel(P, prm, st);
         return;
     }
-    // the wave path pays off for the many small leaves of large batches
-    const bool small = P.n > VOX_WAVE_MIN_N;
+    // The wave path pays off for the many small leaves of large inputs: 1M points
+    // at cap 256 763 us a call with workgroups alone and 753 with waves, but at
+    // cap 1024 1060 and 1071, 2.5M at cap 512 2398 and 2412.
+    const bool small = P.n > VOX_WAVE_MIN_N && (uint32_t)prm.leaf_cap <= VOX_WAVE_MAX;
     if (small) {
         unsigned wb = (P.n / 128 + 3) / 4;
         if (wb > 8192) wb = 8192;
@@ -319,7 +321,7 @@ void launch_voxel(const Plan& P, const Params& prm, hipStream_t st) {
     // call against 84, 20k at cap 512 158 against 155)
     const uint32_t per = prm.leaf_cap < 32 ? 8u : prm.leaf_cap < 128 ? (uint32_t)prm.leaf_cap / 4u : 32u;
     unsigned blocks = (P.n + per - 1) / per;
-    if (blocks > (small ? 2048u : 16384u)) blocks = small ? 2048u : 16384u;  // small: only the big leaves remain
+    if (blocks > (small ? 2048u : 65536u)) blocks = small ? 2048u : 65536u;  // small: only the big leaves remain
     // The smallest table that takes leaves of leaf_cap points from LDS, so
     // that more workgroups share a CU (200k points at cap 512: 272 us a call
     // with 4096 slots, 270 with 1024). Where a minimum leaf side makes
