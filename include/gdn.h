@@ -122,7 +122,7 @@ gdn_status gdn_denoise(gdn_ctx *ctx, const gdn_params *p, const float *xyz, int6
  * fixed scratch array of GDN_NOALLOC_MAX_BYTES inside the library, one per
  * GPU, held from the library's first use on that GPU until the process ends.
  * A frame whose gdn_workspace_size exceeds it is refused with GDN_ECAPACITY
- * (a 120k-point frame at k = 32 needs about 179 MiB). Every call on one GPU
+ * (a 120k-point frame at k = 32 needs about 173 MiB). Every call on one GPU
  * shares that GPU's array and it keeps the last call's contents
  * (gdn_debug_dump reads them): calls that overlap on one GPU, on any streams
  * or contexts, race and give unspecified results. The call never allocates

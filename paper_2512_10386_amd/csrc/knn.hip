@@ -33,8 +33,8 @@
 // (tau, 0xFFFFFFFF) and only candidates with d2 <= tau can ever enter. The
 // result is unchanged.
 //
-// Leaves with many candidates are split into chunks processed as separate
-// items; each writes its partial lists, which knn_merge_kernel combines after
+// With a chunk length given, leaves of more candidates are split into chunks
+// processed as separate items; each writes its partial lists, which knn_merge_kernel combines after
 // this kernel. (Combining them here would need device-scope release/acquire
 // between waves, which on this chip writes back the L2 of the releasing XCD
 // on every chunk.)

@@ -575,11 +575,10 @@ void launch_halo(const Plan& P, const Params& prm, hipStream_t st) {
 
 // ---------------------------------------------------------------- kNN plan
 //
-// Work items are (leaf, tile of up to KNN_TQ queries,
-// candidate chunk). Leaves whose candidate set exceeds the chunk length are
-// split into chunks whose partial top-k lists knn_merge_kernel combines; the
-// chunk length doubles until the partial lists and items fit their
-// workspace. This kernel fixes, per leaf, the chunking and the index of its
+// Work items are (leaf, tile of up to KNN_TQ queries, candidate chunk). Leaves
+// whose candidate set exceeds the chunk length (by default none) are split into
+// chunks whose partial top-k lists knn_merge_kernel combines; the chunk length
+// doubles until the partial lists and items fit their workspace. This kernel fixes, per leaf, the chunking and the index of its
 // first item. Items of chunked leaves (the heaviest) come first in the
 // queue; the other leaves follow in PLAN_CLASSES classes by candidates per
 // query, largest first, each class in leaf order. An item's run time grows
