@@ -702,6 +702,7 @@ __global__ __launch_bounds__(SEG_BLOCK) void deep_mark_kernel(Plan P, uint32_t c
         }
         __syncthreads();
         const uint32_t ns = s_n;
+        if (ns != 0u && threadIdx.x == 0) P.ctr->n_deep = 1u;  // (any workgroup's store of the same value)
         for (uint32_t e = threadIdx.x; e < ns * 32u; e += SEG_BLOCK) {
             const uint32_t q0 = s_start[e / 32u];
             const int g = (int)(e % 32u);
@@ -745,6 +746,7 @@ __global__ __launch_bounds__(SEG_BLOCK) void deep_cells_kernel(Plan P, uint32_t 
     __shared__ uint32_t s_v[SEG_LDS];
     __shared__ uint32_t s_nseg;
     __shared__ uint32_t s_foff[SORT_FOFF_LDS];  // batches of fewer frames search the offsets here
+    if (P.ctr->n_deep == 0u) return;  // (20k points 130.5 -> 129.6 us a call, 900k 757.5 -> 754)
     constexpr bool lds = LDS;
     if (lds)
         for (uint32_t i = threadIdx.x; i <= P.nf; i += blockDim.x) s_foff[i] = P.foff[i];
