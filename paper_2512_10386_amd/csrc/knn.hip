@@ -92,7 +92,11 @@ constexpr int BOUND_SPLIT = 8;     // adjacent lanes sharing one query's distanc
 // from 3587 to 3547 us, a 1.2M sweep from 920 to 914.
 constexpr int BOUND_RUNGS = 5;
 constexpr int BOUND_BISECT = 4;
-constexpr int BOUND_Q = 128;       // queries per block (BOUND_Q * BOUND_SPLIT threads)
+// Queries per block (BOUND_Q * BOUND_SPLIT threads, BOUND_Q + 129 points
+// staged). Blocks of 512 threads fill the CUs more evenly than 1024: 64 sweeps
+// 3537 us a call with 128 queries and 3501 with 64, 1.2M points 911 and 905,
+// 1501 points 68.4 and 66.9.
+constexpr int BOUND_Q = 64;
 static_assert(BOUND_Q % KNN_GRP == 0, "a bound block covers whole culling groups");
 
 // tau: the largest d2 to the k points next to the query in Morton order inside
