@@ -101,7 +101,7 @@ __device__ __forceinline__ void run_step(uint32_t leaf, float (&m)[6]) {
 // deep cells, leaf borders, their scan) takes the few microseconds that any
 // launch and its first loads take, so one workgroup that keeps the points on
 // chip is faster than ten launches over the whole chip. Whole calls, general
-// path and this one: 65 points 90 and 69 us, 500 101 and 78, 1501 112 and 89.
+// path and this one: 65 points 72.5 and 49.5 us, 500 76 and 53, 1501 91 and 67.
 // Most of it is the sort: a pass is six barriers over 16 waves, 3 us.
 // P1: the voxel filter and the P1 compaction too, by all threads over the
 // points (leaf boxes, then hash tables, in the LDS that the sort is done with):
@@ -440,8 +440,8 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
 }
 
 // One frame of so few points that the workgroup is done sooner than the chip
-// (3000 points 125 us the general way and 109 this way, 4096 132 and 120, but
-// 6000 130 and 136, with eight points per thread).
+// (3000 points 102 us the general way and 87.5 this way, 4096 107 and 94, but
+// 6000 106 and 108, with eight points per thread).
 bool small_tree(const Plan& P) { return P.nf == 1 && P.n <= 4u * SMALL_BLOCK; }
 
 void launch_small_tree(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
