@@ -94,6 +94,7 @@ struct Counters {
     // partial lists, items of chunked leaves, items of each class
     uint32_t plan_q[PLAN_COUNTERS];
     uint32_t n_deep;          // 1: some level-10 cell is marked for the re-sort
+    uint32_t n_vox_big;       // 1: some leaf is left to voxel_kernel by voxel_wave_kernel
     uint32_t n_big;           // 1: some leaf has more than SMALL_LEAF P1 points
     unsigned long long plan_acc[PLAN_LEVELS][3];  // per candidate chunk length: lists, items, chunked items
     unsigned long long plan_pairs;

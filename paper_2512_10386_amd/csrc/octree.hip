@@ -130,7 +130,10 @@ __global__ __launch_bounds__(256) void voxel_wave_kernel(Plan P, double beta, ui
     uint32_t* tc = s_cnt[w];
     for (uint32_t t = wid; t < nl; t += nw) {
         const uint32_t b = P.leaf_begin[t], e = P.leaf_begin[t + 1], nt = e - b;
-        if (nt > VOX_WAVE_MAX) continue;
+        if (nt > VOX_WAVE_MAX) {
+            if (lane == 0u) P.ctr->n_vox_big = 1u;  // (any wave's store of the same value)
+            continue;
+        }
         float4 p[VOX_WAVE_MAX / 64];
         float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
@@ -216,6 +219,7 @@ __global__ __launch_bounds__(VOX_BLOCK) void voxel_kernel(Plan P, double beta, u
     __shared__ float s_mn[3];
     __shared__ float s_h;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (skip_small && P.ctr->n_vox_big == 0u) return;
     const uint32_t nl = P.ctr->n_leaves;
     constexpr unsigned long long EMPTY = ~0ull;
     for (uint32_t t = blockIdx.x; t < nl; t += gridDim.x) {

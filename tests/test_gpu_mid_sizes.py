@@ -208,3 +208,19 @@ def test_frame_counts(nf):
     finally:
         bd.close()
         den.close()
+
+
+def test_over_full_leaves_beside_waves(oracle):
+    """Leaves above 256 points (copies of one point) where the voxel filter and
+    the selects of the others run a wave each."""
+    from paper_2512_10386_amd.binding import Denoiser
+    xyz = np.ascontiguousarray(crowded(540_001, 9))
+    xyz[:700] = xyz[5000]
+    ref = oracle.denoise(xyz, k=8, leaf_cap=256)
+    den = Denoiser(0, k=8, leaf_cap=256)
+    try:
+        g = run_gpu(den, xyz)
+        assert (g["leaf_end"] - g["leaf_begin"]).max() > 512
+        compare(g, ref)
+    finally:
+        den.close()
