@@ -89,7 +89,8 @@ gdn_status gdn_default_params(gdn_params *out);
 gdn_status gdn_create(gdn_ctx **out, int device);
 void gdn_destroy(gdn_ctx *ctx);
 
-/* Workspace bytes gdn_denoise needs for a frame of n points (n <= 2^30-1). */
+/* Workspace bytes for gdn_denoise of a frame of n points (n <= 2^30-1), and of
+ * every smaller one: the size never falls as n (or the frames of a batch) grow. */
 gdn_status gdn_workspace_size(gdn_ctx *ctx, const gdn_params *p, int64_t n, size_t *bytes);
 
 /*
@@ -121,8 +122,9 @@ gdn_status gdn_denoise(gdn_ctx *ctx, const gdn_params *p, const float *xyz, int6
  * gdn_denoise, without the workspace: the frame's intermediates live in a
  * fixed scratch array of GDN_NOALLOC_MAX_BYTES inside the library, one per
  * GPU, held from the library's first use on that GPU until the process ends.
- * A frame whose gdn_workspace_size exceeds it is refused with GDN_ECAPACITY
- * (a 120k-point frame at k = 32 needs about 173 MiB). Every call on one GPU
+ * A frame whose intermediates exceed it is refused with GDN_ECAPACITY; one
+ * whose gdn_workspace_size fits never is (a 120k-point frame at k = 32 needs
+ * about 173 MiB). Every call on one GPU
  * shares that GPU's array and it keeps the last call's contents
  * (gdn_debug_dump reads them): calls that overlap on one GPU, on any streams
  * or contexts, race and give unspecified results. The call never allocates

@@ -167,6 +167,18 @@ gdn::Plan make_plan(uint32_t n, uint32_t nf, int k, char* base) {
     return P;
 }
 
+// Workspace bytes reported for frames or batches of n points. A frame just
+// below an edge of the radix tiles has more tiles, and so more look-back words,
+// than one just above it: the largest layout of any size up to n is reported,
+// so that a workspace made for n points takes every smaller frame too.
+static_assert(gdn::SCAN_SMALL_N == gdn::SORT_TILE_EDGES[2], "the scans' tiles change at an edge of the radix tiles");
+size_t workspace_bytes(uint32_t n, uint32_t nf, int k) {
+    size_t bytes = make_plan(n, nf, k, nullptr).bytes;
+    for (const uint32_t edge : gdn::SORT_TILE_EDGES)
+        if (edge < n) bytes = std::max(bytes, make_plan(edge, nf, k, nullptr).bytes);
+    return bytes;
+}
+
 bool params_ok(const gdn_params* p, std::string* why) {
     auto bad = [&](const char* m) { *why = m; return false; };
     if (!p) return bad("params is NULL");
@@ -341,7 +353,7 @@ gdn_status gdn_workspace_size_batch(gdn_ctx* ctx, const gdn_params* p, int64_t n
     if (!bytes) return fail(ctx, GDN_EINVAL, "bytes is NULL");
     const gdn_status e = size_checks(ctx, p, n, nf);
     if (e != GDN_OK) return e;
-    *bytes = n == 0 ? 0 : make_plan((uint32_t)n, (uint32_t)nf, p->k, nullptr).bytes;
+    *bytes = n == 0 ? 0 : workspace_bytes((uint32_t)n, (uint32_t)nf, p->k);
     return GDN_OK;
 }
 
@@ -428,9 +440,9 @@ gdn_status gdn_denoise(gdn_ctx* ctx, const gdn_params* p, const float* xyz, int6
 gdn_status gdn_denoise_noalloc(gdn_ctx* ctx, const gdn_params* p, const float* xyz, int64_t n, uint8_t* keep,
                                float* score, uint8_t* stage, uint32_t* kept_idx, int64_t* n_kept, void* stream) {
     if (!ctx) return GDN_EINVAL;
-    size_t need = 0;
-    const gdn_status e = gdn_workspace_size(ctx, p, n, &need);
+    const gdn_status e = size_checks(ctx, p, n, 1);
     if (e != GDN_OK) return e;
+    const size_t need = n == 0 ? 0 : make_plan((uint32_t)n, 1u, p->k, nullptr).bytes;
     if (need > (size_t)GDN_NOALLOC_MAX_BYTES)
         return fail(ctx, GDN_ECAPACITY,
                     "frame needs " + std::to_string(need) + " bytes of scratch; gdn_denoise_noalloc holds " +

@@ -193,8 +193,11 @@ inline bool plan_in_halo(uint32_t n, int32_t leaf_cap) {
 // 300.2, 900k - / 875 / 863. 4096 keys, staged in LDS, by 512 threads of 8 keys
 // against 256 of 16 (the same LDS with twice the waves): 1.2M points 1051 and
 // 1042 us, 6.2M 3990 and 3948.
+constexpr uint32_t SORT_TILE_EDGES[] = {1u << 14, 7u << 14, 1u << 20};  // the largest n of each tile but the last
 inline uint32_t sort_tile_for(uint32_t n) {
-    return n <= (1u << 14) ? 512u : n <= (7u << 14) ? 1024u : n <= (1u << 20) ? 2048u : 4096u;
+    uint32_t tile = 512u;
+    for (const uint32_t edge : SORT_TILE_EDGES) tile <<= n > edge ? 1 : 0;
+    return tile;
 }
 
 // Method parameters as the kernels use them.

@@ -1,0 +1,63 @@
+"""Workspace sizes never fall as inputs grow: a workspace made for the largest
+frame (or for a server's slot) takes every smaller one. Host side only."""
+import pytest
+
+# the tile of the radix passes changes at 2^14, 7 * 2^14 and 2^20 points, the
+# tile of the scans at 2^20
+EDGES = [1 << 14, 7 << 14, 1 << 20]
+
+
+@pytest.mark.parametrize("k", [1, 12, 32, 64])
+@pytest.mark.parametrize("frames", [1, 2, 300])
+def test_workspace_never_falls_as_points_grow(k, frames):
+    from paper_2512_10386_amd import binding as B
+    p = B.make_params(k=k)
+    for edge in EDGES:
+        sizes = [B.gdn_workspace_size_batch(0, p, n, frames) for n in range(edge - 3, edge + 4)]
+        sizes += [B.gdn_workspace_size_batch(0, p, edge + d, frames) for d in (100, 1000, 3000, 10_000)]
+        assert sizes == sorted(sizes), (edge, sizes)
+
+
+def test_workspace_of_a_slot_takes_fewer_frames():
+    from paper_2512_10386_amd import binding as B
+    p = B.make_params(k=32)
+    for points in (16_400, 114_800, 1_048_700):
+        slot = B.gdn_workspace_size_batch(0, p, points, 8)
+        for n in (points, points - 150, points - 16, EDGES[0], points // 2):
+            for frames in (1, 2, 7, 8):
+                if n <= points:
+                    assert B.gdn_workspace_size_batch(0, p, n, frames) <= slot, (points, n, frames)
+
+
+@pytest.mark.gpu
+def test_server_slot_runs_a_slightly_smaller_batch():
+    """A slot of 114,800 points takes a batch of 114,650, on the other side of
+    an edge; its frames equal the same frames denoised alone."""
+    import time
+
+    import numpy as np
+    import torch
+
+    from paper_2512_10386_amd import synth
+    from paper_2512_10386_amd.binding import Denoiser
+    from paper_2512_10386_amd.serve import Server
+    x = torch.from_numpy(synth.lidar_frame(seed=5, n_az=1800)[0][:114_650].astype(np.float32)).cuda()
+    frames = [x[:60_000].contiguous(), x[60_000:].contiguous()]
+    torch.cuda.synchronize()
+    srv = Server(0, hbm_budget=8 << 30, max_slots=1, slot_points=114_800, slot_frames=8, k=32, leaf_cap=512)
+    den = Denoiser(0, k=32, leaf_cap=512)
+    try:
+        outs = [srv.alloc(len(f)) for f in frames]
+        left = {srv.submit(f, o) for f, o in zip(frames, outs)}
+        t0 = time.time()
+        while left:
+            assert time.time() - t0 < 30.0, "server did not finish"
+            left.difference_update(srv.poll()[0])
+        torch.cuda.synchronize()
+        for f, o in zip(frames, outs):
+            ref = den(f)
+            for a, b in ((o.keep, ref.keep), (o.score, ref.score), (o.stage, ref.stage)):
+                assert torch.equal(a[:len(f)], b[:len(f)])
+    finally:
+        den.close()
+        srv.close()
