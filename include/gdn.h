@@ -217,7 +217,8 @@ gdn_status gdn_autotune(gdn_ctx *ctx, gdn_params *p, const int32_t *caps, int nc
  *     unspecified; and optionally the queue length and the number of busy
  *     slots.
  * Results of a frame equal those of gdn_denoise on it alone. Not thread-safe;
- * poll from one thread. After a GDN_EHIP from poll the server is unusable.
+ * poll from one thread. Requests whose batch could not be started stay queued;
+ * after a GDN_EHIP from poll the server is otherwise unusable.
  * Destroy waits for running slots, drops frames still queued and frees the
  * slots; destroy the server before its context. GDN_ENOMEM from create if
  * the budget holds no slot (gdn_server_info gives the bytes per slot).

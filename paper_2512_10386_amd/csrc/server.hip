@@ -126,16 +126,16 @@ void free_slot(Slot& sl) {
     sl = Slot{};
 }
 
-// Start a batch in a free slot from the head of the queue.
+// Start a batch in a free slot from the head of the queue. The requests leave
+// the queue once all of the batch is enqueued; after an error they still wait.
 gdn_status launch_slot(gdn_server* S, Slot& sl) {
     uint32_t nr = 0;
     int64_t total = 0;
     sl.tickets.clear();
-    while (!S->waiting.empty() && (int)nr < S->cap_frames && total + S->waiting.front().desc.n <= S->cap_points) {
-        Req r = S->waiting.front();
-        S->waiting.pop_front();
-        r.desc.off = total;
-        sl.desc_host[nr++] = r.desc;
+    for (const Req& r : S->waiting) {
+        if ((int)nr == S->cap_frames || total + r.desc.n > S->cap_points) break;
+        sl.desc_host[nr] = r.desc;
+        sl.desc_host[nr++].off = total;
         sl.tickets.push_back(r.ticket);
         total += r.desc.n;
     }
@@ -156,6 +156,7 @@ gdn_status launch_slot(gdn_server* S, Slot& sl) {
         return srv_fail(S, GDN_EHIP, "hipMemcpyAsync of the status word failed");
     if (hipEventRecord(sl.done, sl.stream) != hipSuccess) return srv_fail(S, GDN_EHIP, "hipEventRecord failed");
     if (hipGetLastError() != hipSuccess) return srv_fail(S, GDN_EHIP, "kernel launch failed");
+    S->waiting.erase(S->waiting.begin(), S->waiting.begin() + nr);
     sl.busy = true;
     return GDN_OK;
 }
