@@ -37,18 +37,12 @@ __device__ __forceinline__ double wave_sum_f(double v) {
     return v;
 }
 
-// Per P1 point, at its P1 position (where the neighbour lists point): ln rho,
-// ln rho - ln(rho_med^2 + eps) and 1 / r_K^2. rho = 0 (fewer than k candidates)
-// gives -inf. The last two are kept in memory the pass no longer uses (its
-// partial kNN lists).
-__global__ __launch_bounds__(256) void fit_prep_kernel(Plan P, double eps, double* __restrict__ lrho_p,
-                                                       double2* __restrict__ own_p) {
+// ln rho of every P1 point, at its P1 position (where the neighbour lists
+// point). rho = 0 (fewer than k candidates) gives -inf.
+__global__ __launch_bounds__(256) void fit_prep_kernel(Plan P, double* __restrict__ lrho_p) {
     const uint32_t np1 = P.ctr->n_p1;
-    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < np1; q += gridDim.x * blockDim.x) {
-        const double l = log(P.rho_c[q]), med = P.leaf_rho_med[P.cand_leaf[q]], r = P.r64_c[q];
-        lrho_p[q] = l;
-        own_p[q] = make_double2(l - log(med * med + eps), 1.0 / (r * r));
-    }
+    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < np1; q += gridDim.x * blockDim.x)
+        lrho_p[q] = log(P.rho_c[q]);
 }
 
 template <int M>
@@ -73,10 +67,11 @@ __device__ __forceinline__ double seg_sum4(const double (&v)[4], uint32_t kp, ui
 }
 
 // FP64 exponentials and logarithms bound this kernel. Each wave takes
-// FIT_TILE queries at a time: the neighbour terms one lane per neighbour, with
-// one logarithm and one exponential per term (the three exponents are added
-// first, their rounding errors carried along), the sums into
-// LDS, and then the loss of the tile's queries one lane per query. (With three
+// FIT_TILE queries at a time: what depends on the query alone (ln rho -
+// ln(rho_med^2 + eps) and 1 / r_K^2) one lane per query, into LDS; the neighbour
+// terms one lane per neighbour, with one logarithm and one exponential per term
+// (the three exponents are added first, their rounding errors carried along),
+// the sums into LDS; then the loss of the tile's queries one lane per query. (With three
 // logarithms and three exponentials per term and the loss evaluated by one
 // lane per segment: 62 us for 107k P1 points at k = 16, this 27.)
 constexpr uint32_t FIT_TILE = 32;
@@ -87,10 +82,10 @@ struct FitSigma {
 };
 
 __global__ __launch_bounds__(256) void fit_kernel(Plan P, const uint8_t* __restrict__ label,
-                                                  const double* __restrict__ lrho_p,
-                                                  const double2* __restrict__ own_p, int kk, FitArgs a, FitSigma S,
+                                                  const double* __restrict__ lrho_p, int kk, FitArgs a, FitSigma S,
                                                   double* __restrict__ part) {
     __shared__ double s_red[4][FIT_PARTS];
+    __shared__ double2 s_own[4][FIT_TILE];    // per wave and query: its part of ln(ratio), 1 / r_K^2
     __shared__ double s_sum[4][4][FIT_TILE];  // per wave and query: F and its three weighted sums
     const uint32_t np1 = P.ctr->n_p1;
     const uint32_t k = (uint32_t)kk;
@@ -101,14 +96,40 @@ __global__ __launch_bounds__(256) void fit_kernel(Plan P, const uint8_t* __restr
     const uint32_t wid = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const double ha = 0.5 * a.alpha, hg = -0.5 * a.gamma;
     double acc[FIT_PARTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (uint32_t q0 = wid * FIT_TILE; q0 < np1; q0 += nw * FIT_TILE) {
+    // what a tile's queries read (lane l: query l of the tile) is fetched while
+    // the tile before it is worked on, the leaf's median one step behind the leaf
+    bool mine = false;
+    uint32_t leaf = 0;
+    double lrho = 0.0, r64 = 1.0, med = 0.0;
+    auto fetch = [&](uint32_t q0) {
+        const uint32_t ql = q0 + lane;
+        mine = lane < FIT_TILE && ql < np1;
+        if (mine) {
+            mine = P.p2[ql] != 0;
+            leaf = P.cand_leaf[ql];
+            lrho = lrho_p[ql];
+            r64 = P.r64_c[ql];
+        }
+    };
+    auto fetch_median = [&]() {
+        if (mine) med = P.leaf_rho_med[leaf];
+    };
+    const uint32_t first = wid * FIT_TILE;
+    fetch(first);
+    fetch_median();
+    for (uint32_t q0 = first; q0 < np1; q0 += nw * FIT_TILE) {
+        const bool live = mine;  // the loss of query q0 + lane is this lane's
+        if (lane < FIT_TILE)  // (queries outside P2: a radius that none has)
+            s_own[wave][lane] = live ? make_double2(lrho - log(med * med + a.eps), 1.0 / (r64 * r64)) : make_double2(0.0, -1.0);
+        wave_lds_fence();
+        fetch(q0 + nw * FIT_TILE);
         for (uint32_t i0 = 0; i0 < FIT_TILE; i0 += qpw) {
             const uint32_t qi = q0 + i0 + seg;
             double v[4] = {0.0, 0.0, 0.0, 0.0};
-            if (seg < qpw && r < k && qi < np1 && P.p2[qi]) {
+            const double2 own = seg < qpw ? s_own[wave][i0 + seg] : make_double2(0.0, -1.0);
+            if (r < k && !(own.y < 0.0)) {
                 const uint32_t j = P.nbr[(size_t)qi * k + r];
                 if (j < P.n) {
-                    const double2 own = own_p[qi];
                     const double lr = own.x + lrho_p[j];
                     // the neighbour (P1 position j) and the query from their sorted
                     // copies of the input coordinates
@@ -148,11 +169,11 @@ __global__ __launch_bounds__(256) void fit_kernel(Plan P, const uint8_t* __restr
             }
         }
         wave_lds_fence();
-        const uint32_t qi = q0 + lane;
-        if (lane < FIT_TILE && qi < np1 && P.p2[qi]) {
+        fetch_median();
+        if (live) {
             const double F = s_sum[wave][0][lane];
             if (F > 0.0 && F < INFINITY) {
-                const double y = label[__float_as_uint(P.cand4[qi].w)] ? 0.0 : 1.0;
+                const double y = label[__float_as_uint(P.cand4[q0 + lane].w)] ? 0.0 : 1.0;
                 const double z = (log(F) - a.tau) / a.T;
                 const double p = 1.0 / (1.0 + exp(-z));
                 acc[0] += (z > 0.0 ? z + log1p(exp(-z)) : log1p(exp(z))) - y * z;
@@ -226,13 +247,11 @@ void launch_fit(const Plan& P, const float*, const uint8_t* label, const FitArgs
     unsigned pb = (P.n + 255) / 256;
     if (pb > 4096) pb = 4096;
     if (pb == 0) pb = 1;
-    // (plist holds at least 24 bytes per point)
-    double2* own_p = (double2*)P.plist;
-    hipLaunchKernelGGL(fit_prep_kernel, dim3(pb), dim3(256), 0, st, P, a.eps, lrho_p, own_p);
+    hipLaunchKernelGGL(fit_prep_kernel, dim3(pb), dim3(256), 0, st, P, lrho_p);
     const unsigned nb = fit_blocks(P.n);
     const long double s2 = (long double)a.sigma * a.sigma, h = -0.5L / s2;
     const FitSigma S{(double)h, (double)(h - (double)h), (double)(1.0L / (s2 * a.sigma))};
-    hipLaunchKernelGGL(fit_kernel, dim3(nb), dim3(256), 0, st, P, label, lrho_p, own_p, P.k, a, S, part);
+    hipLaunchKernelGGL(fit_kernel, dim3(nb), dim3(256), 0, st, P, label, lrho_p, P.k, a, S, part);
     hipLaunchKernelGGL(fit_final_kernel, dim3(1), dim3(FIT_FINAL), 0, st, part, nb, out);
 }
 
