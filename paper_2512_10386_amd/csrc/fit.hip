@@ -16,6 +16,9 @@
 // One lane per neighbour (as the score kernel); per-block partial sums in a
 // fixed order, then one block sums the partials: the result does not depend
 // on scheduling.
+#include <algorithm>
+#include <limits>
+
 #include "kernels.hpp"
 #include "wave.hpp"
 
@@ -249,8 +252,11 @@ void launch_fit(const Plan& P, const float*, const uint8_t* label, const FitArgs
     if (pb == 0) pb = 1;
     hipLaunchKernelGGL(fit_prep_kernel, dim3(pb), dim3(256), 0, st, P, lrho_p);
     const unsigned nb = fit_blocks(P.n);
-    const long double s2 = (long double)a.sigma * a.sigma, h = -0.5L / s2;
-    const FitSigma S{(double)h, (double)(h - (double)h), (double)(1.0L / (s2 * a.sigma))};
+    // (a bandwidth so small that its powers overflow leaves the neighbours at
+    // d = 0 alone, whose d^2 / r^2 = 0 must not meet an infinity)
+    const long double top = std::numeric_limits<double>::max();
+    const long double s2 = (long double)a.sigma * a.sigma, h = std::max(-0.5L / s2, -top);
+    const FitSigma S{(double)h, (double)(h - (double)h), (double)std::min(1.0L / (s2 * a.sigma), top)};
     hipLaunchKernelGGL(fit_kernel, dim3(nb), dim3(256), 0, st, P, label, lrho_p, P.k, a, S, part);
     hipLaunchKernelGGL(fit_final_kernel, dim3(1), dim3(FIT_FINAL), 0, st, part, nb, out);
 }
