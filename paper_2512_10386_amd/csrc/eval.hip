@@ -13,6 +13,8 @@
 // chunks' answers are combined with a 64-bit atomic minimum on the key
 // (fp32 d2 bits << 32 | index): d2 >= 0, so the bit order is the value
 // order, and equal distances resolve to the smaller index.
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "radix.hpp"
 #include "wave.hpp"
@@ -1018,9 +1020,15 @@ size_t eval_min_workspace_bytes(uint32_t nc, uint32_t nd) {
     return al256((size_t)8 * nc) + al256((size_t)8 * nd) + 2 * al256((size_t)8 * EV_STRIDE * EV_BLOCKS_MAX);
 }
 
+// The largest layout of any two clouds up to these sizes: just below an edge of
+// the radix tiles there are more tiles, and look-back words, than just above it,
+// and a workspace kept for larger clouds must not send those to brute force.
 size_t eval_workspace_bytes(uint32_t nc, uint32_t nd) {
-    const size_t brute = eval_min_workspace_bytes(nc, nd), groups = nn_plan(nullptr, nc, nullptr, nd, nullptr).bytes;
-    return brute > groups ? brute : groups;
+    size_t bytes = std::max(eval_min_workspace_bytes(nc, nd), nn_plan(nullptr, nc, nullptr, nd, nullptr).bytes);
+    for (const uint32_t edge : SORT_TILE_EDGES)
+        if (edge < std::max(nc, nd))
+            bytes = std::max(bytes, nn_plan(nullptr, std::min(nc, edge), nullptr, std::min(nd, edge), nullptr).bytes);
+    return bytes;
 }
 
 void launch_eval(const float* clean, uint32_t nc, const float* den, uint32_t nd, void* ws, size_t ws_bytes, double* out,

@@ -29,6 +29,17 @@ def test_workspace_of_a_slot_takes_fewer_frames():
                     assert B.gdn_workspace_size_batch(0, p, n, frames) <= slot, (points, n, frames)
 
 
+@pytest.mark.parametrize("other", [1000, 0, 3_000_000])
+def test_eval_workspace_never_falls_as_clouds_grow(other):
+    """Sizes around the edges, against a small, an equal and a large cloud."""
+    from paper_2512_10386_amd import binding as B
+    for edge in EDGES + [1 << 15]:
+        ns = list(range(edge - 3, edge + 4)) + [edge + d for d in (100, 1000, 3000, 10_000)]
+        for pair in (lambda n: (n, other or n), lambda n: (other or n, n)):
+            sizes = [B.gdn_eval_workspace_size(0, *pair(n)) for n in ns]
+            assert sizes == sorted(sizes), (edge, sizes)
+
+
 @pytest.mark.gpu
 def test_server_slot_runs_a_slightly_smaller_batch():
     """A slot of 114,800 points takes a batch of 114,650, on the other side of
