@@ -34,15 +34,19 @@ constexpr int EV_BLOCK = 256;
 constexpr unsigned EV_BLOCKS_MAX = 1024;
 constexpr int EV_STRIDE = 8;                // doubles per block partial
 
-// One direction of a brute-force search: na queries, the best key of each.
+// One direction of a brute-force search: na queries, the best key of each; its
+// workgroups are `blocks` blocks of queries times the chunks of the reference.
 struct NnDir {
     const float* a;
     const float* b;
-    uint32_t na, nb, chunk;
+    uint32_t na, nb, chunk, blocks, chunks;
     unsigned long long* key;
 };
 
-// (the metrics run both directions in each launch: blockIdx.z)
+// (the metrics run both directions in each launch: blockIdx.z here, one after
+// the other in the search, whose grids differ: as one z-grid of both directions'
+// largest sizes 300 against 10M points took 18 ms, nearly all of it workgroups
+// without work)
 __global__ __launch_bounds__(256) void nn_init_kernel(NnDir d0, NnDir d1) {
     const NnDir& d = blockIdx.z ? d1 : d0;
     const unsigned long long none = (unsigned long long)__float_as_uint(INFINITY) << 32;
@@ -50,11 +54,13 @@ __global__ __launch_bounds__(256) void nn_init_kernel(NnDir d0, NnDir d1) {
 }
 
 __global__ __launch_bounds__(NN_BLOCK) void nn_kernel(NnDir d0, NnDir d1) {
-    __shared__ float4 s_b[NN_TILE];
-    const NnDir& d = blockIdx.z ? d1 : d0;
-    const uint32_t i = blockIdx.x * NN_BLOCK + threadIdx.x;
-    const uint64_t c0 = (uint64_t)blockIdx.y * d.chunk;
-    if (blockIdx.x * (uint32_t)NN_BLOCK >= d.na || c0 >= d.nb) return;
+    __shared__ float s_x[NN_TILE], s_y[NN_TILE], s_z[NN_TILE];
+    const uint32_t blocks0 = d0.blocks * d0.chunks;
+    const bool second = blockIdx.x >= blocks0;
+    const NnDir& d = second ? d1 : d0;
+    const uint32_t blk = second ? blockIdx.x - blocks0 : blockIdx.x;
+    const uint32_t i = blk % d.blocks * NN_BLOCK + threadIdx.x;
+    const uint32_t c0 = blk / d.blocks * d.chunk;  // (below nb: the last chunk is not empty)
     const bool live = i < d.na;
     float ax = 0.f, ay = 0.f, az = 0.f;
     if (live) {
@@ -62,21 +68,31 @@ __global__ __launch_bounds__(NN_BLOCK) void nn_kernel(NnDir d0, NnDir d1) {
         ay = d.a[3 * (size_t)i + 1];
         az = d.a[3 * (size_t)i + 2];
     }
-    const uint32_t c1 = (uint32_t)min((uint64_t)d.nb, c0 + d.chunk);
+    const uint32_t c1 = min(d.nb, c0 + d.chunk);
+    // a thread's point of the next tile, read while the tile before is evaluated
+    // (past the end: the last point again, which changes nothing)
+    static_assert(NN_TILE == NN_BLOCK, "a point of the tile per thread");
+    float nx, ny, nz;
+    auto read = [&](uint32_t t0) {
+        const size_t j = min(t0 + threadIdx.x, c1 - 1u);
+        nx = d.b[3 * j];
+        ny = d.b[3 * j + 1];
+        nz = d.b[3 * j + 2];
+    };
+    read(c0);
     float best = INFINITY;
     uint32_t bi = 0;
-    for (uint32_t t0 = (uint32_t)c0; t0 < c1; t0 += NN_TILE) {
-        const uint32_t tn = min((uint32_t)NN_TILE, c1 - t0);
+    for (uint32_t t0 = c0; t0 < c1; t0 += NN_TILE) {
         __syncthreads();
-        for (uint32_t e = threadIdx.x; e < (uint32_t)NN_TILE; e += NN_BLOCK) {
-            const size_t j = t0 + min(e, tn - 1u);  // (past the end: the last point again, which changes nothing)
-            s_b[e] = make_float4(d.b[3 * j], d.b[3 * j + 1], d.b[3 * j + 2], 0.f);
-        }
+        s_x[threadIdx.x] = nx;
+        s_y[threadIdx.x] = ny;
+        s_z[threadIdx.x] = nz;
         __syncthreads();
+        if (t0 + NN_TILE < c1) read(t0 + NN_TILE);
+        const uint32_t end = min((uint32_t)NN_TILE, (c1 - t0 + 7u) & ~7u);
 #pragma unroll 8
-        for (uint32_t e = 0; e < (uint32_t)NN_TILE; ++e) {
-            const float4 c = s_b[e];
-            const float dx = c.x - ax, dy = c.y - ay, dz = c.z - az;
+        for (uint32_t e = 0; e < end; ++e) {
+            const float dx = s_x[e] - ax, dy = s_y[e] - ay, dz = s_z[e] - az;
             const float v = (dx * dx + dy * dy) + dz * dz;  // compiled without contraction (no FMA)
             if (v < best) {
                 best = v;
@@ -982,23 +998,23 @@ size_t nearest_workspace_bytes(uint32_t na) { return al256((size_t)8 * na); }
 // Brute-force keys of one direction, or of both in one launch each.
 static void launch_nearest_keys(NnDir d0, NnDir d1, hipStream_t st) {
     const unsigned dirs = d1.key ? 2u : 1u;
-    unsigned qb = 1, split = 1;
+    unsigned qb = 1, total = 0;
     for (unsigned i = 0; i < dirs; ++i) {
         NnDir& d = i ? d1 : d0;
-        const unsigned q = (d.na + NN_BLOCK - 1) / NN_BLOCK;
+        d.blocks = (d.na + NN_BLOCK - 1) / NN_BLOCK;
         const unsigned tiles = (d.nb + NN_TILE - 1) / NN_TILE;
-        unsigned s = (NN_MIN_BLOCKS + q - 1) / q;
+        unsigned s = (NN_MIN_BLOCKS + d.blocks - 1) / d.blocks;
         if (s > tiles) s = tiles;
         if (s < 1) s = 1;
         d.chunk = ((d.nb + s - 1) / s + NN_TILE - 1) / NN_TILE * NN_TILE;
-        s = (d.nb + d.chunk - 1) / d.chunk;
-        if (q > qb) qb = q;
-        if (s > split) split = s;
+        d.chunks = (d.nb + d.chunk - 1) / d.chunk;
+        qb = std::max(qb, d.blocks);
+        total += d.blocks * d.chunks;
     }
     unsigned ib = qb;
     if (ib > 4096) ib = 4096;
     hipLaunchKernelGGL(nn_init_kernel, dim3(ib, 1, dirs), dim3(256), 0, st, d0, d1);
-    hipLaunchKernelGGL(nn_kernel, dim3(qb, split, dirs), dim3(NN_BLOCK), 0, st, d0, d1);
+    hipLaunchKernelGGL(nn_kernel, dim3(total), dim3(NN_BLOCK), 0, st, d0, d1);
 }
 
 void launch_nearest(const float* a, uint32_t na, const float* b, uint32_t nb, void* ws, size_t ws_bytes, uint32_t* idx,
@@ -1010,7 +1026,7 @@ void launch_nearest(const float* a, uint32_t na, const float* b, uint32_t nb, vo
         return;
     }
     unsigned long long* key = (unsigned long long*)ws;
-    launch_nearest_keys(NnDir{a, b, na, nb, 0u, key}, NnDir{}, st);
+    launch_nearest_keys(NnDir{a, b, na, nb, 0u, 0u, 0u, key}, NnDir{}, st);
     unsigned ob = (na + 255) / 256;
     if (ob > 4096) ob = 4096;
     hipLaunchKernelGGL(nn_out_kernel, dim3(ob), dim3(256), 0, st, key, na, idx, d2);
@@ -1052,7 +1068,7 @@ void launch_eval(const float* clean, uint32_t nc, const float* den, uint32_t nd,
     double* pc = (double*)w;
     w += al256((size_t)8 * EV_STRIDE * EV_BLOCKS_MAX);
     double* pd = (double*)w;
-    const NnDir d0{clean, den, nc, nd, 0u, kc}, d1{den, clean, nd, nc, 0u, kd};
+    const NnDir d0{clean, den, nc, nd, 0u, 0u, 0u, kc}, d1{den, clean, nd, nc, 0u, 0u, 0u, kd};
     launch_nearest_keys(d0, d1, st);
     const unsigned bc = ev_blocks(nc), bd = ev_blocks(nd);
     hipLaunchKernelGGL(ev_sum_kernel, dim3(bc + bd), dim3(EV_BLOCK), 0, st, d0, d1, bc, pc, pd);

@@ -1,0 +1,45 @@
+"""Nearest neighbours and metrics of clouds of unequal sizes: the two directions
+of the brute-force search have grids of their own (few queries take the
+reference in many chunks), one point on a side among them. Against the oracle,
+tolerances as in test_gpu_eval.py."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ev():
+    from paper_2512_10386_amd.evaluate import Evaluator
+    e = Evaluator(0)
+    yield e
+    e.close()
+
+
+def cloud(n, seed):
+    x = np.random.default_rng(seed).normal(size=(n, 3)).astype(np.float32)
+    x[n // 2:n // 2 + 3] = x[:1]  # copies: equal distances go to the smaller index
+    return x
+
+
+@pytest.mark.parametrize("na,nb", [(1, 70_001), (70_001, 1), (2, 255), (257, 3), (256, 40_000), (255, 40_193),
+                                   (40_193, 257), (3_000, 20_000), (524_289, 5), (5, 600_000), (300, 300_000)])
+def test_unequal_clouds_vs_oracle(ev, oracle, na, nb):
+    import torch
+    from paper_2512_10386_amd import binding as B
+    a, b = cloud(na, 1), cloud(nb, 2)
+    at, bt = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+    print(f"[unequal] {na} {nb}", flush=True)
+    idx, d2 = ev.nearest(at, bt)
+    ri, rd = oracle.nearest(a, b)
+    assert np.array_equal(idx.cpu().numpy().view(np.uint32), ri)
+    assert np.array_equal(d2.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+    exp = oracle.eval_metrics(a, b)
+    assert np.allclose(ev.metrics(at, bt).cpu().numpy(), exp, rtol=1e-12, atol=0)
+    # the smallest workspace accepted
+    least = -(-8 * na // 256) * 256 + -(-8 * nb // 256) * 256 + 2 * 65536
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    out = torch.empty(4, dtype=torch.float64, device="cuda")
+    B.gdn_eval_metrics(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, out.data_ptr(),
+                       torch.cuda.current_stream().cuda_stream)
+    assert np.allclose(out.cpu().numpy(), exp, rtol=1e-12, atol=0)
