@@ -272,10 +272,12 @@ gdn_status gdn_fit_loss_grad(gdn_ctx *ctx, const gdn_fit_params *fp, const float
  * gdn_nearest: for every point of a [na][3] its nearest point of b [nb][3],
  *   exact over all pairs, fp32 squared distance (dx*dx + dy*dy) + dz*dz, ties
  *   to the smaller index: idx [na] uint32, d2 [na] float (device arrays). A
- *   query with a NaN coordinate gets idx 0, d2 +inf. With a workspace of
- *   gdn_eval_workspace_size(na, nb) bytes the clouds are sorted and most pairs
- *   skipped (same results); with less (gdn_nearest_workspace_size at least)
- *   every pair is evaluated.
+ *   query with a NaN coordinate gets idx 0, d2 +inf. A workspace of
+ *   gdn_nearest_workspace_size(na) bytes is enough, and every pair is evaluated
+ *   then. With gdn_nearest_best_workspace_size(na, nb) bytes (or
+ *   gdn_eval_workspace_size(na, nb)) the clouds are sorted and most pairs
+ *   skipped, with the same results, where that is faster; the size is the least
+ *   one where it is not.
  * gdn_eval_metrics: clean [nc][3] against denoised [nd][3]; each point is
  *   matched to its nearest point of the other cloud, squared distances of
  *   the matched pairs in FP64; out DEVICE double[4]:
@@ -285,11 +287,13 @@ gdn_status gdn_fit_loss_grad(gdn_ctx *ctx, const gdn_fit_params *fp, const float
  *     PSNR = 10 log10(M^2 / MSE) dB with M the diagonal of the clean cloud's
  *     bounding box (Eq. 29); +inf when MSE = 0.
  * Both need 1 <= na, nb, nc, nd <= 2^30-1 (GDN_EINVAL / GDN_ECAPACITY) and a
- * 256-byte aligned workspace of the reported size. (gdn_eval_metrics also
- * takes a smaller one, from 8 bytes per point of both clouds and 132 KB on,
- * and then evaluates every pair; GDN_ENOMEM below that.)
+ * 256-byte aligned workspace of the reported size; the sizes never fall as the
+ * clouds grow. (gdn_eval_metrics also takes a smaller one, from 8 bytes per
+ * point of both clouds and 132 KB on, and then evaluates every pair; GDN_ENOMEM
+ * below that.)
  */
 gdn_status gdn_nearest_workspace_size(gdn_ctx *ctx, int64_t na, size_t *bytes);
+gdn_status gdn_nearest_best_workspace_size(gdn_ctx *ctx, int64_t na, int64_t nb, size_t *bytes);
 gdn_status gdn_nearest(gdn_ctx *ctx, const float *a, int64_t na, const float *b, int64_t nb,
                        void *workspace, size_t workspace_bytes, uint32_t *idx, float *d2, void *stream);
 gdn_status gdn_eval_workspace_size(gdn_ctx *ctx, int64_t nc, int64_t nd, size_t *bytes);

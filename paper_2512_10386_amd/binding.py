@@ -99,6 +99,7 @@ def lib():
         L.gdn_debug_dump.argtypes = [vp, C.c_int, vp, sz, vp]
         L.gdn_fit_workspace_size.argtypes = [vp, i64, C.POINTER(sz)]
         L.gdn_nearest_workspace_size.argtypes = [vp, i64, C.POINTER(sz)]
+        L.gdn_nearest_best_workspace_size.argtypes = [vp, i64, i64, C.POINTER(sz)]
         L.gdn_nearest.argtypes = [vp, vp, i64, vp, i64, vp, sz, vp, vp, vp]
         L.gdn_eval_workspace_size.argtypes = [vp, i64, i64, C.POINTER(sz)]
         L.gdn_eval_metrics.argtypes = [vp, vp, i64, vp, i64, vp, sz, vp, vp]
@@ -113,6 +114,7 @@ def lib():
                   "gdn_debug_dump", "gdn_set_timing", "gdn_timing", "gdn_workspace_size_batch",
                   "gdn_denoise_batch", "gdn_graph_create", "gdn_graph_launch", "gdn_autotune",
                   "gdn_fit_workspace_size", "gdn_fit_loss_grad", "gdn_nearest_workspace_size",
+                  "gdn_nearest_best_workspace_size",
                   "gdn_nearest", "gdn_eval_workspace_size", "gdn_eval_metrics",
                   "gdn_server_create", "gdn_server_info", "gdn_server_submit", "gdn_server_poll"):
             getattr(L, f).restype = C.c_int
@@ -256,6 +258,12 @@ def gdn_nearest_workspace_size(ctx, na) -> int:
     b = C.c_size_t()
     _check(ctx, lib().gdn_nearest_workspace_size(ctx, na, C.byref(b)))
     return b.value
+
+
+def gdn_nearest_best_workspace_size(ctx, na, nb) -> int:
+    out = C.c_size_t()
+    _check(ctx, lib().gdn_nearest_best_workspace_size(ctx, na, nb, C.byref(out)))
+    return out.value
 
 
 def gdn_nearest(ctx, a, na, b, nb, ws, ws_bytes, idx, d2, stream) -> None:

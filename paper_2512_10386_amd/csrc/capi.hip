@@ -654,6 +654,15 @@ gdn_status gdn_nearest_workspace_size(gdn_ctx* ctx, int64_t na, size_t* bytes) {
     return GDN_OK;
 }
 
+gdn_status gdn_nearest_best_workspace_size(gdn_ctx* ctx, int64_t na, int64_t nb, size_t* bytes) {
+    if (!bytes) return fail(ctx, GDN_EINVAL, "bytes is NULL");
+    gdn_status e = cloud_size(ctx, na, "the query cloud");
+    if (e == GDN_OK) e = cloud_size(ctx, nb, "the reference cloud");
+    if (e != GDN_OK) return e;
+    *bytes = gdn::nearest_best_workspace_bytes((uint32_t)na, (uint32_t)nb);
+    return GDN_OK;
+}
+
 gdn_status gdn_nearest(gdn_ctx* ctx, const float* a, int64_t na, const float* b, int64_t nb, void* workspace,
                        size_t workspace_bytes, uint32_t* idx, float* d2, void* stream) {
     if (!ctx) return GDN_EINVAL;

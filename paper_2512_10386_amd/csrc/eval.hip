@@ -26,10 +26,6 @@ namespace {
 constexpr int NN_BLOCK = 256;
 constexpr int NN_TILE = 256;                // reference points per LDS tile (short, so that small clouds make many blocks)
 constexpr unsigned NN_MIN_BLOCKS = 2048;    // split the reference until the grid has this many blocks
-// Fewer pairs than this over all directions: brute force (its four launches
-// and the pairs against the sort's eight to ten: an object frame of 14k points
-// 73 and 70 us for the metrics, 9k points 37 and 70 us, 20k points 127 and 73 us).
-constexpr uint64_t NN_GROUPS_MIN_PAIRS = 220'000'000ull;
 constexpr int EV_BLOCK = 256;
 constexpr unsigned EV_BLOCKS_MAX = 1024;
 constexpr int EV_STRIDE = 8;                // doubles per block partial
@@ -984,16 +980,62 @@ void nn_search(const NnPlan& P, uint32_t* idx, float* d2, hipStream_t st) {
                        P, idx, d2);
 }
 
-// Whether the search goes by groups: enough pairs, and a workspace that
-// holds the sorted clouds.
+// Whether sorting pays for na queries in nb points (1 direction) or both clouds
+// in each other (2). Brute force takes 0.21 us a million pairs; the sort and the
+// search of groups are eight to ten launches, 55 to 70 us, and then some 0.24 us
+// a thousand queries and 0.07 a thousand reference points; few queries or few
+// reference points spread them over less of the chip. Brute force against
+// groups, on a shell and a LiDAR sweep: nearest 15000 in 15000 points 58 us and
+// 55 / 67, 18000 in 18000 82 and 57 / 69; 3000 in 100k 78 and 88 / 109, 5000 in
+// 100k 118 and 108; 100 in 10M 540 and 713, 700 in 3M 474 and 275; 100k in 3000
+// 73 and 86 / 117, 300k in 3000 196 and 135 / 167; 10M in 300 608 and 2047, 10M
+// in 1500 2730 and 2104; metrics of 11500 and 11500 points 66 and 59 / 70, 12500
+// and 12500 80 and 59 / 74, 3000 and 50k 78 and 90 / 102, 1M and 1000 405 and
+// 316 / 343, 1M and 500 212 and 310.
+constexpr uint32_t NN_EVEN = 8;  // clouds up to this many times the size of the other
+bool nn_groups_pay(uint32_t na, uint32_t nb, uint32_t directions) {
+    const uint64_t pairs = (uint64_t)na * nb * directions;
+    if (directions == 2u) return pairs >= 260'000'000ull + 1300ull * ((uint64_t)na + nb);
+    const bool even = std::max(na, nb) / NN_EVEN <= std::min(na, nb);
+    return pairs >= (even ? 240'000'000ull : 310'000'000ull) + 1100ull * na + 300ull * nb;
+}
+
+// Whether it pays for any two clouds up to these sizes, for the workspaces: where
+// it pays at all it pays for all larger clouds, but for even ones that grow
+// uneven.
+bool nn_groups_pay_within(uint32_t na, uint32_t nb, uint32_t directions) {
+    constexpr uint32_t most = NN_EVEN, rest = NN_EVEN - 1u;  // the largest even clouds within
+    return nn_groups_pay(na, nb, directions) ||
+           nn_groups_pay((uint32_t)std::min<uint64_t>(na, (uint64_t)most * nb + rest),
+                         (uint32_t)std::min<uint64_t>(nb, (uint64_t)most * na + rest), directions);
+}
+
+// Whether the search goes by groups: it pays, and the workspace holds the
+// sorted clouds.
 bool nn_by_groups(uint32_t na, uint32_t nb, uint32_t directions, size_t ws_bytes) {
-    if ((uint64_t)na * nb * directions < NN_GROUPS_MIN_PAIRS) return false;
-    return nn_plan(nullptr, na, nullptr, nb, nullptr).bytes <= ws_bytes;
+    return nn_groups_pay(na, nb, directions) && nn_plan(nullptr, na, nullptr, nb, nullptr).bytes <= ws_bytes;
+}
+
+// Workspace bytes of the groups: the largest layout of any two clouds up to
+// these sizes. (Just below an edge of the radix tiles there are more tiles, and
+// look-back words, than just above it, and a workspace kept for larger clouds
+// must not send those to brute force.)
+size_t nn_groups_bytes(uint32_t na, uint32_t nb) {
+    size_t bytes = nn_plan(nullptr, na, nullptr, nb, nullptr).bytes;
+    for (const uint32_t edge : SORT_TILE_EDGES)
+        if (edge < std::max(na, nb))
+            bytes = std::max(bytes, nn_plan(nullptr, std::min(na, edge), nullptr, std::min(nb, edge), nullptr).bytes);
+    return bytes;
 }
 
 }  // namespace
 
 size_t nearest_workspace_bytes(uint32_t na) { return al256((size_t)8 * na); }
+
+size_t nearest_best_workspace_bytes(uint32_t na, uint32_t nb) {
+    const size_t brute = nearest_workspace_bytes(na);
+    return nn_groups_pay_within(na, nb, 1u) ? std::max(brute, nn_groups_bytes(na, nb)) : brute;
+}
 
 // Brute-force keys of one direction, or of both in one launch each.
 static void launch_nearest_keys(NnDir d0, NnDir d1, hipStream_t st) {
@@ -1036,15 +1078,10 @@ size_t eval_min_workspace_bytes(uint32_t nc, uint32_t nd) {
     return al256((size_t)8 * nc) + al256((size_t)8 * nd) + 2 * al256((size_t)8 * EV_STRIDE * EV_BLOCKS_MAX);
 }
 
-// The largest layout of any two clouds up to these sizes: just below an edge of
-// the radix tiles there are more tiles, and look-back words, than just above it,
-// and a workspace kept for larger clouds must not send those to brute force.
+// (enough for gdn_nearest too)
 size_t eval_workspace_bytes(uint32_t nc, uint32_t nd) {
-    size_t bytes = std::max(eval_min_workspace_bytes(nc, nd), nn_plan(nullptr, nc, nullptr, nd, nullptr).bytes);
-    for (const uint32_t edge : SORT_TILE_EDGES)
-        if (edge < std::max(nc, nd))
-            bytes = std::max(bytes, nn_plan(nullptr, std::min(nc, edge), nullptr, std::min(nd, edge), nullptr).bytes);
-    return bytes;
+    const size_t brute = eval_min_workspace_bytes(nc, nd);
+    return nn_groups_pay_within(nc, nd, 1u) || nn_groups_pay(nc, nd, 2u) ? std::max(brute, nn_groups_bytes(nc, nd)) : brute;
 }
 
 void launch_eval(const float* clean, uint32_t nc, const float* den, uint32_t nd, void* ws, size_t ws_bytes, double* out,

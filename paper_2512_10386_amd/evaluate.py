@@ -52,9 +52,7 @@ class Evaluator:
         """Nearest point of b for every point of a: (idx int32 view of uint32, fp32 d2)."""
         t = self.torch
         na, nb = a.shape[0], b.shape[0]
-        need = B.gdn_nearest_workspace_size(self.ctx, na)
-        if nb > 0:  # room for the sorted search
-            need = max(need, B.gdn_eval_workspace_size(self.ctx, na, nb))
+        need = B.gdn_nearest_best_workspace_size(self.ctx, na, nb)
         ws = t.empty(need, dtype=t.uint8, device=self.device)
         idx = t.empty(na, dtype=t.int32, device=self.device)
         d2 = t.empty(na, dtype=t.float32, device=self.device)

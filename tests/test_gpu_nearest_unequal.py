@@ -43,3 +43,24 @@ def test_unequal_clouds_vs_oracle(ev, oracle, na, nb):
     B.gdn_eval_metrics(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, out.data_ptr(),
                        torch.cuda.current_stream().cuda_stream)
     assert np.allclose(out.cpu().numpy(), exp, rtol=1e-12, atol=0)
+
+
+# both sides of the lines between sorting and evaluating every pair, the key
+# widths (2^15 points) and the radix tiles (7 * 2^14 and 2^20) with uneven clouds
+@pytest.mark.parametrize("na,nb,sorts", [
+    (32_768, 12_000, True), (32_769, 12_001, True), (1_048_577, 3_000, True), (3_000, 1_048_577, True),
+    (114_689, 4_500, True), (4_500, 114_688, True), (16_400, 16_400, True), (15_000, 15_000, False),
+    (100_000, 3_000, False), (3_000, 100_000, False), (1_048_577, 301, False)])
+def test_sorted_search_of_uneven_clouds(ev, na, nb, sorts):
+    import torch
+    from paper_2512_10386_amd import binding as B
+    at, bt = torch.from_numpy(cloud(na, 3)).cuda(), torch.from_numpy(cloud(nb, 4)).cuda()
+    least = B.gdn_nearest_workspace_size(ev.ctx, na)
+    assert (B.gdn_nearest_best_workspace_size(ev.ctx, na, nb) > least) == sorts
+    print(f"[unequal] {na} {nb}", flush=True)
+    idx, d2 = ev.nearest(at, bt)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")  # every pair
+    ri, rd = torch.empty_like(idx), torch.empty_like(d2)
+    B.gdn_nearest(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, ri.data_ptr(), rd.data_ptr(),
+                  torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(idx, ri) and torch.equal(d2.view(torch.int32), rd.view(torch.int32))

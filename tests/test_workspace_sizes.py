@@ -72,3 +72,29 @@ def test_server_slot_runs_a_slightly_smaller_batch():
     finally:
         den.close()
         srv.close()
+
+
+def test_nearest_workspace_is_the_least_where_every_pair_is_evaluated():
+    """Few queries or few reference points do not pay for sorting millions of
+    others, and ask for no room to do it."""
+    from paper_2512_10386_amd import binding as B
+    for na, nb in ((1, 200_000_000), (2, 120_000_000), (200, 2_000_000), (2_000_000, 200), (20_000_000, 16),
+                   (1_000_000, 1000), (3000, 100_000), (5000, 5000)):
+        assert B.gdn_nearest_best_workspace_size(0, na, nb) == B.gdn_nearest_workspace_size(0, na), (na, nb)
+    for n in (500, 1_000_000):
+        least = 2 * (-(-8 * n // 256) * 256) + 2 * 65536
+        assert B.gdn_eval_workspace_size(0, 1_000_000, 16) < 2 * 8 * 1_000_000
+        assert (B.gdn_eval_workspace_size(0, n, n) > least) == (n > 500)
+    for na, nb in ((20_000, 20_000), (1_000_000, 3000), (3000, 1_000_000)):
+        best = B.gdn_nearest_best_workspace_size(0, na, nb)
+        assert B.gdn_nearest_workspace_size(0, na) < best <= B.gdn_eval_workspace_size(0, na, nb)
+
+
+def test_nearest_workspace_never_falls_as_clouds_grow():
+    from paper_2512_10386_amd import binding as B
+    ns = sorted({int(16 * 1.13 ** i) for i in range(110)} | {e + d for e in EDGES for d in (-1, 0, 1)})
+    for size in (B.gdn_nearest_best_workspace_size, B.gdn_eval_workspace_size):
+        for other in (5, 300, 2500, 16_000, 200_000, 5_000_000):
+            for pair in (lambda n: (n, other), lambda n: (other, n), lambda n: (n, n)):
+                sizes = [size(0, *pair(n)) for n in ns]
+                assert sizes == sorted(sizes), (size.__name__, other)
