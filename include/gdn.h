@@ -329,6 +329,11 @@ enum {
  * rows not defined for a point are filled with the padding values). */
 gdn_status gdn_debug_dump(gdn_ctx *ctx, int what, void *dst, size_t dst_bytes, void *stream);
 
+/* Test aid. While enabled, gdn_nearest and gdn_eval_metrics on this context run
+ * as if a wait of their sort had expired (which leaves the clouds unordered):
+ * every pair is evaluated from the clouds as given, with the same results. */
+gdn_status gdn_debug_lose_order(gdn_ctx *ctx, int enable);
+
 /* Profiling aid. With timing enabled, each gdn_denoise records HIP events on
  * its stream (call start, kNN kernel start, kNN kernel end, call end) into a
  * ring of the last 256 calls. gdn_timing reads call `back` (0 = the latest),

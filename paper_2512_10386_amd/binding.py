@@ -104,6 +104,7 @@ def lib():
         L.gdn_eval_workspace_size.argtypes = [vp, i64, i64, C.POINTER(sz)]
         L.gdn_eval_metrics.argtypes = [vp, vp, i64, vp, i64, vp, sz, vp, vp]
         L.gdn_fit_loss_grad.argtypes = [vp, C.POINTER(gdn_fit_params), vp, vp, i64, vp, sz, vp, vp]
+        L.gdn_debug_lose_order.argtypes = [vp, C.c_int]
         L.gdn_set_timing.argtypes = [vp, C.c_int]
         L.gdn_timing.argtypes = [vp, i64, C.POINTER(C.c_float), C.POINTER(C.c_float)]
         L.gdn_status_string.argtypes = [C.c_int]
@@ -114,7 +115,7 @@ def lib():
                   "gdn_debug_dump", "gdn_set_timing", "gdn_timing", "gdn_workspace_size_batch",
                   "gdn_denoise_batch", "gdn_graph_create", "gdn_graph_launch", "gdn_autotune",
                   "gdn_fit_workspace_size", "gdn_fit_loss_grad", "gdn_nearest_workspace_size",
-                  "gdn_nearest_best_workspace_size",
+                  "gdn_nearest_best_workspace_size", "gdn_debug_lose_order",
                   "gdn_nearest", "gdn_eval_workspace_size", "gdn_eval_metrics",
                   "gdn_server_create", "gdn_server_info", "gdn_server_submit", "gdn_server_poll"):
             getattr(L, f).restype = C.c_int
@@ -282,6 +283,10 @@ def gdn_eval_metrics(ctx, clean, nc, den, nd, ws, ws_bytes, out, stream) -> None
 
 def gdn_debug_dump(ctx, what, dst, dst_bytes, stream) -> None:
     _check(ctx, lib().gdn_debug_dump(ctx, what, dst, dst_bytes, stream))
+
+
+def gdn_debug_lose_order(ctx, enable: bool) -> None:
+    _check(ctx, lib().gdn_debug_lose_order(ctx, int(enable)))
 
 
 def gdn_set_timing(ctx, enable: bool) -> None:

@@ -27,6 +27,7 @@ struct gdn_ctx {
     gdn::Params last_prm{};
     bool has_last = false;
     bool timing = false;
+    bool lose_order = false;  // gdn_debug_lose_order
     std::vector<CallEvents> ring;
     int64_t timed_calls = 0;
 };
@@ -674,7 +675,8 @@ gdn_status gdn_nearest(gdn_ctx* ctx, const float* a, int64_t na, const float* b,
     if (workspace_bytes < gdn::nearest_workspace_bytes((uint32_t)na))
         return fail(ctx, GDN_ENOMEM, "workspace too small");
     DeviceGuard guard(ctx->device);
-    gdn::launch_nearest(a, (uint32_t)na, b, (uint32_t)nb, workspace, workspace_bytes, idx, d2, (hipStream_t)stream);
+    gdn::launch_nearest(a, (uint32_t)na, b, (uint32_t)nb, workspace, workspace_bytes, idx, d2,
+                        ctx->lose_order, (hipStream_t)stream);
     hipError_t he = hipGetLastError();
     if (he != hipSuccess) return fail(ctx, GDN_EHIP, hipGetErrorString(he));
     ctx->err.clear();
@@ -701,10 +703,17 @@ gdn_status gdn_eval_metrics(gdn_ctx* ctx, const float* clean, int64_t nc, const 
     if (workspace_bytes < gdn::eval_min_workspace_bytes((uint32_t)nc, (uint32_t)nd))
         return fail(ctx, GDN_ENOMEM, "workspace too small");
     DeviceGuard guard(ctx->device);
-    gdn::launch_eval(clean, (uint32_t)nc, den, (uint32_t)nd, workspace, workspace_bytes, out, (hipStream_t)stream);
+    gdn::launch_eval(clean, (uint32_t)nc, den, (uint32_t)nd, workspace, workspace_bytes, out, ctx->lose_order,
+                     (hipStream_t)stream);
     hipError_t he = hipGetLastError();
     if (he != hipSuccess) return fail(ctx, GDN_EHIP, hipGetErrorString(he));
     ctx->err.clear();
+    return GDN_OK;
+}
+
+gdn_status gdn_debug_lose_order(gdn_ctx* ctx, int enable) {
+    if (!ctx) return GDN_EINVAL;
+    ctx->lose_order = enable != 0;
     return GDN_OK;
 }
 

@@ -629,7 +629,7 @@ __device__ __forceinline__ bool nn_best_of(float d, float id, uint32_t lane, flo
 // q, its key and whether its coordinates are finite: others match nothing).
 // best = +inf and bi = 0 if there is no match (as brute force: no distance
 // below +inf). Returns false, with the best among the seeds, for a hard tile.
-__device__ __forceinline__ bool nn_tile(const NnCloud& b, bool bad_order, float4 q, uint32_t key, bool fin,
+__device__ __forceinline__ bool nn_tile(const NnCloud& b, bool lost, float4 q, uint32_t key, bool fin,
                                         uint32_t lane, float& best, uint32_t& bi) {
     best = fin ? INFINITY : -1.0f;
     bi = 0u;
@@ -640,7 +640,7 @@ __device__ __forceinline__ bool nn_tile(const NnCloud& b, bool bad_order, float4
             bi = id;
         }
     };
-    if (bad_order) {
+    if (lost) {  // every pair
         for (uint32_t j = 0; j < b.n; ++j)
             take(b.p[3 * (size_t)j], b.p[3 * (size_t)j + 1], b.p[3 * (size_t)j + 2], j);
         return true;
@@ -769,11 +769,15 @@ __global__ __launch_bounds__(256) void nn_tile_kernel(NnPlan P, uint32_t* __rest
     const uint32_t s = t * NN_TQ + lane;
     const bool in = lane < NN_TQ && s < a.n;
     const uint32_t sc = min(t * NN_TQ + min(lane, NN_TQ - 1u), a.n - 1u);
-    const float4 q = a.pos[sc];
+    // without an order the tile is of the cloud as it came, each query once
+    const bool lost = *P.flag != 0u;
+    float4 q = a.pos[sc];
+    if (lost)
+        q = make_float4(a.p[3 * (size_t)sc], a.p[3 * (size_t)sc + 1], a.p[3 * (size_t)sc + 2], __uint_as_float(sc));
     const bool fin = in && isfinite(q.x) && isfinite(q.y) && isfinite(q.z);
     float best;
     uint32_t bi;
-    const bool done = nn_tile(b, *P.flag != 0u, q, a.key[0][sc], fin, lane, best, bi);
+    const bool done = nn_tile(b, lost, q, a.key[0][sc], fin, lane, best, bi);
     if (!done) {
         if (in) a.seed[s] = make_uint2(__float_as_uint(best), bi);
         if (lane == 0u) a.hard[atomicAdd(a.n_hard, 1u)] = t;
@@ -957,12 +961,16 @@ __global__ __launch_bounds__(1024) void nn_metrics_kernel(NnPlan P, bool two, do
 }
 static_assert(NN_BOX_BLOCKS <= 256, "the metrics kernel reads one box record per thread of four waves");
 
-// Hilbert order, groups and boxes of both clouds.
-void nn_sort(const NnPlan& P, hipStream_t st) {
+__global__ void nn_lose_kernel(uint32_t* flag) { *flag = 1u; }
+
+// Hilbert order, groups and boxes of both clouds. `lose`: no order is made, as
+// if a wait of the radix passes had expired.
+void nn_sort(const NnPlan& P, bool lose, hipStream_t st) {
     hipLaunchKernelGGL(nn_box_kernel, dim3(P.c[0].box_blocks + P.c[1].box_blocks), dim3(256), 0, st, P);
     hipLaunchKernelGGL(P.passes == 3 ? nn_key_kernel<3> : nn_key_kernel<NN_PASSES_MAX>,
                        dim3(P.c[0].key_blocks + P.c[1].key_blocks), dim3(256), 0, st, P);
-    for (int pass = 0; pass < P.passes; ++pass) {
+    if (lose) hipLaunchKernelGGL(nn_lose_kernel, dim3(1), dim3(1), 0, st, P.flag);
+    for (int pass = 0; pass < P.passes && !lose; ++pass) {
         auto kern = P.tile == 1024u ? (pass == 0 ? nn_radix_kernel<4, 256, true> : nn_radix_kernel<4, 256, false>)
                     : P.tile == 2048u ? (pass == 0 ? nn_radix_kernel<4, 512, true> : nn_radix_kernel<4, 512, false>)
                                       : (pass == 0 ? nn_radix_kernel<8, 512, true> : nn_radix_kernel<8, 512, false>);
@@ -1060,10 +1068,10 @@ static void launch_nearest_keys(NnDir d0, NnDir d1, hipStream_t st) {
 }
 
 void launch_nearest(const float* a, uint32_t na, const float* b, uint32_t nb, void* ws, size_t ws_bytes, uint32_t* idx,
-                    float* d2, hipStream_t st) {
+                    float* d2, bool lose_order, hipStream_t st) {
     if (nn_by_groups(na, nb, 1u, ws_bytes)) {
         const NnPlan P = nn_plan(a, na, b, nb, (char*)ws);
-        nn_sort(P, st);
+        nn_sort(P, lose_order, st);
         nn_search<false>(P, idx, d2, st);
         return;
     }
@@ -1085,10 +1093,10 @@ size_t eval_workspace_bytes(uint32_t nc, uint32_t nd) {
 }
 
 void launch_eval(const float* clean, uint32_t nc, const float* den, uint32_t nd, void* ws, size_t ws_bytes, double* out,
-                 hipStream_t st) {
+                 bool lose_order, hipStream_t st) {
     if (nn_by_groups(nc, nd, 2u, ws_bytes)) {
         const NnPlan P = nn_plan(clean, nc, den, nd, (char*)ws);
-        nn_sort(P, st);
+        nn_sort(P, lose_order, st);
         nn_search<true>(P, nullptr, nullptr, st);
         auto sums = [](uint32_t t) { return (t + NN_SUM_TILES - 1) / NN_SUM_TILES; };
         const bool two = P.c[0].qtiles > NN_SUM_TILES || P.c[1].qtiles > NN_SUM_TILES;

@@ -57,15 +57,15 @@ void launch_fit(const Plan& P, const float* xyz, const uint8_t* label, const Fit
 
 // eval.hip: exact nearest neighbours between clouds, PSNR / Chamfer metrics
 // (the least workspace evaluates every pair; the other sizes hold the sorted
-// clouds where sorting pays)
+// clouds where sorting pays). lose_order: as if a wait of the sort had expired.
 size_t nearest_workspace_bytes(uint32_t na);
 size_t nearest_best_workspace_bytes(uint32_t na, uint32_t nb);
 void launch_nearest(const float* a, uint32_t na, const float* b, uint32_t nb, void* ws, size_t ws_bytes, uint32_t* idx,
-                    float* d2, hipStream_t st);
+                    float* d2, bool lose_order, hipStream_t st);
 size_t eval_min_workspace_bytes(uint32_t nc, uint32_t nd);
 size_t eval_workspace_bytes(uint32_t nc, uint32_t nd);
 void launch_eval(const float* clean, uint32_t nc, const float* den, uint32_t nd, void* ws, size_t ws_bytes, double* out,
-                 hipStream_t st);
+                 bool lose_order, hipStream_t st);
 
 // The device status word of a pass: the Counters block opens the workspace.
 inline const uint32_t* status_word(const void* workspace) {

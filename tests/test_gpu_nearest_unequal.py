@@ -64,3 +64,35 @@ def test_sorted_search_of_uneven_clouds(ev, na, nb, sorts):
     B.gdn_nearest(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, ri.data_ptr(), rd.data_ptr(),
                   torch.cuda.current_stream().cuda_stream)
     assert torch.equal(idx, ri) and torch.equal(d2.view(torch.int32), rd.view(torch.int32))
+
+
+def test_lost_order_answers_every_query(ev, oracle):
+    """Where a wait of the sort expires there is no order to go by: each query
+    is still answered once, and the metrics sum each point once."""
+    import torch
+    from paper_2512_10386_amd import binding as B
+    a, b = cloud(18_003, 5), cloud(17_001, 6)
+    a[7, 1] = np.nan
+    at, bt = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+    at2 = at[8:].contiguous()
+    assert B.gdn_nearest_best_workspace_size(ev.ctx, len(a), len(b)) > B.gdn_nearest_workspace_size(ev.ctx, len(a))
+    want, metrics = ev.nearest(at, bt), ev.metrics(at2, bt).cpu().numpy()
+    need = B.gdn_eval_workspace_size(ev.ctx, len(a), len(b))
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")  # no order of an earlier call
+    idx = torch.full((len(a),), -1, dtype=torch.int32, device="cuda")
+    d2 = torch.full((len(a),), -1.0, dtype=torch.float32, device="cuda")
+    out = torch.empty(4, dtype=torch.float64, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    B.gdn_debug_lose_order(ev.ctx, True)
+    try:
+        print("[lost order]", flush=True)
+        B.gdn_nearest(ev.ctx, at.data_ptr(), len(a), bt.data_ptr(), len(b), ws.data_ptr(), need, idx.data_ptr(),
+                      d2.data_ptr(), st)
+        ws2 = torch.zeros_like(ws)
+        B.gdn_eval_metrics(ev.ctx, at2.data_ptr(), len(at2), bt.data_ptr(), len(b), ws2.data_ptr(), need,
+                           out.data_ptr(), st)
+    finally:
+        B.gdn_debug_lose_order(ev.ctx, False)
+    assert torch.equal(idx, want[0]) and torch.equal(d2.view(torch.int32), want[1].view(torch.int32))
+    assert np.allclose(out.cpu().numpy(), metrics, rtol=1e-12, atol=0)
+    assert np.allclose(out.cpu().numpy(), oracle.eval_metrics(a[8:], b), rtol=1e-12, atol=0)
