@@ -760,7 +760,8 @@ __device__ __forceinline__ double nn_dist64(const NnCloud& b, uint32_t bi, const
 template <bool EVAL>
 __global__ __launch_bounds__(256) void nn_tile_kernel(NnPlan P, uint32_t* __restrict__ idx, float* __restrict__ d2) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t w = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t w = (blockIdx.y * gridDim.x + blockIdx.x) * 4u +
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool back = EVAL && w >= P.c[0].qtiles;
     const NnCloud& a = P.c[back ? 1 : 0];
     const NnCloud& b = P.c[back ? 0 : 1];
@@ -983,7 +984,11 @@ void nn_sort(const NnPlan& P, bool lose, hipStream_t st) {
 template <bool EVAL>
 void nn_search(const NnPlan& P, uint32_t* idx, float* d2, hipStream_t st) {
     const uint32_t tiles = P.c[0].qtiles + (EVAL ? P.c[1].qtiles : 0u);
-    hipLaunchKernelGGL(nn_tile_kernel<EVAL>, dim3((tiles + 3u) / 4u), dim3(256), 0, st, P, idx, d2);
+    // (a grid dimension holds fewer than 2^32 threads, and a query takes four)
+    constexpr uint32_t ROW = 1u << 22;
+    const uint32_t blocks = (tiles + 3u) / 4u;
+    hipLaunchKernelGGL(nn_tile_kernel<EVAL>, dim3(std::min(blocks, ROW), (blocks + ROW - 1u) / ROW), dim3(256), 0, st, P,
+                       idx, d2);
     hipLaunchKernelGGL(nn_far_kernel<EVAL>, dim3(tiles < NN_FAR_BLOCKS ? tiles : NN_FAR_BLOCKS), dim3(64 * NN_TQ), 0, st,
                        P, idx, d2);
 }
