@@ -262,6 +262,8 @@ constexpr uint32_t NN_SHORT_N = 1u << 15;       // clouds up to this size: 8 key
 constexpr uint32_t NN_BOX_BLOCKS = 256;         // box records per cloud, at most
 constexpr int NN_REC = 12;                      // floats per box record: finite min, max, then min, max of all points
 constexpr uint32_t NN_FAR_BLOCKS = 512;         // far kernel: 16 waves each
+constexpr uint32_t NN_FAR_MOST = 48;            // far kernel: groups one query evaluates by itself, at most,
+constexpr uint32_t NN_FAR_SHARE = 16;           // or this share of all, if that is more
 constexpr uint32_t NN_SUM_TILES = 1u << 14;     // tile sums one block adds up
 
 struct NnBox {
@@ -612,7 +614,7 @@ __device__ __forceinline__ float nn_dist(float cx, float cy, float cz, float x, 
 // distance itself only a smaller index counts.
 __device__ __forceinline__ bool nn_best_of(float d, float id, uint32_t lane, float& bj, uint32_t& ij) {
     if (__builtin_amdgcn_ballot_w64(d <= bj) == 0ull) return false;
-    const float m = wave_min(d, lane);
+    const float m = wave_fmin(d);
     if (!(m < INFINITY)) return false;
     unsigned long long at = __builtin_amdgcn_ballot_w64(d == m);
     uint32_t i = m < bj ? 0xFFFFFFFFu : ij;
@@ -794,13 +796,68 @@ __global__ __launch_bounds__(256) void nn_tile_kernel(NnPlan P, uint32_t* __rest
     }
 }
 
+// The best of up to four queries of a hard tile (bits of `left`, which they are
+// taken from) over all points of b, by the whole workgroup: each lane takes
+// points of its wave's share and compares each with the four queries, then the
+// lanes' bests are combined in `key` (d2 bits, index). Ten instructions a pair
+// where one group after another takes fifty.
+__device__ __forceinline__ void nn_all_points(const NnCloud& b, uint32_t& left, const float4* s_pos,
+                                              unsigned long long* s_key, uint32_t lane, uint32_t wave) {
+    constexpr int N = 4;
+    uint32_t q[N], bi[N];
+    float x[N], y[N], z[N], bd[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        q[j] = left != 0u ? (uint32_t)__ffs((int)left) - 1u : q[0];  // (the first once more)
+        left &= left - 1u;
+        const float4 p = s_pos[q[j]];
+        const unsigned long long k = s_key[q[j]];
+        x[j] = lane_f32(p.x, 0u);  // (scalar registers)
+        y[j] = lane_f32(p.y, 0u);
+        z[j] = lane_f32(p.z, 0u);
+        bd[j] = __uint_as_float((uint32_t)(k >> 32));
+        bi[j] = (uint32_t)k;
+    }
+    // (whole groups of 64 points, NaN past the last)
+    const uint32_t groups = (b.n + (uint32_t)NN_GRP - 1u) / (uint32_t)NN_GRP;
+    for (uint32_t g = wave; g < groups; g += NN_TQ) {
+        const float4 c = b.pos[(size_t)g * NN_GRP + lane];
+        const uint32_t id = __float_as_uint(c.w);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const float d = nn_dist(c.x, c.y, c.z, x[j], y[j], z[j]);
+            if (d < bd[j] || (d == bd[j] && id < bi[j])) {
+                bd[j] = d;
+                bi[j] = id;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const unsigned long long k = wave_umin(((unsigned long long)__float_as_uint(bd[j]) << 32) | bi[j]);
+        if (lane == 0u) atomicMin(&s_key[q[j]], k);
+    }
+}
+
 // Queries of the hard tiles, a wave each: the nearest supers first, and in
 // each the nearest groups first, four at a time, until the next box is
-// farther than the best.
+// farther than the best. A query that has evaluated NN_FAR_MOST groups (or more,
+// by NN_FAR_SHARE) stops there: the points lie about as far from it in all
+// directions, or in no useful order. The workgroup then takes such queries of its
+// tile over all points together. It bounds what such clouds cost: 60000 queries
+// in the middle of a shell of 60000 points take 1290 us so, without it 4870, all
+// pairs 640. Clouds that lie apart stay below the line: 18000 points and 18000
+// take 115 us, with a line at 24 groups 204 (all pairs 77).
+// The minima over the wave go by DPP: with exchanges through the LDS unit two
+// calls took 73.1 and 148.7 us, so 71.3 and 144.8 (metrics of an object of 20k
+// points and a 120k sweep).
 template <bool EVAL>
-__global__ __launch_bounds__(64 * NN_TQ) void nn_far_kernel(NnPlan P, uint32_t* __restrict__ idx,
+__global__ __launch_bounds__(64 * NN_TQ, 8) void nn_far_kernel(NnPlan P, uint32_t* __restrict__ idx,
                                                             float* __restrict__ d2) {
     __shared__ double s_e[NN_TQ];
+    __shared__ float4 s_pos[NN_TQ];
+    __shared__ unsigned long long s_key[NN_TQ];
+    __shared__ uint32_t s_stop[NN_TQ];
     const uint32_t lane = threadIdx.x & 63u, wq = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t h0 = *P.c[0].n_hard, h1 = EVAL ? *P.c[1].n_hard : 0u;
     for (uint32_t h = blockIdx.x; h < h0 + h1; h += gridDim.x) {
@@ -809,20 +866,34 @@ __global__ __launch_bounds__(64 * NN_TQ) void nn_far_kernel(NnPlan P, uint32_t* 
         const NnCloud& b = P.c[back ? 0 : 1];
         const uint32_t t = a.hard[back ? h - h0 : h];
         const uint32_t s = t * NN_TQ + wq;
-        double e = 0.0;
+        float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+        float best = -1.0f;
+        uint32_t bi = 0;
+        bool fin = false, stop = false;
+        auto put = [&]() {  // the query's answer (lane 0)
+            if constexpr (EVAL) {
+                s_e[wq] = nn_dist64(b, bi, q);
+            } else {
+                const uint32_t i = __float_as_uint(q.w);
+                idx[i] = bi;
+                d2[i] = fin ? best : INFINITY;
+            }
+        };
         if (s < a.n) {
-            const float4 q = a.pos[s];
-            float best = __uint_as_float(a.seed[s].x);
-            uint32_t bi = a.seed[s].y;
-            const bool fin = best >= 0.0f;
-            for (uint32_t s0 = 0; fin && s0 < b.supers; s0 += 64u) {
+            q = a.pos[s];
+            best = __uint_as_float(a.seed[s].x);
+            bi = a.seed[s].y;
+            fin = best >= 0.0f;
+            const uint32_t most = max(NN_FAR_MOST, b.n / ((uint32_t)NN_GRP * NN_FAR_SHARE));
+            uint32_t seen = 0;  // groups evaluated
+            for (uint32_t s0 = 0; fin && !stop && s0 < b.supers; s0 += 64u) {
                 const bool sok = s0 + lane < b.supers;
                 const float sd = box_gap2(super_box(b, sok ? s0 + lane : s0), q.x, q.y, q.z, q.x, q.y, q.z);
                 unsigned long long left = __builtin_amdgcn_ballot_w64(sok);
-                while (left != 0ull) {
+                while (left != 0ull && !stop) {
                     // the nearest super left (an unordered distance, from NaN boxes there are none, counts as far)
                     const float ds = ((left >> lane) & 1ull) ? sd : INFINITY;
-                    const float ms = wave_min(ds, lane);
+                    const float ms = wave_fmin(ds);
                     if (ms > best) break;
                     const uint32_t l = (uint32_t)__ffsll((long long)(left & __builtin_amdgcn_ballot_w64(ds == ms))) - 1u;
                     left &= ~(1ull << l);
@@ -832,6 +903,10 @@ __global__ __launch_bounds__(64 * NN_TQ) void nn_far_kernel(NnPlan P, uint32_t* 
                     unsigned long long lg = ~0ull;
                     bool more = true;
                     while (more && lg != 0ull) {
+                        if (seen >= most) {
+                            stop = true;
+                            break;
+                        }
                         constexpr int NB = 4;
                         float4 c[NB];
                         float dg[NB];
@@ -840,7 +915,7 @@ __global__ __launch_bounds__(64 * NN_TQ) void nn_far_kernel(NnPlan P, uint32_t* 
 #pragma unroll
                         for (int u = 0; u < NB; ++u) {
                             const float dl = ((lg >> lane) & 1ull) ? gd : INFINITY;
-                            dg[u] = wave_min(dl, lane);
+                            dg[u] = wave_fmin(dl);
                             const unsigned long long m = lg & __builtin_amdgcn_ballot_w64(dl == dg[u]);
                             if (!more || m == 0ull || dg[u] > best) {
                                 more = false;
@@ -851,6 +926,7 @@ __global__ __launch_bounds__(64 * NN_TQ) void nn_far_kernel(NnPlan P, uint32_t* 
                                 ++nb;
                             }
                         }
+                        seen += (uint32_t)nb;
 #pragma unroll
                         for (int u = 0; u < NB; ++u) {
                             if (u >= nb || dg[u] > best) break;
@@ -859,24 +935,38 @@ __global__ __launch_bounds__(64 * NN_TQ) void nn_far_kernel(NnPlan P, uint32_t* 
                     }
                 }
             }
-            if constexpr (EVAL) {
-                e = nn_dist64(b, bi, q);
-            } else if (lane == 0u) {
-                const uint32_t i = __float_as_uint(q.w);
-                idx[i] = bi;
-                d2[i] = fin ? best : INFINITY;
+            if (lane == 0u) {
+                if (stop) {
+                    s_pos[wq] = q;
+                    s_key[wq] = ((unsigned long long)__float_as_uint(best) << 32) | bi;
+                } else {
+                    put();
+                }
             }
+        } else if (EVAL && lane == 0u) {
+            s_e[wq] = 0.0;
+        }
+        if (lane == 0u) s_stop[wq] = stop ? 1u : 0u;
+        __syncthreads();
+        uint32_t open = (uint32_t)__builtin_amdgcn_ballot_w64(lane < NN_TQ && s_stop[lane % NN_TQ] != 0u);
+        if (open != 0u) {
+            while (open != 0u) nn_all_points(b, open, s_pos, s_key, lane, wq);
+            __syncthreads();
+            if (stop && lane == 0u) {
+                best = __uint_as_float((uint32_t)(s_key[wq] >> 32));
+                bi = (uint32_t)s_key[wq];
+                put();
+            }
+            __syncthreads();
         }
         if constexpr (EVAL) {
-            if (lane == 0u) s_e[wq] = e;
-            __syncthreads();
             if (threadIdx.x == 0) {
                 double sum = 0.0;
                 for (uint32_t i = 0; i < NN_TQ; ++i) sum += s_e[i];
                 a.part[t] = sum;
             }
-            __syncthreads();
         }
+        __syncthreads();  // the LDS words are rewritten for the next tile
     }
 }
 

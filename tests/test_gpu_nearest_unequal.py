@@ -96,3 +96,40 @@ def test_lost_order_answers_every_query(ev, oracle):
     assert torch.equal(idx, want[0]) and torch.equal(d2.view(torch.int32), want[1].view(torch.int32))
     assert np.allclose(out.cpu().numpy(), metrics, rtol=1e-12, atol=0)
     assert np.allclose(out.cpu().numpy(), oracle.eval_metrics(a[8:], b), rtol=1e-12, atol=0)
+
+
+# queries that have the reference at about one distance all around them: the
+# search of near groups first gives up, and the workgroup takes all points
+@pytest.mark.parametrize("na,nb", [(18_001, 18_003), (16_387, 40_000), (40_003, 16_385), (3_001, 200_003)])
+@pytest.mark.parametrize("what", ["middle", "copies", "some"])
+def test_reference_at_one_distance(ev, na, nb, what):
+    import torch
+    from paper_2512_10386_amd import binding as B
+    rng = np.random.default_rng(na + nb)
+    b = rng.normal(size=(nb, 3))
+    b = (b / np.linalg.norm(b, axis=1, keepdims=True)).astype(np.float32)
+    a = (1e-3 * rng.normal(size=(na, 3))).astype(np.float32)
+    if what == "copies":  # equal distances: the axis points, many times, from the centre
+        b = np.round(b / np.abs(b).max(1, keepdims=True)).astype(np.float32)
+        b[(b != 0).sum(1) != 1] = [0, 0, 1]
+        a[:: 3] = 0
+        a[5] = [np.nan, 0, 0]
+        a[7] = [np.inf, 0, 0]
+    elif what == "some":  # a few queries of a tile each
+        a[np.arange(na) % 5 != 0] += b[rng.integers(0, nb, int((np.arange(na) % 5 != 0).sum()))]
+    at, bt = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+    least = B.gdn_nearest_workspace_size(ev.ctx, na)
+    assert B.gdn_nearest_best_workspace_size(ev.ctx, na, nb) > least
+    print(f"[one distance] {what} {na} {nb}", flush=True)
+    idx, d2 = ev.nearest(at, bt)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")  # every pair
+    ri, rd = torch.empty_like(idx), torch.empty_like(d2)
+    st = torch.cuda.current_stream().cuda_stream
+    B.gdn_nearest(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, ri.data_ptr(), rd.data_ptr(), st)
+    assert torch.equal(idx, ri) and torch.equal(d2.view(torch.int32), rd.view(torch.int32))
+    if what != "copies":
+        least = -(-8 * na // 256) * 256 + -(-8 * nb // 256) * 256 + 2 * 65536
+        ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+        out = torch.empty(4, dtype=torch.float64, device="cuda")
+        B.gdn_eval_metrics(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, out.data_ptr(), st)
+        assert np.allclose(ev.metrics(at, bt).cpu().numpy(), out.cpu().numpy(), rtol=1e-12, atol=0)
