@@ -261,6 +261,7 @@ constexpr int NN_PASSES_MAX = 4;
 constexpr uint32_t NN_SHORT_N = 1u << 15;       // clouds up to this size: 8 key bits per axis (3 passes), else 10 (4)
 constexpr uint32_t NN_BOX_BLOCKS = 256;         // box records per cloud, at most
 constexpr int NN_REC = 12;                      // floats per box record: finite min, max, then min, max of all points
+constexpr float NN_TAIL = 16.0f;                // clouds reaching farther than this many times their middle half: see nn_key_kernel
 constexpr uint32_t NN_FAR_BLOCKS = 512;         // far kernel: 16 waves each
 constexpr uint32_t NN_FAR_MOST = 48;            // far kernel: groups one query evaluates by itself, at most,
 constexpr uint32_t NN_FAR_SHARE = 16;           // or this share of all, if that is more
@@ -298,6 +299,7 @@ struct NnPlan {
     char* zero;           // histograms, look-back words, flag
     size_t zero_bytes;
     uint32_t* flag;       // a look-back wait expired: the order is not usable
+    float* core;          // [4] medians of both clouds' coordinates, and the extent of their middle half
     size_t bytes;
 };
 
@@ -330,6 +332,7 @@ NnPlan nn_plan(const float* a, uint32_t na, const float* b, uint32_t nb, char* b
     }
     P.zero = base ? base + z0 : nullptr;
     P.zero_bytes = off - z0;
+    P.core = (float*)take(16);
     for (NnCloud& c : P.c) {
         const size_t padded = (size_t)c.supers * NN_SUP;
         for (int i = 0; i < 2; ++i) {
@@ -353,14 +356,40 @@ NnPlan nn_plan(const float* a, uint32_t na, const float* b, uint32_t nb, char* b
     return P;
 }
 
+// Medians and the extent of the middle half, per axis over 64 points taken at
+// equal steps from both clouds; a wave per axis. One workgroup calls it.
+__device__ void nn_core(const NnPlan& P, float* s_iqr) {
+    const uint32_t lane = threadIdx.x & 63u, axis = threadIdx.x >> 6;
+    if (axis < 3u) {
+        const NnCloud& c = P.c[lane & 1u];
+        const size_t i = (size_t)((uint64_t)(lane | 1u) * c.n / 64u);
+        const float x = c.p[3 * i + axis];
+        const uint32_t v = sort64_u32<true>(isfinite(x) ? f32_ordered(x) : 0xFFFFFFFFu, lane);
+        const float lo = f32_from_ordered((uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+        const float mid = f32_from_ordered((uint32_t)__builtin_amdgcn_readlane((int)v, 32));
+        const float hi = f32_from_ordered((uint32_t)__builtin_amdgcn_readlane((int)v, 47));
+        if (lane == 0u) {
+            P.core[axis] = mid;
+            s_iqr[axis] = hi - lo;
+        }
+    }
+    __syncthreads();
+    // (not a number on an axis where a quarter of the points is not finite: it does not count)
+    if (threadIdx.x == 0) P.core[3] = fmaxf(fmaxf(s_iqr[0], s_iqr[1]), s_iqr[2]);
+}
+
 // Boxes of both clouds, one record per block, and the control words cleared
-// (nothing here uses them).
+// (nothing here uses them). The last block takes nn_core.
 __global__ __launch_bounds__(256) void nn_box_kernel(NnPlan P) {
     __shared__ float s_v[4][NN_REC];
     uint4* z = (uint4*)P.zero;
     const size_t n16 = P.zero_bytes / 16;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
         z[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == gridDim.x - 1u) {
+        nn_core(P, s_v[0]);
+        return;
+    }
     const bool second = blockIdx.x >= P.c[0].box_blocks;
     const NnCloud& c = P.c[second ? 1 : 0];
     const uint32_t blk = second ? blockIdx.x - P.c[0].box_blocks : blockIdx.x;
@@ -433,14 +462,20 @@ __device__ __forceinline__ uint32_t hilbert3(uint32_t x, uint32_t y, uint32_t z)
 
 // Hilbert keys of both clouds in the cube at their common minimum (non-finite
 // coordinates quantise to a border cell: their points only need some place)
-// and the digit histograms.
+// and the digit histograms. A single stray point far out would leave all others
+// in one cell, without an order. Clouds that reach farther from their median than
+// NN_TAIL times the extent of their middle half take cells that grow with the
+// distance from it instead, the logarithm's (18000 against 18000 points, one of
+// them at a million times their size: 231 us all in one cell, 70 so, all pairs
+// 77; 200k against 200k 12.6 ms and 187 us).
 template <int PASSES>
 __global__ __launch_bounds__(256) void nn_key_kernel(NnPlan P) {
     __shared__ float s_lo[4][3], s_hi[4][3];
-    __shared__ float s_c[4];
+    __shared__ float s_c[5];
     __shared__ uint32_t s_hist[PASSES][256];
     constexpr int BITS = PASSES == 3 ? 8 : 10;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+    const float4 core = *(const float4*)P.core;
     for (int p = 0; p < PASSES; ++p) s_hist[p][tid] = 0u;
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int q = 0; q < 2; ++q)
@@ -459,7 +494,8 @@ __global__ __launch_bounds__(256) void nn_key_kernel(NnPlan P) {
     }
     __syncthreads();
     if (tid == 0u) {
-        float side = 0.0f;
+        const float mid[3] = {core.x, core.y, core.z};
+        float side = 0.0f, reach = 0.0f;
         for (int a = 0; a < 3; ++a) {
             float l = s_lo[0][a], h = s_hi[0][a];
             for (int q = 1; q < 4; ++q) {
@@ -468,16 +504,28 @@ __global__ __launch_bounds__(256) void nn_key_kernel(NnPlan P) {
             }
             s_c[a] = l;
             side = fmaxf(side, h - l);
+            reach = fmaxf(reach, fmaxf(h - mid[a], mid[a] - l));
         }
         s_c[3] = side > 0.0f && side < INFINITY ? (float)(1 << BITS) / side : 0.0f;
+        s_c[4] = 0.0f;
+        if (core.w > 0.0f && reach > NN_TAIL * core.w && reach < INFINITY) {
+            for (int a = 0; a < 3; ++a) s_c[a] = mid[a];
+            s_c[3] = (float)(1 << (BITS - 1)) / log2f(1.0f + reach / core.w);
+            s_c[4] = 1.0f / core.w;
+        }
     }
     __syncthreads();
-    const float c0 = s_c[0], c1 = s_c[1], c2 = s_c[2], sc = s_c[3];
+    const float c0 = s_c[0], c1 = s_c[1], c2 = s_c[2], sc = s_c[3], per = s_c[4];
     const bool second = blockIdx.x >= P.c[0].key_blocks;
     const NnCloud& c = P.c[second ? 1 : 0];
     const uint32_t blk = second ? blockIdx.x - P.c[0].key_blocks : blockIdx.x;
     auto q10 = [&](float x, float l) {
-        return (uint32_t)fminf(fmaxf((x - l) * sc, 0.0f), (float)((1 << BITS) - 1));
+        float t = (x - l) * sc;
+        if (per != 0.0f) {
+            const float u = log2f(1.0f + fabsf(x - l) * per) * sc;
+            t = (float)(1 << (BITS - 1)) + (x < l ? -u : u);
+        }
+        return (uint32_t)fminf(fmaxf(t, 0.0f), (float)((1 << BITS) - 1));
     };
     const uint32_t stride = c.key_blocks * 256u;
     constexpr int U = 4;
@@ -1057,7 +1105,7 @@ __global__ void nn_lose_kernel(uint32_t* flag) { *flag = 1u; }
 // Hilbert order, groups and boxes of both clouds. `lose`: no order is made, as
 // if a wait of the radix passes had expired.
 void nn_sort(const NnPlan& P, bool lose, hipStream_t st) {
-    hipLaunchKernelGGL(nn_box_kernel, dim3(P.c[0].box_blocks + P.c[1].box_blocks), dim3(256), 0, st, P);
+    hipLaunchKernelGGL(nn_box_kernel, dim3(P.c[0].box_blocks + P.c[1].box_blocks + 1u), dim3(256), 0, st, P);
     hipLaunchKernelGGL(P.passes == 3 ? nn_key_kernel<3> : nn_key_kernel<NN_PASSES_MAX>,
                        dim3(P.c[0].key_blocks + P.c[1].key_blocks), dim3(256), 0, st, P);
     if (lose) hipLaunchKernelGGL(nn_lose_kernel, dim3(1), dim3(1), 0, st, P.flag);

@@ -133,3 +133,41 @@ def test_reference_at_one_distance(ev, na, nb, what):
         out = torch.empty(4, dtype=torch.float64, device="cuda")
         B.gdn_eval_metrics(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, out.data_ptr(), st)
         assert np.allclose(ev.metrics(at, bt).cpu().numpy(), out.cpu().numpy(), rtol=1e-12, atol=0)
+
+
+# a few points, or many, far outside the others: the cells of the sort grow with
+# the distance from the middle; copies, and clouds of which a half is not finite
+@pytest.mark.parametrize("na,nb", [(18_003, 17_001), (40_001, 36_003)])
+@pytest.mark.parametrize("what", ["one", "one_b", "many", "flat", "copies", "overflow", "nan"])
+def test_stray_points(ev, na, nb, what):
+    import torch
+    from paper_2512_10386_amd import binding as B
+    rng = np.random.default_rng(na)
+    a, b = cloud(na, 7), cloud(nb, 8)
+    if what == "one":
+        a[3] = [1e6, -2e5, 1e6]
+    elif what == "one_b":
+        b[nb - 1] = [-40.0, 300.0, 0.0]
+    elif what == "many":
+        a[::40], b[::50] = 1e4 * rng.normal(size=a[::40].shape), 1e5 * rng.normal(size=b[::50].shape)
+    elif what == "flat":
+        a[:, 2] = b[:, 2] = 1.5
+        b[0, 2] = 1e5
+    elif what == "copies":  # no extent of the middle half
+        a[: na * 3 // 4], b[: nb * 3 // 4] = a[0], a[0]
+        b[5] = 1e3
+    elif what == "overflow":
+        a[0], b[0] = 3e38, -3e38
+    else:
+        a[::2, 0], b[1::2, 1] = np.nan, np.inf
+        b[0] = 1e4
+    at, bt = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+    least = B.gdn_nearest_workspace_size(ev.ctx, na)
+    assert B.gdn_nearest_best_workspace_size(ev.ctx, na, nb) > least
+    print(f"[stray] {what} {na} {nb}", flush=True)
+    idx, d2 = ev.nearest(at, bt)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")  # every pair
+    ri, rd = torch.empty_like(idx), torch.empty_like(d2)
+    B.gdn_nearest(ev.ctx, at.data_ptr(), na, bt.data_ptr(), nb, ws.data_ptr(), least, ri.data_ptr(), rd.data_ptr(),
+                  torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(idx, ri) and torch.equal(d2.view(torch.int32), rd.view(torch.int32))
