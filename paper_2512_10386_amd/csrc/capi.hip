@@ -379,7 +379,7 @@ static gdn_status run(gdn_ctx* ctx, const gdn_params* p, const float* xyz, int64
     if (((uintptr_t)workspace & 255u) != 0) return fail(ctx, GDN_EINVAL, "workspace must be 256-byte aligned");
     gdn::Plan P = make_plan((uint32_t)n, (uint32_t)nf, p->k, (char*)workspace);
     if (workspace_bytes < P.bytes) return fail(ctx, GDN_ENOMEM, "workspace too small");
-    P.big_leaves = gdn::big_leaf_path(P.n, p->leaf_cap);
+    P.big_leaves = gdn::big_leaf_path(P.n, P.nf, p->leaf_cap);
     P.plan_halo = gdn::plan_in_halo(P.n, p->leaf_cap);
     const gdn::Params prm = to_params(p);
     CallEvents* ce = nullptr;

@@ -143,11 +143,23 @@ inline bool small_leaf_path(uint32_t n, int32_t leaf_cap) {
 // the selects themselves in one (larger) workgroup per leaf. Inputs with many
 // leaves fill the chip with the per-leaf kernels: 500k points at cap 4096 take
 // 1339 us with those, 1387 this way; 120k 490 and 426, 100k in one leaf 3598
-// and 733. (Over-full leaves at the depth limit of smaller caps stay with the
-// per-leaf kernels.)
-inline bool big_leaf_path(uint32_t n, int32_t leaf_cap) {
-    return n > SEL_LDS_MAX && (uint32_t)leaf_cap > SEL_LDS_MAX &&
-           (n <= (1u << 18) || (n <= (1u << 20) && (uint32_t)leaf_cap >= n / 16u));
+// and 733. Where frames are small, or split at once into leaves that are, there
+// are no big leaves after all: 1000 frames of 200 points 264 us with the per-leaf
+// kernels and 455 this way, 250 of 1000 306 and 385 (60 of 4000, each in one leaf,
+// 505 and 424); at cap 4096 50 frames of 5000 points 354 and 444, 20 of 10000 348
+// and 390 (10 of 20000 436 and 401); at cap 2100 a 120k object 254 and 324, 20k
+// 138 and 174 (at cap 4096 365 and 319, 262 and 197). A leaf holds an eighth of
+// its parent and more, up to the cap where the density varies, so only low caps
+// are judged by it. (Over-full leaves at the depth limit of smaller caps stay with
+// the per-leaf kernels.)
+constexpr uint32_t BIG_FRAME_MIN = 1024;   // smaller frames (on average): no big leaves
+constexpr uint32_t BIG_CAP_LOW = 4096;     // up to this cap,
+constexpr uint32_t BIG_SPLIT_MIN = 2400;   // an eighth of a frame or the cap, if not above this: none either
+inline bool big_leaf_path(uint32_t n, uint32_t nf, int32_t leaf_cap) {
+    const uint32_t cap = (uint32_t)leaf_cap, frame = n / nf;
+    if (n <= SEL_LDS_MAX || cap <= SEL_LDS_MAX || frame <= BIG_FRAME_MIN) return false;
+    if (frame > cap && cap <= BIG_CAP_LOW && (cap <= BIG_SPLIT_MIN || frame / 8u <= BIG_SPLIT_MIN)) return false;
+    return n <= (1u << 18) || (n <= (1u << 20) && cap >= n / 16u);
 }
 
 // Queries per kNN work item of inputs with n1 P1 points. A wave takes an
