@@ -201,10 +201,13 @@ inline bool plan_in_halo(uint32_t n, int32_t leaf_cap) {
 // per workgroup are read, ranked and written sooner; above, the look-back's
 // traffic (1 KB of status words per tile and round trip) weighs more. Whole
 // calls with tiles of 512 / 1024 / 2048 keys: 10k points 135.9 / 136.9 / 140.5
-// us, 20k 147.5 / 147.7 / 151.1, 80k 226 / 222.8 / 224.6, 120k - / 301.4 /
-// 300.2, 900k - / 875 / 863. 4096 keys, staged in LDS, by 512 threads of 8 keys
-// against 256 of 16 (the same LDS with twice the waves): 1.2M points 1051 and
-// 1042 us, 6.2M 3990 and 3948.
+// us, 20k 147.5 / 147.7 / 151.1, 80k 226 / 222.8 / 224.6; with 1024 / 2048, on a
+// sweep and a torus: 30k 137.7 / 139.1 and 131.4 / 134.4, 60k 164.1 / 164.4 and
+// 146.9 / 148.7, 90k 193.5 / 192.3 and 167.0 / 167.7, 114k 215.8 / 213.9 and 178.1
+// / 178.6, 130k 223.9 / 220.7 and 185.3 / 185.9 (from 60k on the two differ by
+// about what calls do); 900k 875 / 863. 4096 keys, staged in LDS, by 512 threads
+// of 8 keys against 256 of 16 (the same LDS with twice the waves): 1.2M points
+// 1051 and 1042 us, 6.2M 3990 and 3948.
 constexpr uint32_t SORT_TILE_EDGES[] = {1u << 14, 7u << 14, 1u << 20};  // the largest n of each tile but the last
 inline uint32_t sort_tile_for(uint32_t n) {
     uint32_t tile = 512u;

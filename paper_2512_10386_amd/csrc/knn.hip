@@ -1147,11 +1147,14 @@ void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st) {
     // items, where rebuilding the keys costs as much. Whole calls, keys against
     // positions: 250k points 292.6 and 296.8 us, 500k 464 and 465, 900k in
     // nine frames 742 and 735, 1.2M 941 and 942, 64 sweeps 3714 and 3697.
-    // Six waves per SIMD cost some spilled registers, which small inputs, whose
-    // waves are few, only lose by: 1501 points 69.2 us with five and 70.1 with
-    // six, 20k 132.1 and 131.2, 120k 264.6 and 261.3 (cap 256: 210.5 and 207.0).
-    // Large inputs with six / seven / eight (positions): 1.2M points 945 / 925 /
-    // 944 us, 64 sweeps 3709 / 3623 / 3696.
+    // Six waves per SIMD cost some spilled registers, which the smallest inputs,
+    // whose waves are few, only lose by; from there on it depends on the cloud
+    // which is ahead, by 1 %. Whole calls with five and six: 1501 points 69.2 and
+    // 70.1 us, 20k of a scanned object 125.7 and 124.9; a sweep and a torus, 16k
+    // 117.8 / 119.0 and 124.3 / 125.7, 30k 136.5 / 137.7 and 129.8 / 131.4, 60k
+    // 164.2 / 164.0 and 145.8 / 147.0, 90k 195.3 / 193.3 and 167.3 / 167.1, 130k
+    // 222.6 / 220.6 and 187.2 / 185.9. Large inputs with six / seven / eight
+    // (positions): 1.2M points 945 / 925 / 944 us, 64 sweeps 3709 / 3623 / 3696.
     constexpr uint32_t KNN_SIX_WAVES_MIN_N = 1u << 14;
     auto launch = [&](auto kern, bool pos, unsigned waves) {
         hipLaunchKernelGGL(kern, dim3((unsigned)(num_cus > 0 ? num_cus : 256) * 4u * waves), dim3(64),

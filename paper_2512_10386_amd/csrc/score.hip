@@ -479,7 +479,9 @@ __global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params p
 // leaves, a leaf cap within their size and no minimum leaf side, only copies
 // of one point make larger leaves, and the launch is one that finds none: with
 // fewer workgroups, and a voxel kernel told so by the one-wave kernel, 64 sweeps
-// take 3496 us a call instead of 3509, 1.2M points 903.5 instead of 906.7.
+// take 3496 us a call instead of 3509, 1.2M points 903.5 instead of 906.7. Where
+// copies do make such leaves, 2048 workgroups would be ahead: a 1M sweep with 500
+// places of 600 copies 1902 us and 1860, 300k with 300 of 400 851 and 822.
 static unsigned big_leaf_blocks(const Plan& P, const Params& prm, bool small) {
     if (small && (uint32_t)prm.leaf_cap <= SMALL_LEAF && !(prm.min_leaf_side > 0.0)) return 512u;
     return P.n < 2048u ? P.n : 2048u;
