@@ -409,7 +409,7 @@ static gdn_status run(gdn_ctx* ctx, const gdn_params* p, const float* xyz, int64
     gdn::launch_knn(P, prm.k, ctx->num_cus, st);
     if (ce) (void)hipEventRecord(ce->ev[2], st);
     gdn::launch_knn_merge(P, prm, ctx->num_cus, st);
-    gdn::launch_leaf_select(P, prm, xyz, st);
+    gdn::launch_leaf_select(P, prm, st);
     bool written = false;  // outputs already written by the top-lambda pass
     if (prm.stages & GDN_STAGE_SCORE) {
         gdn::launch_score(P, prm, st);

@@ -456,9 +456,6 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t m) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Block exclusive scan of one value per thread (blockDim multiple of 64, <= 1024).
-// `smem` needs blockDim/64 + 1 words. Returns the exclusive prefix; *total gets
-// the block sum. Contains __syncthreads.
 // Workgroups are dealt to the chip's eight XCDs in turn (workgroup b runs on
 // XCD b % 8). xcd_part gives the workgroups of one XCD one contiguous eighth
 // of [0, n) to stride through: a kernel over sorted positions that gathers
@@ -478,6 +475,9 @@ __device__ __forceinline__ XcdPart xcd_part(uint32_t n) {
 }
 inline unsigned xcd_grid(unsigned blocks) { return (blocks + N_XCD - 1u) / N_XCD * N_XCD; }
 
+// Block exclusive scan of one value per thread (blockDim multiple of 64, <= 1024).
+// `smem` needs blockDim/64 + 1 words. Returns the exclusive prefix; *total gets
+// the block sum. Contains __syncthreads.
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* smem, uint32_t* total) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const uint32_t inc = wave_incl_scan(v);

@@ -3,13 +3,13 @@
 // denoised cloud, PSNR (Eq. 29) and the Chamfer distance (Eq. 30).
 //
 // Nearest, by groups (the second half of this file): both clouds in Hilbert
-// order, the reference in groups of 32 points with boxes; a wave of 64
-// neighbouring queries evaluates only the groups whose box lies within some
+// order, the reference in groups of 64 points with boxes; a wave takes 16
+// neighbouring queries and evaluates only the groups whose box lies within some
 // query's best distance so far.
-// Nearest, brute force (small clouds, or a workspace too small for the
-// groups): one thread per query point, the reference cloud
-// streamed through LDS in tiles; the reference is split into chunks over a
-// second grid dimension so that small query sets still fill the chip, and the
+// Nearest, brute force (where sorting does not pay, or a workspace too small for
+// the groups): one thread per query point, the reference cloud
+// streamed through LDS in tiles; the reference is split into chunks, each with
+// workgroups of its own, so that small query sets still fill the chip, and the
 // chunks' answers are combined with a 64-bit atomic minimum on the key
 // (fp32 d2 bits << 32 | index): d2 >= 0, so the bit order is the value
 // order, and equal distances resolve to the smaller index.

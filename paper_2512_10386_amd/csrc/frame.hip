@@ -755,48 +755,47 @@ __global__ __launch_bounds__(SEG_BLOCK) void deep_cells_kernel(Plan P, uint32_t 
     constexpr uint32_t U = 4;
     const uint32_t stride = gridDim.x * SEG_BLOCK;  // (at most 2^20)
     for (uint32_t base0 = blockIdx.x * SEG_BLOCK; base0 < P.n; base0 += U * stride) {
-    // (four flags per load; they are padded with zeros past n)
-    static_assert(U * SEG_BLOCK == 4 * SEG_BLOCK, "a load per thread covers the rounds");
-    const uint32_t s4 = base0 + threadIdx.x / (SEG_BLOCK / U) * stride + threadIdx.x % (SEG_BLOCK / U) * 4u;
-    const uint32_t f4 = s4 < P.n ? *(const uint32_t*)(P.deepf + s4) : 0u;
-    if (!__syncthreads_or((int)(f4 & 0x02020202u))) continue;
-    for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t base = base0 + u * stride;
-        if (base >= P.n) break;
-        if (threadIdx.x == 0) s_nseg = 0u;
-        __syncthreads();
-        const uint32_t s = base + threadIdx.x;
-        if (s < P.n && P.deepf[s] == 2u) {
-            uint32_t fs, fe;
-            const uint32_t f = frame_range(P, s_foff, lds, s, &fs, &fe);
-            const uint64_t c = P.keys_a[s] >> CELL_SHIFT;
-            // the cell's end: doubling steps, then a search of the last one
-            uint32_t lo = s, step = 64u;
-            while (fe - lo > step && (P.keys_a[lo + step] >> CELL_SHIFT) == c) {
-                lo += step;
-                step *= 2u;
+        // (four flags per load, a load per thread; they are padded with zeros past n)
+        const uint32_t s4 = base0 + threadIdx.x / (SEG_BLOCK / U) * stride + threadIdx.x % (SEG_BLOCK / U) * 4u;
+        const uint32_t f4 = s4 < P.n ? *(const uint32_t*)(P.deepf + s4) : 0u;
+        if (!__syncthreads_or((int)(f4 & 0x02020202u))) continue;
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t base = base0 + u * stride;
+            if (base >= P.n) break;
+            if (threadIdx.x == 0) s_nseg = 0u;
+            __syncthreads();
+            const uint32_t s = base + threadIdx.x;
+            if (s < P.n && P.deepf[s] == 2u) {
+                uint32_t fs, fe;
+                const uint32_t f = frame_range(P, s_foff, lds, s, &fs, &fe);
+                const uint64_t c = P.keys_a[s] >> CELL_SHIFT;
+                // the cell's end: doubling steps, then a search of the last one
+                uint32_t lo = s, step = 64u;
+                while (fe - lo > step && (P.keys_a[lo + step] >> CELL_SHIFT) == c) {
+                    lo += step;
+                    step *= 2u;
+                }
+                const uint32_t e = cell_lower_bound(P.keys_a, lo + 1u, fe - lo > step ? lo + step : fe, c + 1u);
+                const uint32_t slot = atomicAdd(&s_nseg, 1u);
+                s_seg[slot] = make_uint2(s, e);
+                s_deep[slot] = (uint8_t)(P.fc[f].dmax > SORT_SHORT_LEVEL && e - s > cap);
             }
-            const uint32_t e = cell_lower_bound(P.keys_a, lo + 1u, fe - lo > step ? lo + step : fe, c + 1u);
-            const uint32_t slot = atomicAdd(&s_nseg, 1u);
-            s_seg[slot] = make_uint2(s, e);
-            s_deep[slot] = (uint8_t)(P.fc[f].dmax > SORT_SHORT_LEVEL && e - s > cap);
-        }
-        __syncthreads();
-        const uint32_t ns = s_nseg;
-        for (uint32_t g = threadIdx.x >> 6; g < ns; g += SEG_BLOCK / 64)
-            if (s_seg[g].y - s_seg[g].x <= 64u)
-                sort_cell_wave(P, s_seg[g].x, s_seg[g].y, s_deep[g] != 0u, threadIdx.x & 63u);
-        for (uint32_t g = 0; g < ns; ++g) {
-            const uint2 r = s_seg[g];
-            if (r.y - r.x <= 64u) continue;
-            if (r.y - r.x <= SEG_LDS)
-                sort_cell_lds(P, r.x, r.y, s_deep[g] != 0u, s_k, s_v, s_base, s_w, s_scan);
-            else
-                sort_cell(P, r.x, r.y, s_deep[g] != 0u, s_base, s_w, s_scan);
+            __syncthreads();
+            const uint32_t ns = s_nseg;
+            for (uint32_t g = threadIdx.x >> 6; g < ns; g += SEG_BLOCK / 64)
+                if (s_seg[g].y - s_seg[g].x <= 64u)
+                    sort_cell_wave(P, s_seg[g].x, s_seg[g].y, s_deep[g] != 0u, threadIdx.x & 63u);
+            for (uint32_t g = 0; g < ns; ++g) {
+                const uint2 r = s_seg[g];
+                if (r.y - r.x <= 64u) continue;
+                if (r.y - r.x <= SEG_LDS)
+                    sort_cell_lds(P, r.x, r.y, s_deep[g] != 0u, s_k, s_v, s_base, s_w, s_scan);
+                else
+                    sort_cell(P, r.x, r.y, s_deep[g] != 0u, s_base, s_w, s_scan);
+                __syncthreads();
+            }
             __syncthreads();
         }
-        __syncthreads();
-    }
     }
 }
 

@@ -35,15 +35,15 @@ void launch_knn(const Plan& P, int k, int num_cus, hipStream_t st);
 void launch_knn_merge(const Plan& P, const Params& prm, int num_cus, hipStream_t st);
 
 // score.hip: density with percentile/median, score, top-lambda, outputs
-void launch_leaf_select(const Plan& P, const Params& prm, const float* xyz, hipStream_t st);
+void launch_leaf_select(const Plan& P, const Params& prm, hipStream_t st);
 void launch_score(const Plan& P, const Params& prm, hipStream_t st);
 // bigleaf.hip: the same steps (and the voxel filter) where leaves are big
 struct ToplOut;
 void launch_big_voxel(const Plan& P, const Params& prm, hipStream_t st);
 void launch_big_select(const Plan& P, const Params& prm, hipStream_t st);
 void launch_big_topl(const Plan& P, double lambda, const ToplOut& out, hipStream_t st);
-// Returns true when top-lambda also wrote keep, score and stage (single
-// frames); launch_outputs then only builds the kept list.
+// Returns true when it wrote the outputs too (keep, score and stage, or large
+// inputs' packed records); launch_outputs then only builds the kept list.
 bool launch_topl(const Plan& P, const Params& prm, uint8_t* keep, float* score, uint8_t* stage, hipStream_t st);
 void launch_keep_p2(const Plan& P, hipStream_t st);
 void launch_outputs(const Plan& P, uint8_t* keep, float* score, uint8_t* stage,

@@ -442,14 +442,7 @@ __device__ __forceinline__ bool bucket_sort_u32(uint32_t (&key)[N], const float 
     for (int i = 0; i < N; ++i) c[i] = hist[i][lane];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        // inclusive scan over the wave: row shifts, then row broadcasts
-        uint32_t inc = c[i];
-        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false);  // row_shr:1
-        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false);  // row_shr:2
-        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false);  // row_shr:4
-        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false);  // row_shr:8
-        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false);  // row_bcast:15
-        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false);  // row_bcast:31
+        const uint32_t inc = wave_incl_scan(c[i]);
         c[i] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(hb[i] << 2), (int)(inc - c[i]));
     }
 #pragma unroll
@@ -580,26 +573,22 @@ __device__ __forceinline__ float flush(unsigned long long* __restrict__ lst,
     return bound_of((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)k - 1));
 }
 
-// k <= 32: the lists of two queries, one per 32-lane half (`two` = false:
-// only the lower half's query). Each half merges at most 32 pending keys.
-// Returns the new bounds of both through b0 / b1.
-template <bool POS>
+// k <= 32, buffers of keys: the final lists of two queries, one per 32-lane half
+// (`two` = false: only the lower half's query). Each half merges at most 32
+// pending keys.
 __device__ __forceinline__ void flush_half(unsigned long long* __restrict__ lst0,
-                                           const typename Pending<POS>::T* __restrict__ pend0,
-                                           uint32_t cnt0, unsigned long long self0, float4 q0,
-                                           unsigned long long* __restrict__ lst1,
-                                           const typename Pending<POS>::T* __restrict__ pend1,
-                                           uint32_t cnt1, unsigned long long self1, float4 q1, bool two,
-                                           uint32_t lane, uint32_t k, const float4* __restrict__ cand4, float* b0,
-                                           float* b1, bool fresh = false) {
+                                           const unsigned long long* __restrict__ pend0, uint32_t cnt0,
+                                           unsigned long long self0, unsigned long long* __restrict__ lst1,
+                                           const unsigned long long* __restrict__ pend1, uint32_t cnt1,
+                                           unsigned long long self1, bool two, uint32_t lane, uint32_t k, bool fresh) {
     wave_lds_fence();
     const bool up = lane >= 32u;
     const uint32_t h = lane & 31u;
     const bool act = !up || two;
     unsigned long long* const lst = up ? lst1 : lst0;
-    const typename Pending<POS>::T* const pend = up ? pend1 : pend0;
+    const unsigned long long* const pend = up ? pend1 : pend0;
     const uint32_t cnt = up ? cnt1 : cnt0;
-    unsigned long long v = act && h < cnt ? pending_key<POS>(cand4, pend, h, up ? q1 : q0) : KEY_EMPTY;
+    unsigned long long v = act && h < cnt ? pend[h] : KEY_EMPTY;
     if (v == (up ? self1 : self0)) v = KEY_EMPTY;
     if (fresh) {  // both lists hold only placeholders (see flush)
         v = ~sort32x2_desc(~v, lane);
@@ -610,9 +599,6 @@ __device__ __forceinline__ void flush_half(unsigned long long* __restrict__ lst0
     }
     if (act && h < k) lst[h] = v;
     wave_lds_fence();
-    const uint32_t hi = (uint32_t)(v >> 32);
-    *b0 = bound_of((uint32_t)__builtin_amdgcn_readlane((int)hi, (int)k - 1));
-    *b1 = bound_of((uint32_t)__builtin_amdgcn_readlane((int)hi, 32 + (int)k - 1));
 }
 
 // ---------------------------------------------------------------- kNN by culling groups
@@ -983,9 +969,7 @@ __global__ __launch_bounds__(64, WAVES) void knn_group_kernel(Plan P, const floa
                 const bool f0 = ((merged >> j) & 1ull) == 0ull;
                 const bool f1 = !two || ((merged >> j1) & 1ull) == 0ull;
                 if (c0 <= (uint32_t)PEND_HALF && c1 <= (uint32_t)PEND_HALF) {
-                    float b0, b1;
-                    flush_half<POS>(l0, p0, c0, sk0, q0, l0 + k, p0 + PEND, c1, sk1, q1, two, lane, k, cand4, &b0,
-                                    &b1, f0 && f1);
+                    flush_half(l0, p0, c0, sk0, l0 + k, p0 + PEND, c1, sk1, two, lane, k, f0 && f1);
                 } else {
                     if (c0) (void)flush<POS>(l0, p0, c0, lane, k, sk0, cand4, q0, f0);
                     if (c1) (void)flush<POS>(l0 + k, p0 + PEND, c1, lane, k, sk1, cand4, q1, f1);

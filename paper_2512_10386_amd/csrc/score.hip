@@ -31,8 +31,7 @@ __device__ __forceinline__ double seg_sum(double v, uint32_t kp) {
     return v;
 }
 
-__device__ __forceinline__ Dens density_at(const Plan& P, const float* __restrict__ xyz, uint32_t k, uint32_t qi) {
-    (void)xyz;
+__device__ __forceinline__ Dens density_at(const Plan& P, uint32_t k, uint32_t qi) {
     return density_finish(P, k, qi, density_load(P, qi));
 }
 
@@ -132,7 +131,7 @@ __device__ T block_select(Get get, uint32_t cnt, uint32_t r, uint32_t (*s_hist)[
 // Given a = the value of ascending rank r, the value of rank r + 1: a again
 // if more than r + 1 values are <= a, else the smallest value above a.
 template <typename T, class Get>
-__device__ T block_next_rank(Get get, uint32_t cnt, uint32_t r, T a, uint32_t* s_sel) {
+__device__ T block_next_rank(Get get, uint32_t cnt, uint32_t r, T a) {
     __shared__ uint32_t s_le[SEL_BLOCK / 64];
     __shared__ T s_mn[SEL_BLOCK / 64];
     uint32_t le = 0;
@@ -157,7 +156,6 @@ __device__ T block_next_rank(Get get, uint32_t cnt, uint32_t r, T a, uint32_t* s
         M = s_mn[q] < M ? s_mn[q] : M;
     }
     __syncthreads();
-    (void)s_sel;
     return L > r + 1u ? a : M;
 }
 
@@ -221,7 +219,7 @@ __device__ void leaf_median(HG rho, uint32_t n1, double* med, uint32_t (*s_hist)
         *med = __longlong_as_double((long long)block_select<unsigned long long>(rho, n1, (n1 - 1) / 2, s_hist, s_sel));
     } else {
         const unsigned long long ab = block_select<unsigned long long>(rho, n1, n1 / 2 - 1, s_hist, s_sel);
-        const unsigned long long bb = block_next_rank<unsigned long long>(rho, n1, n1 / 2 - 1, ab, s_sel);
+        const unsigned long long bb = block_next_rank<unsigned long long>(rho, n1, n1 / 2 - 1, ab);
         *med = (__longlong_as_double((long long)ab) + __longlong_as_double((long long)bb)) / 2.0;
     }
 }
@@ -232,8 +230,7 @@ __device__ void leaf_median(HG rho, uint32_t n1, double* med, uint32_t (*s_hist)
 // same values, stored twice); the two selects, each a chain of
 // barrier-separated passes, then run at the same time instead of in turn.
 template <bool SQRT>
-__global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params prm, bool small,
-                                                               const float* __restrict__ xyz) {
+__global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params prm, bool small) {
     __shared__ uint32_t s_hist[SEL_HISTS][256];
     __shared__ uint32_t s_sel[SEL_SCRATCH];
     __shared__ uint32_t s_r2[SEL_LDS_MAX];
@@ -322,7 +319,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params p
         }
         if (n1 <= SEL_LDS_MAX) {
             for (uint32_t i = threadIdx.x; i < n1; i += blockDim.x) {
-                const Dens dn = density_at(P, xyz, (uint32_t)k, qb + i);
+                const Dens dn = density_at(P, (uint32_t)k, qb + i);
                 if (role == 0u) s_r2[i] = __float_as_uint(dn.r2);
                 else s_rho[i] = (unsigned long long)__double_as_longlong(dn.rho);
             }
@@ -330,7 +327,7 @@ __global__ __launch_bounds__(SEL_BLOCK) void leaf_select_kernel(Plan P, Params p
             if (role == 0u) cut = leaf_cut(LdsBits<uint32_t>{s_r2}, n1, prm.rho_percentile, s_hist, s_sel);
             else leaf_median(LdsBits<unsigned long long>{s_rho}, n1, &med, s_hist, s_sel);
         } else {
-            for (uint32_t i = threadIdx.x; i < n1; i += blockDim.x) (void)density_at(P, xyz, (uint32_t)k, qb + i);
+            for (uint32_t i = threadIdx.x; i < n1; i += blockDim.x) (void)density_at(P, (uint32_t)k, qb + i);
             __syncthreads();
             if (role == 0u) cut = leaf_cut(R2Bits{P.r2k, qb}, n1, prm.rho_percentile, s_hist, s_sel);
             else leaf_median(RhoBits{P.rho_c, qb}, n1, &med, s_hist, s_sel);
@@ -399,7 +396,7 @@ __device__ __forceinline__ unsigned long long wave_next_rank(const WaveVals& w, 
 }
 
 template <bool SQRT>
-__global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params prm, const float* __restrict__ xyz) {
+__global__ __launch_bounds__(256) void leaf_select_small_kernel(Plan P, Params prm) {
     __shared__ uint32_t s_hist[4][256];
     uint32_t* const hist = s_hist[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;
@@ -487,7 +484,7 @@ static unsigned big_leaf_blocks(const Plan& P, const Params& prm, bool small) {
     return P.n < 2048u ? P.n : 2048u;
 }
 
-void launch_leaf_select(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
+void launch_leaf_select(const Plan& P, const Params& prm, hipStream_t st) {
     if (P.big_leaves) {
         launch_big_select(P, prm, st);
         return;
@@ -498,11 +495,11 @@ void launch_leaf_select(const Plan& P, const Params& prm, const float* xyz, hipS
         unsigned wb = (P.n / 128 + 3) / 4;
         if (wb > 8192) wb = 8192;
         hipLaunchKernelGGL(sq ? leaf_select_small_kernel<true> : leaf_select_small_kernel<false>, dim3(wb), dim3(256),
-                           0, st, P, prm, xyz);
+                           0, st, P, prm);
     }
     const unsigned blocks = big_leaf_blocks(P, prm, small);
     hipLaunchKernelGGL(sq ? leaf_select_kernel<true> : leaf_select_kernel<false>, dim3(2 * blocks), dim3(SEL_BLOCK), 0,
-                       st, P, prm, small, xyz);
+                       st, P, prm, small);
 }
 
 // ---------------------------------------------------------------- score

@@ -100,13 +100,15 @@ __device__ __forceinline__ void run_step(uint32_t leaf, float (&m)[6]) {
 // sizes each kernel of the general path (box, keys, four sort passes, two for
 // deep cells, leaf borders, their scan) takes the few microseconds that any
 // launch and its first loads take, so one workgroup that keeps the points on
-// chip is faster than ten launches over the whole chip. Whole calls, general
-// path and this one: 65 points 72.5 and 49.5 us, 500 76 and 53, 1501 91 and 67.
-// Most of it is the sort: a pass is six barriers over 16 waves, 3 us.
+// chip is faster than ten launches over the whole chip. Whole calls of a scanned
+// object, general path and this one: 65 points 66.5 and 49.6 us, 500 74.6 and
+// 52.9, 1501 88.3 and 66.3, 3000 98.2 and 85.0, 4096 102.5 and 91.5. Most of it is
+// the sort: a pass is six barriers over 16 waves, 3 us.
 // P1: the voxel filter and the P1 compaction too, by all threads over the
 // points (leaf boxes, then hash tables, in the LDS that the sort is done with):
-// 500 points 63.6 us a call without and 56.4 with it, 1501 74.2 and 71.3, but
-// 4096, where a workgroup per leaf does more at once, 98.1 and 101.0.
+// 500 points 59.1 us a call without and 52.9 with it, 1501 68.2 and 66.3, 2048
+// 73.7 and 70.4, but 3000 84.9 and 85.7, 4096, where a workgroup per leaf does
+// more at once, 91.4 and 94.1.
 template <int ITEMS, bool P1>
 __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __restrict__ xyz, Plan P,
                                                                  double min_leaf_side, uint32_t cap, double beta,
@@ -440,8 +442,8 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_tree_kernel(const float* __
 }
 
 // One frame of so few points that the workgroup is done sooner than the chip
-// (3000 points 102 us the general way and 87.5 this way, 4096 107 and 94, but
-// 6000 106 and 108, with eight points per thread).
+// (4096 points 102.5 us the general way and 91.5 this way, but 6000 106.7 and
+// 109.4, with eight points per thread).
 bool small_tree(const Plan& P) { return P.nf == 1 && P.n <= 4u * SMALL_BLOCK; }
 
 void launch_small_tree(const Plan& P, const Params& prm, const float* xyz, hipStream_t st) {
