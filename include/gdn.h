@@ -211,14 +211,15 @@ gdn_status gdn_autotune(gdn_ctx *ctx, gdn_params *p, const int32_t *caps, int nc
  *     refused with GDN_ECAPACITY, an empty one with GDN_EINVAL.
  *   gdn_server_poll retires finished batches, then packs waiting frames (in
  *     arrival order) into every free slot and launches them; it never waits
- *     for the GPU. It reports up to max_done finished tickets, and optionally
- *     (done_status, NULL ok) for each the device status word (GDN_DEV_*) of
- *     the batch it ran in: non-zero means that batch's outputs are
- *     unspecified; and optionally the queue length and the number of busy
- *     slots.
+ *     for the GPU, unless a launch fails. It reports up to max_done finished
+ *     tickets, and optionally (done_status, NULL ok) for each the device
+ *     status word (GDN_DEV_*) of the batch it ran in: non-zero means that
+ *     batch's outputs are unspecified; and optionally the queue length and
+ *     the number of busy slots.
  * Results of a frame equal those of gdn_denoise on it alone. Not thread-safe;
- * poll from one thread. Requests whose batch could not be started stay queued;
- * after a GDN_EHIP from poll the server is otherwise unusable.
+ * poll from one thread. Requests whose batch could not be started stay queued,
+ * and what poll had enqueued of it has ended when poll returns the error. After
+ * an error of the GPU itself the server is unusable.
  * Destroy waits for running slots, drops frames still queued and frees the
  * slots; destroy the server before its context. GDN_ENOMEM from create if
  * the budget holds no slot (gdn_server_info gives the bytes per slot).

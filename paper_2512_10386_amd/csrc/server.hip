@@ -268,7 +268,12 @@ gdn_status gdn_server_poll(gdn_server* s, int64_t* done_tickets, uint32_t* done_
         if (s->waiting.empty()) break;
         if (sl.busy) continue;
         const gdn_status st = launch_slot(s, sl);
-        if (st != GDN_OK) return st;
+        if (st != GDN_OK) {
+            // what was enqueued all the same still reads the slot's request table, which the next
+            // batch rewrites, and the callers' frames, whose requests another slot may finish first
+            (void)hipStreamSynchronize(sl.stream);
+            return st;
+        }
     }
     const int k = std::min<int>((int)s->done.size(), std::max(max_done, 0));
     for (int i = 0; i < k; ++i) {
