@@ -249,9 +249,9 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 //
 // Bound by the latency of the chain (search the key, seeds, supers, groups,
 // points) and, on large clouds, by the pair evaluations: the metrics of a 120k
-// LiDAR sweep (114k against 111k points) take 148 us, 64 of them here, 16 the
-// far queries, 51 the keys and the sort; all pairs took 5162 us at 2.6 ms per
-// direction. 16k against 16k points: 75 us, 136 before.
+// LiDAR sweep (114k against 111k points) take 143 us, 65 of them here, 18 the
+// far queries, 56 the boxes, the keys and the sort; all pairs take 5162 us at
+// 2.6 ms per direction. 16k against 16k points: 71 us, 119 by all pairs.
 
 constexpr int NN_GRP = 64;                      // points per group (one per lane)
 constexpr int NN_SUP = 64 * NN_GRP;             // points per super
